@@ -399,7 +399,7 @@ bh_status bh_graph_capture_learned(bh_ctx *ctx, int32_t n_systems, const int64_t
  * target_b)^2 / sum_b w_b with theta_b the network output at shift 0 (FP32
  * throughout).  x device FP32 [batch][12], target and weight device FP32
  * [batch] (weights >= 0, positive sum); grad device FP32 [BH_MLP_PARAMS]
- * (summed over the batch in sample order); loss device FP32 [1], nullable.
+ * (summed over the batch in a fixed order); loss device FP32 [1], nullable.
  * batch in [1, 65536]. */
 bh_status bh_mlp_grad(bh_ctx *ctx, const bh_mlp *net, int32_t batch, const float *x, const float *target,
                       const float *weight, float *grad, float *loss);

@@ -1177,20 +1177,10 @@ bh_status bh_mlp_grad(bh_ctx *c, const bh_mlp *net, int32_t batch, const float *
   if (st) return st;
   if (batch < 1 || batch > 65536) return fail(c, BH_EINVAL, "batch must be in [1, 65536]");
   if (!x || !target || !weight || !grad) return fail(c, BH_EINVAL, "x, target, weight and grad must not be NULL");
-  const size_t per = BH_MLP_FEATURES + 4 * BH_MLP_HIDDEN + 2;
-  st = ensure(c, c->mlp_work, sizeof(float) * (per * (size_t)batch + 1), "training workspace");
+  st = ensure(c, c->mlp_work, mlp_part_bytes(batch), "training workspace");
   if (st) return st;
-  float *w = P<float>(c->mlp_work);
-  MlpWork ws{};
-  ws.xn = w;
-  ws.h1 = ws.xn + (size_t)batch * BH_MLP_FEATURES;
-  ws.h2 = ws.h1 + (size_t)batch * BH_MLP_HIDDEN;
-  ws.dz1 = ws.h2 + (size_t)batch * BH_MLP_HIDDEN;
-  ws.dz2 = ws.dz1 + (size_t)batch * BH_MLP_HIDDEN;
-  ws.dy = ws.dz2 + (size_t)batch * BH_MLP_HIDDEN;
-  ws.loss = ws.dy + batch;
-  ws.wsum = ws.loss + batch;
-  mlp_grad_device(net->params, net->mu, net->sigma, batch, x, target, weight, ws, grad, loss, c->stream);
+  mlp_grad_device(net->params, net->mu, net->sigma, batch, x, target, weight, P<float>(c->mlp_work), grad, loss,
+                  c->stream);
   return hip_check(c, hipGetLastError(), "kernel launch (training)");
 }
 

@@ -515,13 +515,11 @@ void reset_info_device(DevInfo *info, hipStream_t s);
 // k_mlp.hip: per-group theta from a 12 -> 64 -> 64 -> 1 network
 constexpr int kMlpParams = 64 * 12 + 64 + 64 * 64 + 64 + 64 + 1;
 constexpr float kThetaMin = 0.3f, kThetaSpan = 0.7f;
-struct MlpWork {  // per-sample activations and gradients of a training batch
-  float *xn, *h1, *h2, *dz1, *dz2, *dy, *loss, *wsum;
-};
 void mlp_infer_device(const float *params, const float *mu, const float *sigma, const float *x, int64_t rows,
                       int64_t cap_rows, const DevInfo *info, float shift, float *theta, hipStream_t s);
+size_t mlp_part_bytes(int B);  // partial gradients of a training batch
 void mlp_grad_device(const float *params, const float *mu, const float *sigma, int B, const float *x,
-                     const float *target, const float *w, MlpWork ws, float *grad, float *loss, hipStream_t s);
+                     const float *target, const float *w, float *part, float *grad, float *loss, hipStream_t s);
 void adam_device(float *params, const float *grad, float *m, float *v, int n, float lr, float b1, float b2, float eps,
                  int step, hipStream_t s);
 

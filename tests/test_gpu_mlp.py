@@ -154,6 +154,29 @@ def test_gradient_matches_oracle(gpu, batch):
     assert np.abs(g - g_ref).max() <= 1e-4 * np.abs(g_ref).max()
 
 
+@pytest.mark.parametrize("batch", [15, 16, 17, 4095, 4097, 8209, 65536])
+def test_gradient_over_tiles_of_samples(gpu, batch):
+    """Sample tiles of 16: partly filled ones, the largest grid of one tile a
+    block (4096 samples) and several tiles a block.  The FP32 sums run over
+    far fewer terms in a row than the batch, so the bound of the plain test
+    (1e-4 of the norm) holds at every size; the loss is a weighted mean of
+    positive terms, each rounded a few times: 1e-5."""
+    bh = gpu
+    p, mu, sigma = _net(15)
+    rng = np.random.default_rng(batch)
+    x = (rng.normal(size=(batch, 12)) * 2.0).astype(np.float32)
+    t = rng.uniform(0.3, 1.0, batch).astype(np.float32)
+    w = rng.uniform(0.5, 50.0, batch).astype(np.float32)
+    c = bh.Context()
+    g, loss = c.mlp_grad(_f32(p), _f32(mu), _f32(sigma), _f32(x), _f32(t), _f32(w))
+    l_ref, g_ref = mlp.loss_and_grad(p, x.astype(np.float64), mu.astype(np.float64), sigma.astype(np.float64),
+                                     t.astype(np.float64), w.astype(np.float64))
+    g = g.cpu().numpy().astype(np.float64)
+    assert abs(float(loss.cpu()[0]) - l_ref) <= 1e-5 * l_ref
+    assert np.linalg.norm(g - g_ref) <= 1e-4 * np.linalg.norm(g_ref)
+    assert np.abs(g - g_ref).max() <= 1e-4 * np.abs(g_ref).max()
+
+
 def test_adam_matches_oracle(gpu):
     bh = gpu
     n = mlp.N_PARAMS
