@@ -171,15 +171,30 @@ __global__ __launch_bounds__(256) void k_energy_partial(int64_t n, const double 
   }
 }
 
-__global__ void k_energy_final(const double *__restrict__ part, int nb, double *__restrict__ out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// One block: thread t adds partials t, t + 256, ..., then a tree over the
+// threads (one thread adding all 1024 in a row took 82 us, a load's latency a
+// term; this takes 5).
+__global__ __launch_bounds__(256) void k_energy_final(const double *__restrict__ part, int nb,
+                                                      double *__restrict__ out) {
+  __shared__ double red[2][256];
+  const int t = threadIdx.x;
   double a = 0.0, b = 0.0;
-  for (int k = 0; k < nb; ++k) {
+#pragma unroll 4
+  for (int k = t; k < nb; k += 256) {
     a += part[2 * k];
     b += part[2 * k + 1];
   }
-  out[0] = a;
-  out[1] = b;
+  red[0][t] = a;
+  red[1][t] = b;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (t < w) {
+      red[0][t] += red[0][t + w];
+      red[1][t] += red[1][t + w];
+    }
+    __syncthreads();
+  }
+  if (t < 2) out[t] = red[t][0];
 }
 
 }  // namespace
@@ -244,7 +259,7 @@ size_t energy_part_bytes() { return (size_t)kEnergyBlocks * 2 * sizeof(double); 
 void energy_device(int64_t n, const double *vel, const double *mass, const float *pot, double *part, double *out,
                    hipStream_t s) {
   k_energy_partial<<<kEnergyBlocks, 256, 0, s>>>(n, vel, mass, pot, part);
-  k_energy_final<<<1, 64, 0, s>>>(part, kEnergyBlocks, out);
+  k_energy_final<<<1, 256, 0, s>>>(part, kEnergyBlocks, out);
 }
 
 }  // namespace bh
