@@ -64,6 +64,18 @@ __device__ __forceinline__ double shfl_xor_d(double v, int mask) {
   return *reinterpret_cast<double *>(&a);
 }
 
+__device__ __forceinline__ double shfl_d(double v, int lane) {
+  int2 a = *reinterpret_cast<int2 *>(&v);
+  a.x = __shfl(a.x, lane, kWave);
+  a.y = __shfl(a.y, lane, kWave);
+  return *reinterpret_cast<double *>(&a);
+}
+
+__device__ __forceinline__ int64_t shfl_i64(int64_t v, int lane) {
+  const int lo = __shfl((int)(uint32_t)v, lane, kWave), hi = __shfl((int)(v >> 32), lane, kWave);
+  return ((int64_t)hi << 32) | (uint32_t)lo;
+}
+
 // Octal digits shared by two 63-bit keys (21 when equal).
 __device__ __forceinline__ int common_digits(uint64_t a, uint64_t b) {
   uint64_t x = a ^ b;

@@ -87,6 +87,25 @@ def test_neighbors_any_grouping(gpu, n_crit):
     _check(ref, cnt, rho, None, None)
 
 
+@pytest.mark.parametrize("n_crit", [8, 32, 33, 64, 65, 200])
+@pytest.mark.parametrize("power", [-300, 0, 300])
+def test_neighbors_scan_bounds(gpu, n_crit, power):
+    """Radii from 1e-6 to 0.3 side by side in one group, at scales whose FP32
+    distances underflow to 0, are ordinary, and overflow: the marks of the
+    FP32 scan must never lose a neighbour.  Member counts on both sides of 32
+    (shared and unshared candidates) and of 64.  All by the exact scaling of
+    the FP64 decision: counts and sets equal, densities 8^-power times."""
+    rng = np.random.default_rng(n_crit)
+    n = 1500
+    pos = rng.uniform(-1.0, 1.0, (n, 3))
+    pos[n // 2:] = pos[:n - n // 2] * (1.0 + 1e-7)  # near twins, around the smallest radii
+    mass = rng.uniform(0.5, 2.0, n)
+    h = np.exp(rng.uniform(np.log(1e-6), np.log(0.3), n))
+    ref = oracle.neighbors(pos, mass, h, lists=True)
+    cnt, rho, off, nbr, _ = _run(gpu, np.ldexp(pos, power), mass, np.ldexp(h, power), n_crit)
+    _check(ref, cnt, np.ldexp(rho, 3 * power), off, nbr)
+
+
 def test_neighbors_lattice_strict_and_empty(gpu):
     lat = _lattice(6)
     # radius exactly 1: the six lattice neighbours are at distance 1, not < 1
