@@ -85,9 +85,9 @@ typedef struct {
   int32_t n_groups_calls;
   int32_t n_walk_calls;
   int32_t n_force_calls;
-  int32_t n_split_groups;  /* last force call: groups whose walk was handed over to several waves */
+  int32_t n_split_groups;  /* last force call: groups whose walk was shared by several waves or workgroups */
   int32_t n_segments;      /* last force call: list segments of those groups */
-  int32_t n_split_levels;  /* last force call: deepest hand-over level of a split walk (0: none) */
+  int32_t n_split_levels;  /* last force call: deepest hand-over level of a shared walk (0: none) */
   int32_t n_walk_attempts; /* last force call: walks run (more than 1 when a list pool had to grow) */
   double t_particle_ms;     /* per-particle walk calls (thread pointers, walk and sum) */
   int32_t n_particle_calls;
@@ -109,17 +109,15 @@ typedef struct {
   int32_t split_visits;  /* a group walk that has tested this many nodes hands the rest of its
                             stack to up to 16 new walk tasks, which waves with no group left
                             take in the same launch, so that long lists are walked and summed
-                            by several waves; tasks 5 hand-overs deep walk to the end (0:
-                            default, automatic: a single system is not split (its walk then
-                            runs without the split machinery, which is faster); a batch
-                            splits at 16 per particle of a walk wave, i.e.
-                            16 n / (CUs x walk waves per CU), at least 12288, and at least 4
-                            times the mean list length of the previous force call on the
-                            context, so that only outlier walks split; -1: never; else
-                            >= 64, exactly).  Results do not depend on when or where the
-                            tasks ran, only on the cap (with the automatic cap, two calls on
-                            the same input agree bit for bit when their previous calls had
-                            lists of the same mean length). */
+                            by several waves; tasks 5 hand-overs deep walk to the end (>= 64,
+                            exactly; -1: never).  0 (default): no hand-over by visits; groups
+                            whose walk is several times an ordinary one's at their theta
+                            (outliers, a few per system) are walked and summed by many
+                            workgroups, and with the other tuning options at their defaults
+                            trees of up to 2048 n_crit particles (n_crit >= 16) are walked by a
+                            workgroup per group.  Results do not depend on when or where a
+                            walk ran, only on the input and this option; up to FP32 rounding
+                            (the order in which a list is summed) not on the option either. */
   int32_t quadrupole;    /* 1: builds also compute every cell's second mass moments S about its
                             centre of mass (bottom-up, parallel axes, FP64), and bh_compute_forces
                             and bh_compute_forces_batch add to each cell entry of a list the
@@ -222,9 +220,9 @@ bh_status bh_compute_forces(bh_ctx *ctx, double eps, double theta, const float *
 
 /* Same with per-system parameters: eps_sys, theta_sys host FP64 [n_systems].
  * A system's results equal, bit for bit, those of the same system run alone
- * with the same split-walk visit cap (the automatic cap depends on the total
- * particle count and the previous call, so give bh_options.split_visits a
- * fixed value for that). */
+ * with the same split-walk visit cap (by default how a group is walked depends
+ * on the total particle count, so give bh_options.split_visits a fixed value
+ * or -1 for that). */
 bh_status bh_compute_forces_batch(bh_ctx *ctx, const double *eps_sys, const double *theta_sys,
                                   const float *theta_group, float *acc, float *pot);
 
@@ -305,7 +303,11 @@ bh_status bh_direct_sampled_noalloc(bh_ctx *ctx, int64_t n, const double *pos, c
 
 /* ---- time integration (kick-drift-kick leapfrog, FP64 state) ----------- */
 
-/* vel += dt * acc (acc FP32 [n][3] from a force call, vel FP64 [n][3]). */
+/* vel += dt * acc (acc FP32 [n][3] from a force call, vel FP64 [n][3]).
+ * From the first bh_kick, bh_drift or bh_leapfrog step on a context, its force
+ * calls walk each group by one wave at every size (as with split_visits -1):
+ * a trajectory then has one order of its FP32 sums from end to end, whether
+ * its steps are issued by hand or by bh_leapfrog. */
 bh_status bh_kick(bh_ctx *ctx, int64_t n, double *vel, const float *acc, double dt);
 
 /* pos += dt * vel (both FP64 [n][3]). */

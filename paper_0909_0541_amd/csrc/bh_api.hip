@@ -258,7 +258,7 @@ static bh_status check_device_errors(bh_ctx *c) {
   if (e & kErrTheta) return fail(c, BH_EINVAL, "per-group theta outside [0, 1]");
   if (e & kErrBuild) return fail(c, BH_EINTERNAL, "tree build produced an inconsistent node layout");
   if (e & kErrStack) return fail(c, BH_EINTERNAL, "walk stack capacity exceeded or node range corrupt");
-  if (e & kErrPool) return fail(c, BH_EINTERNAL, "interaction list pool exhausted");
+  if (e & (kErrPool | kErrWide)) return fail(c, BH_EINTERNAL, "interaction list pool exhausted");
   if (e & kErrWait) return fail(c, BH_EINTERNAL, "a bounded device wait timed out (walk task or sort look-back)");
   if (e & kErrRadius) return fail(c, BH_EINVAL, "search radius h must be positive and finite");
   if (e & kErrListSpace) return fail(c, BH_EINVAL, "neighbour list offsets do not match the neighbour counts");
@@ -407,7 +407,9 @@ void bh_destroy(bh_ctx *c) {
                     &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_next, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
                     &c->split_ctr, &c->gsplit, &c->gnseg, &c->gsegfirst, &c->skeys[0], &c->skeys[1], &c->svals[0],
                     &c->svals[1], &c->shist, &c->sscan, &c->srows, &c->spbase, &c->sgroups, &c->psum,
-                    &c->qmom, &c->qpack, &c->far_slot, &c->walk_hist};
+                    &c->wide_pool, &c->wide_slot, &c->wide_gblocks, &c->wide_gstat, &c->wide_binfo, &c->wide_psum,
+                    &c->out_groups, &c->out_info, &c->out_nodes, &c->out_tasks, &c->out_rows, &c->out_near, &c->out_mass,
+                    &c->qmom, &c->qpack, &c->far_slot};
   for (DevBuf *b : bufs) free_buf(*b);
   if (c->graph) (void)hipGraphExecDestroy(c->graph);
   if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
@@ -415,6 +417,7 @@ void bh_destroy(bh_ctx *c) {
   if (c->stage) (void)hipHostFree(c->stage);
   if (c->split_host) (void)hipHostFree(c->split_host);
   if (c->stage_event) (void)hipEventDestroy(c->stage_event);
+  if (c->info_event) (void)hipEventDestroy(c->info_event);
   Timer *ts[] = {&c->t_build, &c->t_groups, &c->t_walk, &c->t_force, &c->t_particle, &c->t_neighbor, &c->t_theta};
   for (Timer *t : ts)
     for (hipEvent_t e : t->ev) (void)hipEventDestroy(e);
@@ -501,7 +504,7 @@ bh_status bh_make_groups(bh_ctx *c, int32_t n_crit, int64_t *n_groups_out) {
   B.scan_tmp = c->scan_tmp.p;
   B.num_cu = c->num_cu;
   make_groups_device(B, c->stream);
-  c->xq_clean = true;
+  c->xq_clean = c->counters_clean = true;
   st = timer_stop(c, c->t_groups);
   if (st) return st;
   st = hip_check(c, hipGetLastError(), "kernel launch (groups)");
@@ -515,6 +518,176 @@ bh_status bh_make_groups(bh_ctx *c, int32_t n_crit, int64_t *n_groups_out) {
     if (st) return st;
     *n_groups_out = c->info_host->n_groups;
   }
+  return BH_OK;
+}
+
+// The workgroup walk and list blocks (k_wide.hip) against the single-wave
+// walk and lists (k_walk.hip, k_force.hip): up to about 3000 groups, that is
+// 2048 n_crit particles, the former are faster, being even in their work;
+// beyond, the single waves fill the chip and read each list with scalar loads
+// (walk and sum, us, workgroups against waves: clustered box of 200,000
+// particles 637 against 884 at n_crit 64 and 561 against 881 at 256, of
+// 400,000 1132 against 1053 and 993 against 1211, of 700,000 1932 against 1348
+// and 1696 against 1889).  Every list takes at least one far and one near
+// block, so groups smaller than kWideMinCrit stay with the waves.
+constexpr int64_t kWideGroups = 2048;
+constexpr int kWideMinCrit = 16;
+// Fewest node tests that make a group an outlier (see outlier_cap): a walk
+// this long is a small part of a launch (32 iterations of 256 threads, 256
+// batches of a wave).
+constexpr int kOutMinWide = 8192;
+constexpr int kOutMin = 16384;
+// Largest tree with outliers apart, and their block length: a task's list (at
+// most kTaskNodes cells of n / 2048 particles) then fits the block table.
+constexpr int64_t kOutMaxN = 1 << 26;
+constexpr int kOutBlock = 256;
+
+// Whether the force call takes the workgroup walk: the tuning options (split
+// cap, list tile, waves), each of which asks for the single-wave walk in a
+// given form, are at their defaults.  A context that integrates (a kick, a
+// drift or leapfrog steps ran on it) stays with the single waves at every
+// size: the FP32 sums then keep one list order and one length whatever the
+// particle count, and with them the rounding errors that add up along a
+// trajectory and in its energy.
+static bool wide_path(const bh_ctx *c) {
+  return !c->integrates && c->opt.split_visits == 0 && c->opt.list_tile == 0 && c->opt.waves_per_cu == 0 &&
+         c->n_crit >= kWideMinCrit && c->n <= kWideGroups * c->n_crit && wide_fits(c->n);
+}
+
+// Arguments and buffers of the workgroup kernels (the pool holds c->wide_cap
+// blocks).  groups: the ordinary groups too, not only outliers.
+static bh_status wide_args(bh_ctx *c, bool groups, const float *theta_group, float *acc, float *pot, WideArgs &A) {
+  const bool quad = c->opt.quadrupole != 0;
+  const int block = c->wide_block;
+  const size_t cap = (size_t)c->wide_cap;
+  struct {
+    DevBuf *b;
+    size_t bytes;
+  } want[] = {{&c->wide_pool, cap * block * sizeof(float4)},
+              {&c->wide_slot, quad ? cap * block * sizeof(int32_t) : 0},
+              {&c->wide_gblocks, groups ? sizeof(int2) * (size_t)c->n : 0},
+              {&c->wide_gstat, groups ? sizeof(int2) * (size_t)c->n : 0},
+              {&c->wide_binfo, cap * sizeof(int4)},
+              {&c->wide_psum, cap * (size_t)c->n_crit * 4 * sizeof(double)},
+              {&c->out_groups, sizeof(int32_t) * kOutMax},
+              {&c->out_info, sizeof(OutInfo) * kOutMax},
+              {&c->out_nodes, sizeof(int32_t) * (size_t)kOutMax * kOutNodes},
+              {&c->out_tasks, sizeof(int4) * (size_t)kTaskCap},
+              {&c->out_rows, sizeof(int4) * (size_t)kTaskCap},
+              {&c->out_near, sizeof(int32_t) * (size_t)kTaskCap},
+              {&c->out_mass, sizeof(double) * (size_t)kTaskCap}};
+  for (auto &w : want) {
+    if (w.bytes == 0) continue;
+    bh_status st = ensure(c, *w.b, w.bytes, "list blocks");
+    if (st) return st;
+  }
+  A.nodes = P<NodeRec>(c->nodes);
+  A.sys = P<SysInfo>(c->sys);
+  A.ginfo = P<int32_t>(c->ginfo);
+  A.gbox = P<double>(c->gbox);
+  A.par = P<SysParam>(c->par);
+  A.theta_group = theta_group;
+  A.info = P<DevInfo>(c->info);
+  A.nsys = c->nsys;
+  A.n_crit = c->n_crit;
+  A.block = block;
+  for (A.block_log = 0; (1 << A.block_log) < block;) ++A.block_log;
+  A.block_cap = c->wide_cap;
+  A.pool = P<float4>(c->wide_pool);
+  A.slot = quad ? P<int32_t>(c->wide_slot) : nullptr;
+  A.qpack = quad ? P<float4>(c->qpack) : nullptr;
+  A.glist = P<int32_t>(c->glist);
+  A.gmass = P<double>(c->gmass);
+  A.gblocks = P<int2>(c->wide_gblocks);
+  A.gstat = P<int2>(c->wide_gstat);
+  A.binfo = P<int4>(c->wide_binfo);
+  A.psum = P<double>(c->wide_psum);
+  A.spos = P<double>(c->spos);
+  A.smass = P<double>(c->smass);
+  A.perm = P<int32_t>(c->perm);
+  A.acc = acc;
+  A.pot = pot;
+  A.out = P<int32_t>(c->out_groups);
+  A.outinfo = P<OutInfo>(c->out_info);
+  A.tnodes = P<int32_t>(c->out_nodes);
+  A.tasks = P<int4>(c->out_tasks);
+  A.trows = P<int4>(c->out_rows);
+  A.tnear = P<int32_t>(c->out_near);
+  A.tmass = P<double>(c->out_mass);
+  return BH_OK;
+}
+
+// The pool's capacity counts blocks of one length: recount when it changes,
+// and start from at least `want` blocks.
+static void wide_capacity(bh_ctx *c, int block, int64_t want) {
+  if (c->wide_block != block) {
+    c->wide_cap = (int32_t)((int64_t)c->wide_cap * c->wide_block / block);
+    c->wide_block = block;
+  }
+  if (!c->capturing && c->wide_cap < want) c->wide_cap = (int32_t)std::min<int64_t>(want, INT32_MAX / 2);
+}
+
+static void wide_grow(bh_ctx *c) {
+  const int64_t need = c->info_host->blocks;
+  if (need > c->wide_cap) c->wide_cap = (int32_t)std::min<int64_t>(need + need / 4 + 64, INT32_MAX / 2);
+}
+
+// The force call by workgroup walk and list blocks (parameters uploaded).
+static bh_status forces_wide(bh_ctx *c, const float *theta_group, float *acc, float *pot) {
+  const int64_t n = c->n;
+  // 48 entries per particle and a few partly filled blocks per group to start
+  // with; grown to what a walk reports it needed
+  const int block = wide_block_length(n);
+  wide_capacity(c, block, 48 * n / block + 6 * n / c->n_crit + 96 * (int64_t)c->num_cu);
+  if (!c->info_event) {
+    bh_status st = hip_check(c, hipEventCreateWithFlags(&c->info_event, hipEventDisableTiming), "hipEventCreate");
+    if (st) return st;
+  }
+  if (!c->capturing) c->out_off = false;
+  for (int attempt = 0;; ++attempt) {
+    WideArgs A{};
+    bh_status st = wide_args(c, true, theta_group, acc, pot, A);
+    if (st) return st;
+    // (a walk tests at most 2 n nodes: small trees have no outliers)
+    const bool outliers = 2 * n > kOutMinWide && !c->out_off;
+    A.out_min = outliers ? kOutMinWide : 0;
+    if (!c->counters_clean) reset_list_counters(P<DevInfo>(c->info), c->stream);
+    c->counters_clean = false;
+    st = timer_start(c, c->t_walk);
+    if (st) return st;
+    walk_wide_device(A, n, c->num_cu, c->stream);
+    if (outliers) walk_tasks_device(A, c->num_cu, c->stream);
+    st = timer_stop(c, c->t_walk);
+    if (st) return st;
+    // The sums are queued behind the walk and leave at once when a list did
+    // not fit; the host looks at the walk's counters meanwhile (a captured
+    // step cannot: an overflow then leaves kErrPool for bh_sync).
+    if (!c->capturing) {
+      st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
+                     "hipMemcpyAsync info");
+      if (!st) st = hip_check(c, hipEventRecord(c->info_event, c->stream), "hipEventRecord");
+      if (st) return st;
+    }
+    st = timer_start(c, c->t_force);
+    if (st) return st;
+    force_blocks_device(A, c->num_cu, c->stream);
+    block_reduce_device(A, c->num_cu, c->stream);
+    if (outliers) task_reduce_device(A, c->stream);
+    st = timer_stop(c, c->t_force);
+    if (st) return st;
+    st = hip_check(c, hipGetLastError(), "kernel launch (force)");
+    if (st) return st;
+    c->last_attempts = attempt + 1;
+    if (c->capturing) break;
+    st = hip_check(c, hipEventSynchronize(c->info_event), "hipEventSynchronize");
+    if (st) return st;
+    if (!(c->info_host->err & (kErrPool | kErrWide))) break;
+    if (attempt > 5) return fail(c, BH_EINTERNAL, "interaction list pool still too small after growing");
+    if (c->info_host->err & kErrWide) c->out_off = true;  // every group by one workgroup
+    wide_grow(c);
+  }
+  c->last_segments = c->last_split_groups = c->last_depth = 0;
+  c->have_forces = true;
   return BH_OK;
 }
 
@@ -543,6 +716,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     c->have_forces = true;
     return BH_OK;
   }
+  if (wide_path(c)) return forces_wide(c, theta_group, acc, pot);
   // list pools: start from an estimate (32 far and 4 near entries per
   // particle), grow to what a walk reports it needed; the capacities count
   // chunks of the current tile (recounted when the tile changes)
@@ -575,26 +749,12 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   // split walks (long lists walked and summed by several waves)
   const int grid = c->num_cu * (c->opt.waves_per_cu > 0 ? c->opt.waves_per_cu : c->walk_bpc);
   const int fgrid = c->num_cu * (c->opt.waves_per_cu > 0 ? c->opt.waves_per_cu : (quad ? c->force_bpc_q : c->force_bpc));
-  // The automatic visit cap scales with the particles per walk wave (a walk
-  // that outlasts a multiple of the average wave's share is the one to
-  // split), never below kSplitVisits; in the walk it also grows to
-  // kSplitMeanFactor times the mean list length of the previous walk on this
-  // context, so that where every list is long (small theta) only the outliers
-  // split: splitting most groups costs more than it balances.
-  // A single system is not split by default: its lists are rarely far longer
-  // than the mean, and the walk without the split machinery is faster (see
-  // k_walk_lists).
-  const int64_t auto_cap = std::max<int64_t>(kSplitVisits, kSplitPerParticle * c->n / std::max(grid, 1));
-  const bool auto_split = c->opt.split_visits == 0;
-  const int visit_cap = c->opt.split_visits < 0
-                            ? 0
-                            : (auto_split ? (c->nsys > 1 ? (int)std::min<int64_t>(auto_cap, INT32_MAX / 2) : 0)
-                                          : c->opt.split_visits);
-  if (!c->walk_hist.p) {
-    st = ensure(c, c->walk_hist, 4 * sizeof(int32_t), "walk history");
-    if (st) return st;
-    fill_i32(P<int32_t>(c->walk_hist), 0, 4, c->stream);
-  }
+  // Split walks only on request; by default outliers go to the workgroup
+  // walk (not on a context that integrates, see wide_path).
+  const int visit_cap = std::max(c->opt.split_visits, 0);
+  if (!c->capturing) c->out_off = false;
+  bool outliers = c->opt.split_visits == 0 && !c->integrates && c->n <= kOutMaxN && 2 * c->n > kOutMin && !c->out_off;
+  if (outliers) wide_capacity(c, kOutBlock, 2 * c->n / kOutBlock + 4096);
   if (c->seg_cap == 0) {
     c->task_cap = 4096;
     c->range_cap = 1 << 16;
@@ -608,6 +768,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   if (st) return st;
   SplitBuffers S{};
   int32_t nsegs_host = 0;
+  bool have_out = outliers;  // (a capture replays on other particles: it always has the outliers' launches)
   for (int attempt = 0;; ++attempt) {
     st = ensure(c, c->far_pool, (size_t)c->far_cap * tile * sizeof(float4), "far list pool");
     if (st) return st;
@@ -655,16 +816,29 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     W.seg_cap = c->seg_cap;
     W.gsplit = P<int32_t>(c->gsplit);
     W.visit_cap = visit_cap;
-    W.mean_list = auto_split ? P<int32_t>(c->walk_hist) : nullptr;
+    W.out_min = outliers ? kOutMin : 0;
+    W.n_crit = c->n_crit;
+    WideArgs A{};
+    if (outliers) {
+      st = wide_args(c, false, theta_group, acc, pot, A);
+      if (st) return st;
+      W.out = A.out;
+    }
     W.order = (theta_group && c->walk_order_valid) ? P<int32_t>(c->walk_order) : nullptr;
     W.wait_ticks = c->wait_ticks;
-    reset_list_counters(P<DevInfo>(c->info), c->stream);
-    split_reset(W.ctr, P<DevInfo>(c->info), W.tasks, c->task_cap, c->stream);
+    if (!c->counters_clean || !c->xq_clean) reset_list_counters(P<DevInfo>(c->info), c->stream);
+    c->counters_clean = false;
+    if (visit_cap > 0) split_reset(W.ctr, P<DevInfo>(c->info), W.tasks, c->task_cap, c->stream);
     st = timer_start(c, c->t_walk);
     if (st) return st;
     c->last_attempts = attempt + 1;
     walk_lists_device(W, grid, c->stream);
     c->xq_clean = false;
+    // (outside a capture the host looks first whether there are outliers)
+    if (outliers && c->capturing) {
+      walk_outliers_device(A, c->stream);
+      walk_tasks_device(A, c->num_cu, c->stream);
+    }
     st = timer_stop(c, c->t_walk);
     if (st) return st;
     st = hip_check(c, hipGetLastError(), "kernel launch (walk)");
@@ -682,12 +856,27 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     }
     st = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
     if (st) return st;
+    have_out = outliers && c->info_host->n_out > 0;
+    if (have_out) {
+      walk_outliers_device(A, c->stream);
+      walk_tasks_device(A, c->num_cu, c->stream);
+      st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
+                     "hipMemcpyAsync info");
+      if (!st) st = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
+      if (st) return st;
+    }
     if (visit_cap > 0) nsegs_host = c->split_host->segs;
     c->last_segments = nsegs_host;
     c->last_split_groups = visit_cap > 0 ? c->split_host->n_split : 0;
     c->last_depth = visit_cap > 0 ? c->split_host->depth : 0;
-    if (!(c->info_host->err & kErrPool)) break;
+    if (!(c->info_host->err & (kErrPool | kErrWide))) break;
     if (attempt > 5) return fail(c, BH_EINTERNAL, "interaction list pool still too small after growing");
+    if (c->info_host->err & kErrWide) {
+      c->out_off = true;  // every group by one wave after all
+      outliers = have_out = false;
+      continue;
+    }
+    wide_grow(c);
     const int64_t fneed = (int64_t)c->info_host->far_chunks * kChunkRun, nneed = (int64_t)c->info_host->near_chunks * kChunkRun;
     c->far_cap = std::max(c->far_cap, (int32_t)std::min<int64_t>(fneed + fneed / 4 + 64, INT32_MAX / 2));
     c->near_cap = std::max(c->near_cap, (int32_t)std::min<int64_t>(nneed + nneed / 4 + 64, INT32_MAX / 2));
@@ -755,10 +944,18 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   F.pbase = S.pbase;
   F.psum = split ? P<double>(c->psum) : nullptr;
   item_order_device(F, P<int32_t>(c->gsplit), P<int32_t>(c->gnseg), (int64_t)gcap, P<int32_t>(c->order_hist),
-                    P<int32_t>(c->walk_hist), P<int32_t>(c->items), c->stream);
+                    P<int32_t>(c->items), c->stream);
   st = timer_start(c, c->t_force);
   if (st) return st;
   force_lists_device(F, fgrid, c->stream);
+  if (have_out) {
+    // (after the lists' sums, which leave an outlier's members with none)
+    WideArgs A{};
+    st = wide_args(c, false, theta_group, acc, pot, A);
+    if (st) return st;
+    force_blocks_device(A, c->num_cu, c->stream);
+    task_reduce_device(A, c->stream);
+  }
   st = timer_stop(c, c->t_force);
   if (st) return st;
   if (split)
@@ -816,6 +1013,7 @@ static bh_status particle_common(bh_ctx *c, const double *eps_sys, const double 
   st = ensure(c, c->pp_next, sizeof(int32_t) * (size_t)std::max<int64_t>(nslots, 1), "thread pointers");
   if (st) return st;
   reset_list_counters(P<DevInfo>(c->info), c->stream);
+  c->counters_clean = false;
   st = timer_start(c, c->t_particle);
   if (st) return st;
   particle_forces_device(P<NodeRec>(c->nodes), (int)nslots, c->nsys, P<SysInfo>(c->sys), P<SysParam>(c->par),
@@ -881,6 +1079,7 @@ static bh_status capture_common(bh_ctx *c, int32_t n_systems, const int64_t *off
   // 2. headroom in the list pools for replays on moved particles
   c->far_cap += c->far_cap / 4;
   c->near_cap += c->near_cap / 4;
+  c->wide_cap += c->wide_cap / 4;
   st = forces_common(c, eps_sys, theta_sys, net ? theta_out : theta_group, acc, pot);
   if (!st) st = bh_sync(c);
   if (st) return st;
@@ -966,9 +1165,10 @@ bh_status bh_get_stats(bh_ctx *c, bh_stats *out) {
     out->interactions = (int64_t)d.interactions;
     out->list_entries = (int64_t)d.list_entries;
     out->max_list = d.max_list;
-    out->n_split_groups = c->last_split_groups;
-    out->n_segments = c->last_segments;
-    out->n_split_levels = c->last_depth;
+    const int32_t outs = std::min(d.n_out, kOutMax);
+    out->n_split_groups = c->last_split_groups + outs;
+    out->n_segments = c->last_segments + outs + d.tasks;
+    out->n_split_levels = outs ? 1 : c->last_depth;
     out->n_walk_attempts = c->last_attempts;
     out->n_theta_fallback = d.theta_fallback;
     out->node_visits = (int64_t)d.node_visits;
@@ -1028,6 +1228,7 @@ bh_status bh_kick(bh_ctx *c, int64_t n, double *vel, const float *acc, double dt
   if (!c) return BH_EINVAL;
   c->err.clear();
   if (n < 0 || (n > 0 && (!vel || !acc))) return fail(c, BH_EINVAL, "bad kick arguments");
+  c->integrates = true;
   kick_device(n, vel, acc, dt, c->stream);
   return hip_check(c, hipGetLastError(), "kernel launch (kick)");
 }
@@ -1036,6 +1237,7 @@ bh_status bh_drift(bh_ctx *c, int64_t n, double *pos, const double *vel, double 
   if (!c) return BH_EINVAL;
   c->err.clear();
   if (n < 0 || (n > 0 && (!pos || !vel))) return fail(c, BH_EINVAL, "bad drift arguments");
+  c->integrates = true;
   drift_device(n, pos, vel, dt, c->stream);
   return hip_check(c, hipGetLastError(), "kernel launch (drift)");
 }
@@ -1248,6 +1450,7 @@ bh_status bh_neighbors(bh_ctx *c, const double *h, int32_t *count, double *rho, 
   A.nbr = nbr;
   bh_status st = timer_start(c, c->t_neighbor);
   if (st) return st;
+  c->counters_clean = false;  // (the search shares the group queue)
   neighbors_device(A, c->n_crit, grid, c->stream);
   st = timer_stop(c, c->t_neighbor);
   if (st) return st;

@@ -46,6 +46,14 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
   return v;
 }
 
+// The same within each row of 16 lanes.
+__device__ __forceinline__ int wave_row_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr1, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr2, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr4, 0xf, 0xf, false);
+  return v + __builtin_amdgcn_update_dpp(0, v, kDppRowShr8, 0xf, 0xf, false);
+}
+
 __device__ __forceinline__ int wave_inclusive_max(int v) {
   constexpr int kId = -2147483647 - 1;
   v = max(v, __builtin_amdgcn_update_dpp(kId, v, kDppRowShr1, 0xf, 0xf, false));
@@ -74,6 +82,30 @@ __device__ __forceinline__ double shfl_d(double v, int lane) {
 __device__ __forceinline__ int64_t shfl_i64(int64_t v, int lane) {
   const int lo = __shfl((int)(uint32_t)v, lane, kWave), hi = __shfl((int)(v >> 32), lane, kWave);
   return ((int64_t)hi << 32) | (uint32_t)lo;
+}
+
+// Node tests after which a group's walk is an outlier's: four times what such
+// a group takes in an ordinary place, at least out_min.  Lists hold about
+// (60 + 25 sqrt(n_crit)) theta^-1.5 entries per factor of eight in particle
+// number (mean lists of clustered boxes, Plummer and uniform spheres from
+// 30,000 to 4 million particles at theta 0.33 to 0.75 lie within 0.6 to 1.4
+// of that), and a walk tests 1.3 nodes an entry.  A function of the group
+// alone, so that the same groups are outliers in every run.
+__device__ __forceinline__ int outlier_cap(int out_min, int n_crit, int count, double theta) {
+  if (out_min <= 0 || !(theta > 0.0)) return 0;
+  const float octaves = fmaxf(1.0f, log2f((float)count / (float)n_crit) * (1.0f / 3.0f));
+  const float th = (float)theta;
+  const float cap = 5.2f * (60.0f + 25.0f * sqrtf((float)n_crit)) * octaves / (th * sqrtf(th));
+  return max(out_min, (int)fminf(cap, 1e9f));
+}
+
+// Place among the outliers; beyond the last one an error that makes the host
+// walk every group whole.  One lane.
+__device__ __forceinline__ int take_outlier(DevInfo *info) {
+  const int o = atomicAdd(&info->n_out, 1);
+  if (o < kOutMax) return o;
+  atomicOr(&info->err, kErrWide);
+  return -1;
 }
 
 // Octal digits shared by two 63-bit keys (21 when equal).

@@ -91,6 +91,10 @@ struct DevInfo {
   // Counters that every wave of a kernel updates, each in a 128-byte line of
   // its own (atomics on one line serialise behind each other).
   alignas(128) int32_t queue2;  // force work queue head
+  alignas(128) int32_t blocks;  // list blocks taken by the workgroup walk (may exceed the pool: then it is the need)
+  int32_t rows;                 // list blocks it used (rows of partial sums)
+  int32_t n_out;                // outlier groups (more than kOutMax: an error, the host walks another way)
+  int32_t tasks;                // their walk tasks
   alignas(128) int32_t far_chunks;   // runs of kChunkRun list chunks taken (may exceed the pool: then it is the need)
   alignas(128) int32_t near_chunks;
   alignas(128) int32_t xq[8 * kLineInts];  // walk queue heads, one per XCD: xq[x * kLineInts]
@@ -117,6 +121,7 @@ enum : int32_t {
   kErrPool = 32,
   kErrWait = 64,          // a bounded wait ended without its condition (walk tasks, sort look-back)
   kErrRadius = 128,      // neighbour search: a radius not positive and finite
+  kErrWide = 512,        // too many outliers, or a list too long for the block table (the host walks another way)
   kErrListSpace = 256,   // neighbour search: offsets leave a list too little or too much room
 };
 
@@ -140,9 +145,6 @@ struct Segment {
   double mass;
 };
 constexpr int kSplitDepth = 5;       // tasks this many hand-overs deep walk to the end
-constexpr int kSplitVisits = 12288;  // smallest default node tests before a walk hands over
-constexpr int kSplitPerParticle = 16;  // default cap: this many node tests per particle of a walk wave
-constexpr int kSplitMeanFactor = 4;    // and at least this many times the previous walk's mean list length
 constexpr int kDonateTasks = 16;     // tasks made from one handed-over stack
 struct SplitCounters {               // device
   int32_t tasks;                     // task slots reserved
@@ -188,6 +190,8 @@ struct bh_ctx {
   bool have_forces = false;
   bool have_quad = false;  // the current tree carries second moments
   bool have_neighbors = false;  // a neighbour search ran since the last build
+  bool out_off = false;    // the last force call found more outliers than fit: every group walked whole
+  bool integrates = false; // a kick or drift ran on this context: force calls keep the single-wave list order
   bool capturing = false;         // recording a step into a HIP graph: no uploads, syncs or timers
   hipStream_t capture_stream = nullptr;
   hipGraphExec_t graph = nullptr; // the captured step
@@ -245,11 +249,16 @@ struct bh_ctx {
   bh::DevBuf feps;              // FP64 [nsys] softening of the feature call
   bh::DevBuf mlp_work;          // training batch workspace
   bh::DevBuf mlp_feat;          // FP32 [n][12] features of bh_group_theta
+  // lists in blocks (sizes at which a group is walked by a workgroup)
+  bh::DevBuf wide_pool, wide_slot, wide_gblocks, wide_gstat, wide_binfo, wide_psum;
+  bh::DevBuf out_groups, out_info, out_nodes, out_tasks, out_rows, out_near, out_mass;  // outliers and their walk tasks
+  int32_t wide_cap = 0, wide_block = 0;  // blocks in the pool, entries per block
+  bool counters_clean = false;           // the force counters are known to be 0 (reset by make_groups)
+  hipEvent_t info_event = nullptr;       // completion of a read-back of the counters
   bh::DevBuf pp_next;           // int32 per slot: thread pointers of the per-particle walk
   bh::DevBuf order_hist;        // int32 cost bins of the queue orders
   bh::DevBuf walk_order;        // int32 [n] order in which the list walk takes the groups (learned theta)
   bh::DevBuf walk_order_hist;   // int32 cost bins of the walk order (zero between calls)
-  bh::DevBuf walk_hist;         // int32 [4]: mean list length of the last force call (automatic split cap)
   // split walks: tasks (ping-pong), range pool, segments, counters, per-group
   // flags, segment sort and partial sums
   bh::DevBuf tasks, ranges, segs, split_ctr, gsplit, gnseg, gsegfirst;
@@ -373,7 +382,6 @@ struct WalkListArgs {
   int32_t *far_slot;         // nullable: node slot of each far entry (-1 a particle), for quadrupoles
   // split walks
   int visit_cap;             // node tests before a walk hands over its stack (0: never)
-  const int32_t *mean_list;  // nullable: previous mean list length; the cap is raised to kSplitMeanFactor x it
   SplitCounters *ctr;
   WalkTask *tasks;           // task slots (ctr->tasks reserved)
   int task_cap;
@@ -383,6 +391,9 @@ struct WalkListArgs {
   int seg_cap;
   long long wait_ticks;      // wall-clock ticks a wave may wait for a task
   int32_t *gsplit;           // per group: 1 when its list is in segments
+  int out_min;               // smallest number of node tests that makes a group an outlier (0: never, see outlier_cap)
+  int n_crit;
+  int32_t *out;              // [kOutMax] outlier groups (info->n_out of them)
   const int32_t *order;      // nullable: the groups in the order the walk takes them; each eighth of
                              // [0, G) a permutation of itself (walk_order_device)
 };
@@ -481,11 +492,11 @@ struct ForceArgs {
   const float4 *qpack;        // quadrupole sums: [slots][2] second moments
 };
 void force_lists_device(const ForceArgs &a, int grid, hipStream_t s);
-// The force items in queue order (k_order.hip), with the list statistics and
-// the mean list length; hist holds order_hist_bytes() and is zero on entry
+// The force items in queue order (k_order.hip), with the list statistics;
+// hist holds order_hist_bytes() and is zero on entry
 // (order_clear_device once after allocation; every call leaves it zero).
 void item_order_device(const ForceArgs &f, const int32_t *gsplit, const int32_t *gnseg, int64_t gcap, int32_t *hist,
-                       int32_t *mean_list, int32_t *items, hipStream_t s);
+                       int32_t *items, hipStream_t s);
 void order_clear_device(int32_t *hist, hipStream_t s);
 // Walk order of a learned-theta step (k_order.hip): within each eighth of
 // the groups, the groups by predicted walk time from their features (FP32
@@ -495,6 +506,58 @@ void walk_order_device(const float *feat, const float *theta, const DevInfo *inf
                        int32_t *order, hipStream_t s);
 int force_lists_blocks_per_cu(bool quad);
 void reset_list_counters(DevInfo *info, hipStream_t s);
+
+// k_wide.hip: walk by workgroups, sums over list blocks
+constexpr int kOutMax = 256;      // outlier groups of one walk
+constexpr int kOutNodes = 8192;   // task nodes of one outlier
+constexpr int kTaskNodes = 8;     // nodes per task
+constexpr int kTaskCap = kOutMax * (kOutNodes / kTaskNodes);
+struct OutInfo {
+  int32_t g, task0, tasks;      // group, its tasks
+  int32_t row0, rows, len;      // rows and entries of its own part of the list
+  int32_t visits, near;         // node tests (those of the given-up walk too), near entries
+  double mass;
+};
+struct WideArgs {
+  const NodeRec *nodes;
+  const SysInfo *sys;
+  const int32_t *ginfo;
+  const double *gbox;
+  const SysParam *par;
+  const float *theta_group;
+  DevInfo *info;
+  int nsys, n_crit;
+  int block, block_log;  // far entries per list block (a near block holds half as many), its log2
+  int block_cap;         // blocks in the pool
+  float4 *pool;          // [block_cap][block]; a near block: block / 2 values, then their rounding residues
+  int32_t *slot;         // nullable (quadrupole sums): node slot of each far entry, -1 a particle
+  const float4 *qpack;
+  int32_t *glist;
+  double *gmass;
+  int2 *gblocks;         // [G] first row of the group's list blocks, their number (far, then near); -1 an outlier
+  int2 *gstat;           // [G] node tests, near entries
+  int4 *binfo;           // [rows] group, block, entries, 1 for a near block
+  double *psum;          // [rows][n_crit][4] partial sums
+  const double *spos, *smass;
+  const int32_t *perm;
+  float *acc, *pot;
+  int out_min;           // smallest number of node tests that makes a group an outlier (0: never, see outlier_cap)
+  int32_t *out;          // [kOutMax] outlier groups
+  OutInfo *outinfo;      // [kOutMax]
+  int32_t *tnodes;       // [kOutMax][kOutNodes] task nodes
+  int4 *tasks;           // [kTaskCap] group, first task node, nodes
+  int4 *trows;           // [kTaskCap] first row, rows, entries, node tests
+  int32_t *tnear;        // [kTaskCap] near entries
+  double *tmass;         // [kTaskCap] list mass
+};
+int wide_block_length(int64_t n);  // of a tree of n particles
+bool wide_fits(int64_t n);         // whether the longest list of n particles fits the walk's block table
+void walk_wide_device(const WideArgs &a, int64_t n, int num_cu, hipStream_t s);
+void walk_outliers_device(const WideArgs &a, hipStream_t s);  // a.out over the large cells
+void walk_tasks_device(const WideArgs &a, int num_cu, hipStream_t s);
+void force_blocks_device(const WideArgs &a, int num_cu, hipStream_t s);
+void block_reduce_device(const WideArgs &a, int num_cu, hipStream_t s);  // members of ordinary groups
+void task_reduce_device(const WideArgs &a, hipStream_t s);               // members of outliers
 
 // k_misc.hip
 size_t direct_part_bytes(int64_t n, int64_t s, int num_cu, int64_t *chunk, int64_t *nchunk);

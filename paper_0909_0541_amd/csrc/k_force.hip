@@ -25,116 +25,32 @@
 //   potential  -3 (u.S.u) / (2 R^5) + T / (2 R^3)
 //   force      -3 S u / R^5 + (15 (u.S.u) / (2 R^7) - 3 T / (2 R^5)) u.
 #include "bh_device.h"
+#include "force_terms.h"
 
 namespace bh {
 
 namespace {
 
-struct Member {
-  float x, y, z;     // FP32 x_i - c_g
-  float lx, ly, lz;  // rounding residue of x_i - c_g
-  float ax, ay, az, pt;
-  double dx, dy, dz, dp;
-};
-
-// The quadrupole term of one cell entry at relative position (dx, dy, dz),
-// with R^2 = |u|^2 + eps^2 and ri = 1/R; a = 3 (xx, yy, zz, xy), b = (3 xz,
-// 3 yz, T, 1.5 T).  With S3 = 3 S and w = u.S3.u the terms above read
-//   force       r5 (2.5 w ri^2 - 1.5 T) u - r5 S3 u
-//   -potential  0.5 r5 (w - T R^2),        r5 = ri^5.
-__device__ __forceinline__ void quad_term(Member &M, const float4 a, const float4 b, float dx, float dy, float dz,
-                                          float R2, float ri) {
-  const float sx = __builtin_fmaf(a.x, dx, __builtin_fmaf(a.w, dy, b.x * dz));
-  const float sy = __builtin_fmaf(a.w, dx, __builtin_fmaf(a.y, dy, b.y * dz));
-  const float sz = __builtin_fmaf(b.x, dx, __builtin_fmaf(b.y, dy, a.z * dz));
-  const float w = __builtin_fmaf(dx, sx, __builtin_fmaf(dy, sy, dz * sz));
-  const float ri2 = ri * ri;
-  const float r5 = ri2 * ri2 * ri;
-  const float c = r5 * __builtin_fmaf(2.5f * w, ri2, -b.w);
-  M.ax = __builtin_fmaf(-r5, sx, __builtin_fmaf(c, dx, M.ax));
-  M.ay = __builtin_fmaf(-r5, sy, __builtin_fmaf(c, dy, M.ay));
-  M.az = __builtin_fmaf(-r5, sz, __builtin_fmaf(c, dz, M.az));
-  M.pt = __builtin_fmaf(0.5f * r5, __builtin_fmaf(-b.z, R2, w), M.pt);
-}
-
-// U entries (value e, rounding residue l when NEAR) against this lane's
-// member, written stage by stage across the U independent terms.  With QUAD,
-// sl[u] is the node slot of a far entry (near entries: l[u].w), -1 for a
-// particle.
+// U entries against this lane's member; with QUAD, sl[u] is the node slot of a
+// far entry (near entries: l[u].w), -1 for a particle.  The moments are
+// fetched first (a particle's slot is clamped to 0 and its values unused), so
+// that the monopole terms hide their latency.
 template <int U, bool NEAR, bool QUAD = false>
 __device__ __forceinline__ void terms(Member &M, const float4 (&e)[U], const float4 (&l)[U], float eps2,
                                       const int (&sl)[U], const float4 *__restrict__ qpack) {
-  float dx[U], dy[U], dz[U], q[U], mr[U], ri[U], R2[U];
-  // the moments are fetched first (a particle's slot is clamped to 0 and its
-  // values unused), so that the monopole terms hide their latency
   float4 qa[U], qb[U];
-  int slot[U];
-  if (QUAD) {
+  bool cell[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      slot[u] = NEAR ? __float_as_int(l[u].w) : sl[u];
-      const int64_t at = 2 * (int64_t)max(slot[u], 0);
+  for (int u = 0; u < U; ++u) {
+    const int slot = QUAD ? (NEAR ? __float_as_int(l[u].w) : sl[u]) : -1;
+    cell[u] = slot >= 0;
+    if (QUAD) {
+      const int64_t at = 2 * (int64_t)max(slot, 0);
       qa[u] = qpack[at];
       qb[u] = qpack[at + 1];
     }
   }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    dx[u] = e[u].x - M.x;
-    dy[u] = e[u].y - M.y;
-    dz[u] = e[u].z - M.z;
-  }
-  if (NEAR) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      dx[u] += l[u].x - M.lx;
-      dy[u] += l[u].y - M.ly;
-      dz[u] += l[u].z - M.lz;
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) q[u] = __builtin_fmaf(dx[u], dx[u], eps2);
-#pragma unroll
-  for (int u = 0; u < U; ++u) q[u] = __builtin_fmaf(dy[u], dy[u], q[u]);
-#pragma unroll
-  for (int u = 0; u < U; ++u) q[u] = __builtin_fmaf(dz[u], dz[u], q[u]);
-  if (QUAD) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) R2[u] = q[u];
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) q[u] = __builtin_amdgcn_rsqf(q[u]);  // 1/r
-  if (QUAD) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) ri[u] = q[u];
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    mr[u] = e[u].w * q[u];
-    q[u] = q[u] * q[u];  // 1/r^2
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) q[u] = mr[u] * q[u];  // m/r^3
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    M.ax = __builtin_fmaf(q[u], dx[u], M.ax);
-    M.ay = __builtin_fmaf(q[u], dy[u], M.ay);
-    M.az = __builtin_fmaf(q[u], dz[u], M.az);
-    M.pt += mr[u];
-  }
-  if (QUAD) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (slot[u] >= 0) quad_term(M, qa[u], qb[u], dx[u], dy[u], dz[u], R2[u], ri[u]);
-  }
-}
-
-__device__ __forceinline__ void fold(Member &M) {
-  M.dx += (double)M.ax;
-  M.dy += (double)M.ay;
-  M.dz += (double)M.az;
-  M.dp += (double)M.pt;
-  M.ax = M.ay = M.az = M.pt = 0.0f;
+  entry_terms<U, NEAR, QUAD>(M, e, l, eps2, cell, qa, qb);
 }
 
 constexpr int kU = 8;      // entries per block of terms
@@ -313,14 +229,7 @@ __global__ __launch_bounds__(kWave) void k_force_lists(ForceArgs a, const float4
         ry = __dsub_rn(q[1], cen[1]);
         rz = __dsub_rn(q[2], cen[2]);
       }
-      M.x = (float)rx;
-      M.y = (float)ry;
-      M.z = (float)rz;
-      M.lx = (float)__dsub_rn(rx, (double)M.x);
-      M.ly = (float)__dsub_rn(ry, (double)M.y);
-      M.lz = (float)__dsub_rn(rz, (double)M.z);
-      M.ax = M.ay = M.az = M.pt = 0.0f;
-      M.dx = M.dy = M.dz = M.dp = 0.0;
+      member_init(M, rx, ry, rz);
     }
 
     int ch = fh;
@@ -359,8 +268,7 @@ __global__ __launch_bounds__(kWave) void k_force_lists(ForceArgs a, const float4
       }
     } else if (part == 0 && u < m) {
       const int i = gf + b0 + u;
-      const float self_ri = __builtin_amdgcn_rsqf(__builtin_fmaf(0.0f, 0.0f, eps2));
-      const double self = (double)((float)a.smass[i] * self_ri);
+      const double self = self_potential(a.smass[i], eps2);
       const int o = a.perm[i];
       a.acc[3 * (int64_t)o] = (float)vx;
       a.acc[3 * (int64_t)o + 1] = (float)vy;

@@ -106,6 +106,10 @@ __global__ void k_reset_force_counters(DevInfo *info) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     info->queue = 0;
     info->queue2 = 0;
+    info->blocks = 0;
+    info->rows = 0;
+    info->n_out = 0;
+    info->tasks = 0;
     info->far_chunks = 0;
     info->near_chunks = 0;
     info->interactions = 0;
@@ -114,7 +118,7 @@ __global__ void k_reset_force_counters(DevInfo *info) {
     info->theta_fallback = 0;
     info->node_visits = 0;
     info->near_entries = 0;
-    info->err &= ~kErrPool;
+    info->err &= ~(kErrPool | kErrWide);
     for (int x = 0; x < 8; ++x) {
       info->xq[x * kLineInts] = 0;
       info->fq[x * kLineInts] = 0;

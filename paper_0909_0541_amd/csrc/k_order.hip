@@ -89,11 +89,9 @@ __global__ __launch_bounds__(256) void k_order_hist(ForceArgs f, const int32_t *
 
 // Exclusive scan of the bins (one block of 1024 threads, kKeys / 1024 bins
 // each) into the cursors; hist is left zero for the next call.  xstart[x] =
-// first queue position of XCD x, xstart[8] the item count; mean_list (when
-// set) = this call's mean list length, for the next walk's split cap.
+// first queue position of XCD x, xstart[8] the item count.
 __global__ __launch_bounds__(1024) void k_order_scan(int32_t *__restrict__ hist, int32_t *__restrict__ cursor,
-                                                     int32_t *__restrict__ xstart, const DevInfo *__restrict__ info,
-                                                     int32_t *__restrict__ mean_list) {
+                                                     int32_t *__restrict__ xstart) {
   constexpr int kPer = kKeys / 1024;
   __shared__ int32_t w[1024 / kWave];
   const int t = threadIdx.x;
@@ -118,10 +116,6 @@ __global__ __launch_bounds__(1024) void k_order_scan(int32_t *__restrict__ hist,
     off += v[j];
   }
   if (t == 1023) xstart[kXcd] = off;
-  if (t == 0 && mean_list) {
-    const unsigned long long G = (unsigned long long)max(info->n_groups, 1);
-    mean_list[0] = (int32_t)min(info->list_entries / G, (unsigned long long)(INT32_MAX / 64));
-  }
 }
 
 // Each group takes a run of queue places from its bin's cursor and writes
@@ -260,12 +254,12 @@ size_t order_hist_bytes() { return sizeof(int32_t) * (2 * kKeys + 16); }
 void order_clear_device(int32_t *hist, hipStream_t s) { k_order_clear<<<1, 256, 0, s>>>(hist); }
 
 void item_order_device(const ForceArgs &f, const int32_t *gsplit, const int32_t *gnseg, int64_t gcap, int32_t *hist,
-                       int32_t *mean_list, int32_t *items, hipStream_t s) {
+                       int32_t *items, hipStream_t s) {
   if (gcap <= 0) return;
   const unsigned grid = (unsigned)((gcap + kTile - 1) / kTile);
   int32_t *cursor = hist + kKeys, *xstart = hist + 2 * kKeys;
   k_order_hist<<<grid, 256, 0, s>>>(f, gsplit, gnseg, gcap, hist);
-  k_order_scan<<<1, 1024, 0, s>>>(hist, cursor, xstart, f.info, mean_list);
+  k_order_scan<<<1, 1024, 0, s>>>(hist, cursor, xstart);
   k_order_scatter<<<grid, 256, 0, s>>>(f, gsplit, gnseg, gcap, cursor, items);
 }
 
@@ -279,7 +273,7 @@ void walk_order_device(const float *feat, const float *theta, const DevInfo *inf
   const unsigned grid = (unsigned)((cap + kTile - 1) / kTile);
   int32_t *cursor = hist + kKeys, *xstart = hist + 2 * kKeys;
   k_worder_hist<<<grid, 256, 0, s>>>(feat, theta, info, cap, hist);
-  k_order_scan<<<1, 1024, 0, s>>>(hist, cursor, xstart, info, nullptr);
+  k_order_scan<<<1, 1024, 0, s>>>(hist, cursor, xstart);
   k_worder_scatter<<<grid, 256, 0, s>>>(feat, theta, info, cap, cursor, order);
 }
 

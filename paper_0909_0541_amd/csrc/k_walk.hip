@@ -261,10 +261,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) v
   const int lane = lane_id();
   const int G = a.info->n_groups;
   const int nslots = a.nsys + a.info->n_slots;
-  // the automatic cap also stays above a multiple of the last mean list
-  int visit_cap = SPLIT ? a.visit_cap : 0;
-  if (SPLIT && visit_cap > 0 && a.mean_list)
-    visit_cap = max(visit_cap, kSplitMeanFactor * min(__builtin_amdgcn_readfirstlane(a.mean_list[0]), INT32_MAX / 64));
+  const int visit_cap = SPLIT ? a.visit_cap : 0;
 
   const int xcd = blockIdx.x & 7;
   int tried = 0, ticket = -1;
@@ -332,6 +329,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     int cap = (SPLIT && visit_cap > 0 && key_depth(key) < kSplitDepth) ? visit_cap : 0;
     wave_sync();
     int visits = 0;
+    int out_cap = SPLIT ? 0 : __builtin_amdgcn_readfirstlane(outlier_cap(a.out_min, a.n_crit, a.sys[gs].count, theta));
+    bool outlier = false;
     // Software pipeline: the records of the next batch are loaded while the
     // current batch is tested, so that one batch's memory latency hides
     // behind the other's work.  The next batch is taken from the stack before
@@ -471,6 +470,21 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) v
       rcur = rnext;
       ncur = node;
       if (bcur == 0 && sp == 0) break;
+      // An outlier: its list so far is dropped and the workgroup walk takes
+      // the group (unless it has its share already: then walk on).
+      if (!SPLIT && out_cap > 0 && visits >= out_cap) {
+        int o = -1;
+        if (lane == 0) {
+          o = take_outlier(a.info);
+          if (o >= 0) a.out[o] = g;
+        }
+        o = __builtin_amdgcn_readfirstlane(o);
+        out_cap = 0;
+        if (o >= 0) {
+          outlier = true;
+          break;
+        }
+      }
       // Visit cap reached: hand the rest (the popped batch as runs of
       // consecutive nodes, then the stack) to new tasks.
       if (SPLIT && cap > 0 && visits >= cap) {
@@ -555,7 +569,20 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     }
     if (lane == 0) {
       atomicAdd(&a.info->node_visits, (unsigned long long)visits);
-      atomicAdd(&a.info->near_entries, (unsigned long long)N.count);
+      atomicAdd(&a.info->near_entries, outlier ? 0ull : (unsigned long long)N.count);
+    }
+    if (outlier) {  // no entries here; its sums come from the list blocks
+      if (lane == 0) {
+        int32_t *q = a.glists + 4 * (int64_t)g;
+        q[0] = -1;
+        q[1] = 0;
+        q[2] = -1;
+        q[3] = 0;
+        a.gsplit[g] = 0;
+        a.glist[g] = 0;
+        a.gmass[g] = 0.0;
+      }
+      continue;
     }
     if (!corrupt) {
 #pragma unroll
