@@ -286,7 +286,6 @@ static bh_status build_common(bh_ctx *c, int32_t nsys, const int64_t *offsets, c
   if (st) return st;
   st = timer_start(c, c->t_build);
   if (st) return st;
-  reset_info_device(P<DevInfo>(c->info), c->stream);
   TreeBuffers B{};
   B.pos = pos;
   B.mass = mass;

@@ -309,6 +309,7 @@ void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 void iota_u32(uint32_t *v, int64_t n, hipStream_t s);
 
 // k_tree.hip
+constexpr int kSmallMax = 16384;  // largest system sorted by counting (k_small_sort)
 struct TreeBuffers {
   const double *pos, *mass;
   int64_t n;

@@ -201,17 +201,24 @@ __global__ __launch_bounds__(kSortThreads) void k_digit_counts(const uint64_t *_
   }
 }
 
-// One key pass: rank, look back, scatter.
+// One key pass: rank, look back, scatter.  A pass over a few tiles is the chain
+// of one tile (its chunks are ranked one after another) on as many compute
+// units as there are tiles, so over fewer keys the tiles are shorter: 100,003
+// keys, 16.2 us a pass with 16 chunks per wave, 10.3 with 4; the build of
+// 400,000 particles 385 us with 4 or 16, 357 with 8; of 1M 540 with 16, 553 with
+// 8 (a longer look-back costs more than the shorter tiles save).
+template <int CHUNKS>
 __global__ __launch_bounds__(kSortThreads) void k_onesweep(const uint64_t *__restrict__ kin,
                                                            const uint32_t *__restrict__ vin,
                                                            uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
                                                            int64_t n, int bit, int pass, int64_t ntiles,
                                                            uint32_t *__restrict__ state, int32_t *err) {
   static_assert(kSortThreads == kRadix, "one thread per digit");
+  constexpr int TILE = kSortThreads * CHUNKS;
   __shared__ uint32_t cnt[kSortWaves][kRadix];
   __shared__ uint32_t dstart[kRadix];  // tile-local start of each digit; then its output index minus that
-  __shared__ uint64_t skey[kSortTile];
-  __shared__ uint32_t sval[kSortTile];
+  __shared__ uint64_t skey[TILE];
+  __shared__ uint32_t sval[TILE];
   __shared__ uint32_t wtot[2][kSortWaves];
   __shared__ int tile_sh;
   const int w = threadIdx.x / kWave, lane = lane_id();
@@ -220,15 +227,15 @@ __global__ __launch_bounds__(kSortThreads) void k_onesweep(const uint64_t *__res
   __syncthreads();
   const int64_t tile = tile_sh;
   uint32_t *post = state + kStateHead + ((int64_t)pass * ntiles + tile) * kRadix;
-  const int64_t tile0 = tile * kSortTile;
-  const int64_t base = tile0 + (int64_t)w * (kSortChunks * kWave);
-  const int tile_n = (int)min((int64_t)kSortTile, n - tile0);
-  uint64_t key[kSortChunks];
-  uint32_t val[kSortChunks];
-  int rank[kSortChunks];
-  int digit[kSortChunks];
+  const int64_t tile0 = tile * TILE;
+  const int64_t base = tile0 + (int64_t)w * (CHUNKS * kWave);
+  const int tile_n = (int)min((int64_t)TILE, n - tile0);
+  uint64_t key[CHUNKS];
+  uint32_t val[CHUNKS];
+  int rank[CHUNKS];
+  int digit[CHUNKS];
 #pragma unroll
-  for (int c = 0; c < kSortChunks; ++c) {
+  for (int c = 0; c < CHUNKS; ++c) {
     int64_t i = base + c * kWave + lane;
     bool ok = i < n;
     key[c] = ok ? kin[i] : 0;
@@ -312,7 +319,7 @@ __global__ __launch_bounds__(kSortThreads) void k_onesweep(const uint64_t *__res
   __syncthreads();
   // stage the tile in LDS in digit order
 #pragma unroll
-  for (int c = 0; c < kSortChunks; ++c) {
+  for (int c = 0; c < CHUNKS; ++c) {
     const int64_t i = base + c * kWave + lane;
     if (i < n) {
       const uint32_t p = dstart[digit[c]] + cnt[w][digit[c]] + (uint32_t)rank[c];
@@ -350,11 +357,32 @@ void one_pass(const uint64_t *kin, const uint32_t *vin, uint64_t *kout, uint32_t
 
 }  // namespace
 
+// Chunks per wave of a key pass's tiles: 4 up to kFewKeys keys, 8 up to
+// kMoreKeys, 16 beyond (k_onesweep).
+constexpr int64_t kFewKeys = 1 << 18, kMoreKeys = 700000;
+
+static int pass_chunks(int64_t n) { return n <= kFewKeys ? 4 : (n <= kMoreKeys ? 8 : kSortChunks); }
+
+static int64_t pass_tiles(int64_t n) {
+  const int64_t tile = kSortThreads * pass_chunks(n);
+  return (n + tile - 1) / tile;
+}
+
 size_t radix_hist_bytes(int64_t n) {
   const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-  const int64_t table = ntiles * kRadix + 1;                        // external-digit passes
-  const int64_t state = kStateHead + (int64_t)kMaxPasses * ntiles * kRadix;  // key passes
+  const int64_t table = ntiles * kRadix + 1;  // external-digit passes
+  // key passes (a smaller sort in the same buffer may have more, shorter tiles)
+  const int64_t tiles =
+      std::max({pass_tiles(n), pass_tiles(std::min(n, kFewKeys)), pass_tiles(std::min(n, kMoreKeys))});
+  const int64_t state = kStateHead + (int64_t)kMaxPasses * tiles * kRadix;
   return (size_t)std::max(table, state) * sizeof(uint32_t);
+}
+
+template <int CHUNKS>
+static void key_pass(const uint64_t *kin, const uint32_t *vin, uint64_t *kout, uint32_t *vout, int64_t n, int bit,
+                     int pass, uint32_t *state, int32_t *err, hipStream_t s) {
+  const int64_t ntiles = pass_tiles(n);
+  k_onesweep<CHUNKS><<<(unsigned)ntiles, kSortThreads, 0, s>>>(kin, vin, kout, vout, n, bit, pass, ntiles, state, err);
 }
 
 size_t radix_scan_elems(int64_t n) {
@@ -370,12 +398,12 @@ int radix_sort_pairs(uint64_t *k0, uint64_t *k1, uint32_t *v0, uint32_t *v1, int
   int cur = 0;
   if (n <= 1) return cur;
   const int npass = (bit1 - bit0 + 7) / 8;
-  const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
+  const int64_t ntiles = pass_tiles(n);
   fill_i32(reinterpret_cast<int32_t *>(hist), 0, kStateHead + (int64_t)npass * ntiles * kRadix, s);
   k_digit_counts<<<(unsigned)std::min<int64_t>(ntiles, 512), kSortThreads, 0, s>>>(k[cur], n, bit0, npass, hist);
   for (int p = 0; p < npass; ++p) {
-    k_onesweep<<<(unsigned)ntiles, kSortThreads, 0, s>>>(k[cur], v[cur], k[cur ^ 1], v[cur ^ 1], n, bit0 + 8 * p, p,
-                                                         ntiles, hist, err);
+    auto *run = pass_chunks(n) == 4 ? key_pass<4> : (pass_chunks(n) == 8 ? key_pass<8> : key_pass<kSortChunks>);
+    run(k[cur], v[cur], k[cur ^ 1], v[cur ^ 1], n, bit0 + 8 * p, p, hist, err, s);
     cur ^= 1;
   }
   return cur;
