@@ -209,6 +209,8 @@ static bh_status ensure_particles(bh_ctx *c, int64_t n, int nsys) {
   const size_t slots = 2 * N + (size_t)nsys + 1;
   const size_t hist = radix_hist_bytes((int64_t)N);
   const size_t scan_elems = std::max<size_t>(N, hist / sizeof(uint32_t)) + 1;
+  // (cells above the subtrees are disjoint on each level)
+  const size_t lists = 4 * (kKeyLevels + 1) * (N / (size_t)subtree_particles(c->opt.quadrupole != 0) + 1);
   struct Want {
     DevBuf *b;
     size_t bytes;
@@ -223,15 +225,17 @@ static bh_status ensure_particles(bh_ctx *c, int64_t n, int nsys) {
       {&c->cdigit, N, "cdigit"},          {&c->pdigit, N, "pdigit"},
       {&c->owner, 4 * N, "owner"},        {&c->cfirst, 4 * N, "cfirst"},
       {&c->ccount, 4 * N, "ccount"},      {&c->cparent, 4 * N, "cparent"},
-      {&c->pparent, 4 * N, "pparent"},    {&c->mask, 4 * N, "mask"},
-      {&c->nchild, 4 * N, "nchild"},      {&c->cfirst_child, 4 * N, "cfirst_child"},
+      {&c->pparent, 4 * N, "pparent"},    {&c->mask, 4 * (N + 16), "mask"},
+      {&c->nchild, 4 * (N + 16), "nchild"}, {&c->cfirst_child, 4 * (N + 16), "cfirst_child"},
       {&c->cslot, 4 * N, "cslot"},        {&c->hist, hist, "hist"},
       {&c->scan_tmp, scan_tmp_bytes((int64_t)scan_elems), "scan_tmp"},
       {&c->nodes, sizeof(NodeRec) * slots, "nodes"},
       {&c->msum, 32 * slots, "msum"},
       {&c->meta, slots, "meta"},
-      {&c->levels, 3 * 24 * sizeof(int32_t), "level table"},
-      {&c->lcells, sizeof(CellRec) * N, "cells by level"},
+      {&c->kind, N + 16, "cell classes"}, {&c->tiles, 32 * (N / 4096 + 1), "child scan"},
+      {&c->subs, 2 * N + 4, "subtrees"},  {&c->pieces, lists, "pieces"},
+      {&c->tops, lists, "top cells"},     {&c->highs, lists, "high cells"},
+      {&c->highs2, lists, "high cells by level"},
       {&c->gflag, 4 * N, "gflag"},        {&c->gidx, 4 * N, "gidx"},
       {&c->glen, 4 * N, "glen"},          {&c->ginfo, 12 * N, "ginfo"},
       {&c->gbox, 48 * N, "gbox"},         {&c->glist, 4 * N, "glist"},
@@ -321,14 +325,21 @@ static bh_status build_common(bh_ctx *c, int32_t nsys, const int64_t *offsets, c
   B.nodes = P<NodeRec>(c->nodes);
   B.msum = P<double>(c->msum);
   B.meta = P<int8_t>(c->meta);
-  B.lcount = P<int32_t>(c->levels);
-  B.loff = B.lcount + 24;
-  B.lcursor = B.lcount + 48;
-  B.lcells = P<CellRec>(c->lcells);
+  B.kind = P<uint8_t>(c->kind);
+  B.tiles = P<int32_t>(c->tiles);
+  B.subs = P<int32_t>(c->subs);
+  B.pieces = P<int32_t>(c->pieces);
+  B.tops = P<int32_t>(c->tops);
+  B.highs = P<int32_t>(c->highs);
+  B.highs2 = P<int32_t>(c->highs2);
   B.slot_cap = (int64_t)std::min({c->nodes.bytes / sizeof(NodeRec), c->msum.bytes / 32, c->meta.bytes});
   B.curve = c->opt.curve;
   B.any_empty = false;
-  for (int s = 0; s < nsys; ++s) B.any_empty |= c->sys_host[s].count == 0;
+  B.nonempty = 0;
+  for (int s = 0; s < nsys; ++s) {
+    B.any_empty |= c->sys_host[s].count == 0;
+    B.nonempty += c->sys_host[s].count > 0;
+  }
   const bool quad = c->opt.quadrupole != 0;
   if (quad) {
     const size_t slots = (size_t)B.slot_cap;
@@ -400,7 +411,7 @@ void bh_destroy(bh_ctx *c) {
   DevBuf *bufs[] = {&c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->sys_in, &c->spos, &c->smass,
                     &c->perm, &c->delta, &c->level, &c->cdigit, &c->pdigit, &c->owner, &c->cfirst, &c->ccount,
                     &c->cparent, &c->pparent, &c->mask, &c->nchild, &c->cfirst_child, &c->cslot, &c->scan_tmp,
-                    &c->hist, &c->nodes, &c->msum, &c->meta, &c->levels, &c->lcells, &c->gflag, &c->gidx, &c->glen, &c->ginfo, &c->gbox, &c->glist,
+                    &c->hist, &c->nodes, &c->msum, &c->meta, &c->kind, &c->tiles, &c->subs, &c->pieces, &c->tops, &c->highs, &c->highs2, &c->gflag, &c->gidx, &c->glen, &c->ginfo, &c->gbox, &c->glist,
                     &c->gmass, &c->bbox_part, &c->sys, &c->par, &c->info, &c->direct_part, &c->energy_part,
                     &c->glists, &c->far_pool, &c->near_pool, &c->far_next, &c->near_next,
                     &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_next, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,

@@ -191,6 +191,15 @@ __device__ __forceinline__ int system_of(const SysInfo *__restrict__ sys, int ns
   return lo;
 }
 
+// Cell coordinate (21 bits) of a position along one axis.
+__device__ __forceinline__ uint32_t quantise(double x, double lo, double scale) {
+  double u = __dsub_rn(x, lo);
+  u = __dmul_rn(u, scale);
+  if (!(u >= 0.0)) return 0u;
+  if (u >= (double)kQMax) return kQMax;
+  return (uint32_t)u;  // truncation == floor for u >= 0
+}
+
 // Cell coordinates (21 bits per axis) of a Morton key.
 __device__ __forceinline__ void key_cells(uint64_t k, uint32_t q[3]) {
   q[0] = q[1] = q[2] = 0;

@@ -32,19 +32,6 @@ struct alignas(16) NodeRec {
 };
 static_assert(sizeof(NodeRec) == 64, "node record must be 64 bytes");
 
-// What the moments pass reads of one cell, written by the level scatter in
-// position order (one coalesced record per cell instead of reads scattered
-// over the per-position arrays): the children's slots [c0, c0 + nc), the
-// cell's own slot and particle range, and its integer coordinates at its
-// geometric level (the level, or the chain cell's above a bucket) with that
-// level in bits 21-25 of cz_geo and bit 26 set for a bucket that is always
-// opened.
-struct alignas(16) CellRec {
-  int32_t c0, nc, slot, first, count;
-  uint32_t cx, cy, cz_geo;
-};
-static_assert(sizeof(CellRec) == 32, "cell record must be 32 bytes");
-
 // A particle's position and mass in input order, packed by the key pass so
 // that the gather into key order reads one aligned 32-byte record per
 // particle rather than two scattered reads.
@@ -76,6 +63,7 @@ struct DevInfo {
   int32_t max_level;
   int32_t n_cells;
   int32_t n_slots;
+  int32_t n_subs, n_pieces, n_tops, n_highs;  // lists of the moments pass
   int32_t n_groups;
   int32_t queue;          // walk work queue head
   unsigned long long interactions;
@@ -224,8 +212,11 @@ struct bh_ctx {
   bh::DevBuf qpack;             // FP32 [slots][8] 3 x the same, the trace T and 1.5 T, as read by the force sum
   bh::DevBuf far_slot;          // int32 per far-pool entry: node slot of a cell entry, -1 a particle
   bh::DevBuf meta;              // int8 [slots] 32 * kind + level (inspection only)
-  bh::DevBuf levels;            // int32 level counts, offsets and cursors (3 x 24)
-  bh::DevBuf lcells;            // CellRec cells grouped by level
+  bh::DevBuf kind;              // uint8 class of the owned cell in the moments pass
+  bh::DevBuf tiles;             // int32 tile sums of the child scan
+  bh::DevBuf subs;              // int32 roots of the subtrees
+  bh::DevBuf pieces, tops;      // int32 pieces of the cells above them, and those cells
+  bh::DevBuf highs, highs2;     // int32 cells above the pieces, and the same by level
   bh::DevBuf gflag;             // int32 group start flags
   bh::DevBuf gidx;              // int32 exclusive scan of the flags (group index)
   bh::DevBuf glen;              // int32 group length at its start position
@@ -334,13 +325,43 @@ struct TreeBuffers {
   int8_t *meta;           // per slot: 32 * kind + level (export only)
   int curve;              // key order: 0 Morton, 1 Peano-Hilbert
   bool any_empty;         // some system holds no particle (its root record is written apart)
-  int32_t *lcount, *loff, *lcursor;  // cells per level: counts, offsets [23], scatter cursors
-  CellRec *lcells;                   // cell records grouped by level
+  int nonempty;           // systems that hold particles
+  uint8_t *kind;          // class of the owned cell in the moments pass, flags (kKind...)
+  int32_t *tiles;         // tile sums of the child scan
+  int32_t *subs, *pieces, *tops, *highs, *highs2;  // lists of the moments pass
   int64_t slot_cap;       // capacity of nodes/msum/meta in slots
   uint64_t *sorted_keys;  // out: the buffer holding the sorted keys
 };
 int bbox_blocks_per_system(int nsys);
 void build_tree_device(TreeBuffers &B, hipStream_t s);
+// k_moments.hip: slots, node records and moments from the topology
+struct MomentArgs {
+  int64_t n;
+  int nsys, nonempty;
+  int64_t cap;  // capacity in slots
+  const SysInfo *sys;
+  const int8_t *level, *cdigit, *pdigit;
+  const int32_t *cfirst, *ccount, *cparent, *pparent, *mask;
+  int32_t *nchild, *cfc, *cslot;
+  const double *spos, *smass;
+  NodeRec *nodes;
+  double *msum, *qmom;
+  float4 *qpack;
+  int8_t *meta;
+  DevInfo *info;
+  const uint8_t *kind;
+  int32_t *tiles;
+  int32_t *subs, *pieces, *tops;  // roots of subtrees; of pieces (indices into tops); cells of pieces
+  int32_t *highs, *highs2;        // cells above the pieces, and the same by level
+};
+// Classes of cells by their particles and their parents' (k_moments.hip), and
+// flags: a bucket is owned here; this particle's parent is above the subtrees.
+constexpr int kClassMask = 7, kClassSub = 1, kClassTop = 2, kClassPiece = 3, kClassHigh = 4;
+constexpr int kKindBucket = 8, kKindLone = 128;
+int subtree_particles(bool quad); // most particles of a subtree
+int piece_particles(bool quad);   // and of a piece of the cells above
+void moments_device(const TreeBuffers &B, hipStream_t s);
+void empty_roots_device(const TreeBuffers &B, hipStream_t s);
 
 // k_groups.hip
 struct GroupBuffers {

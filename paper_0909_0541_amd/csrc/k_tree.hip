@@ -11,11 +11,8 @@
 // its opening test never accepts it while rejecting the child.
 //
 // Per-position arrays (index = Morton position) describe the cell owned
-// there.  Node records are then placed in slots: system roots first, the
-// children of every cell in consecutive slots in octant order.  Moments are
-// summed level by level from the deepest level up, each cell adding its
-// children in slot order starting from zero, so the FP64 sums are exactly
-// those of a recursive evaluation.
+// there.  Node records are then placed in slots (k_moments.hip): system roots
+// first, the children of every cell in consecutive slots in octant order.
 #include <algorithm>
 
 #include "bh_device.h"
@@ -125,14 +122,6 @@ __global__ void k_system_of_input(const SysInfo *__restrict__ sys, int nsys, int
   if (i < n) out[i] = system_of(sys, nsys, (int)i);
 }
 
-__device__ __forceinline__ uint32_t quantise(double x, double lo, double scale) {
-  double u = __dsub_rn(x, lo);
-  u = __dmul_rn(u, scale);
-  if (!(u >= 0.0)) return 0u;
-  if (u >= (double)kQMax) return kQMax;
-  return (uint32_t)u;  // truncation == floor for u >= 0
-}
-
 __device__ __forceinline__ uint64_t spread3(uint32_t v) {
   uint64_t x = v & 0x1fffffu;
   x = (x | (x << 32)) & 0x1f00000000ffffull;
@@ -200,14 +189,11 @@ __global__ void k_keys(const double *__restrict__ pos, const double *__restrict_
 }
 
 // Sorted copies and the inverse permutation; the octant masks cleared for the
-// topology pass and the level counters for the level pass.
+// topology pass.
 __global__ void k_gather(const uint32_t *__restrict__ vals,
                          const PosMass *__restrict__ pm, int64_t n, double *__restrict__ spos,
-                         double *__restrict__ smass, int32_t *__restrict__ perm, int32_t *__restrict__ mask,
-                         int32_t *__restrict__ lcount) {
+                         double *__restrict__ smass, int32_t *__restrict__ perm, int32_t *__restrict__ mask) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0)
-    for (int l = 0; l < 72; ++l) lcount[l] = 0;  // counts, offsets, cursors
   if (i >= n) return;
   uint32_t j = vals[i];
   perm[i] = (int32_t)j;
@@ -247,7 +233,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_sort(const double *__re
                                                               SysInfo *__restrict__ sys, uint64_t *__restrict__ keys,
                                                               double *__restrict__ spos, double *__restrict__ smass,
                                                               int32_t *__restrict__ perm, int32_t *__restrict__ mask,
-                                                              int32_t *__restrict__ lcount, DevInfo *info) {
+                                                              DevInfo *info) {
   extern __shared__ uint64_t lkeys[];  // [n rounded up to 64]
   __shared__ double red[6][kSmallThreads / kWave];
   __shared__ int32_t rank[kSmallTile];
@@ -257,7 +243,6 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_sort(const double *__re
   const bool first = blockIdx.x == 0;
   if (first) {
     reset_counters(info, t);
-    if (t < 72) lcount[t] = 0;
     __syncthreads();
   }
   double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
@@ -418,20 +403,25 @@ __device__ __forceinline__ void or_into_parent(int32_t *__restrict__ mask, int P
   if (active && tail && v) atomicOr(&mask[P], v);
 }
 
-// Parent and octant of every owned cell; octant masks of the parents.
-__global__ void k_cells(const uint64_t *__restrict__ keys, const int8_t *__restrict__ delta,
-                        const int32_t *__restrict__ owner, const int8_t *__restrict__ level, int64_t n,
-                        const SysInfo *__restrict__ sys, int nsys, const int32_t *__restrict__ cfirst,
-                        const int32_t *__restrict__ ccount, int32_t *__restrict__ cparent, int8_t *__restrict__ cdigit,
-                        int32_t *__restrict__ mask, DevInfo *info) {
+// Parents: of every owned cell (its octant too) and of every particle (a cell,
+// a bucket, or none for a system of one particle); octant masks of the parents;
+// classes of the cells for the moments pass (sub, piece: its limits).
+__global__ void k_parents(const uint64_t *__restrict__ keys, const int8_t *__restrict__ delta,
+                          const int32_t *__restrict__ owner, const int8_t *__restrict__ level, int64_t n,
+                          const SysInfo *__restrict__ sys, int nsys, const int32_t *__restrict__ cfirst,
+                          const int32_t *__restrict__ ccount, int32_t *__restrict__ cparent,
+                          int8_t *__restrict__ cdigit, int32_t *__restrict__ pparent, int8_t *__restrict__ pdigit,
+                          int32_t *__restrict__ mask, int sub, int piece, uint8_t *__restrict__ kind) {
   const int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int j = (int)jj;
-  const int l = (jj < n) ? level[j] : -1;
-  int P = -1, bit = 0;
+  const bool live = jj < n;
+  const int s = live ? system_of(sys, nsys, j) : 0;
+  const int lo = live ? sys[s].first : 0;
+  const int l = live ? level[j] : -1;
+  int P = -1, bit = 0, kd = 0;
   if (l >= 0) {
-    const int s = system_of(sys, nsys, j);
-    const int lo = sys[s].first;
-    const int a = cfirst[j], b = a + ccount[j] - 1;
+    const int c = ccount[j];
+    const int a = cfirst[j], b = a + c - 1;
     const int dl = (a > lo) ? delta[a - 1] : -1;
     const int dr = delta[b];
     const int lp = max(dl, dr);
@@ -446,360 +436,38 @@ __global__ void k_cells(const uint64_t *__restrict__ keys, const int8_t *__restr
       cdigit[j] = (int8_t)dg;
       bit = 1 << dg;
     }
+    const int cp = P >= 0 ? ccount[P] : INT32_MAX;
+    if (c > piece) kd = kClassHigh;
+    else if (c > sub) kd = cp > piece ? kClassPiece : kClassTop;
+    else if (cp > sub) kd = kClassSub;
+    if (l == kKeyLevels) kd |= kKindBucket;
   }
   or_into_parent(mask, P, bit, P >= 0);
-}
-
-// Parent of every particle: a cell (octant mask updated), a bucket, or none
-// (a system holding one particle).
-__global__ void k_particle_parents(const uint64_t *__restrict__ keys, const int8_t *__restrict__ delta,
-                                   const int32_t *__restrict__ owner, int64_t n, const SysInfo *__restrict__ sys,
-                                   int nsys, int32_t *__restrict__ pparent, int8_t *__restrict__ pdigit,
-                                   int32_t *__restrict__ mask) {
-  const int64_t ii = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = (int)ii;
-  int P = -1, bit = 0;
-  if (ii < n) {
-    const int s = system_of(sys, nsys, i);
-    const int lo = sys[s].first;
-    const int dl = (i > lo) ? delta[i - 1] : -1;
-    const int dr = delta[i];
+  P = -1;
+  bit = 0;
+  if (live) {
+    const int dl = (j > lo) ? delta[j - 1] : -1;
+    const int dr = delta[j];
     const int lp = max(dl, dr);
     if (lp < 0) {
-      pparent[i] = -1 - s;
-      pdigit[i] = 0;
+      pparent[j] = -1 - s;
+      pdigit[j] = 0;
     } else {
-      const int sp = (dl == lp) ? i - 1 : i;
+      const int sp = (dl == lp) ? j - 1 : j;
       P = owner[sp];
-      pparent[i] = P;
+      pparent[j] = P;
       if (lp == kKeyLevels) {
-        pdigit[i] = 0;  // bucket member: slot order is Morton order
+        pdigit[j] = 0;  // bucket member: slot order is Morton order
       } else {
-        const int dg = key_digit(keys[i], lp + 1);
-        pdigit[i] = (int8_t)dg;
+        const int dg = key_digit(keys[j], lp + 1);
+        pdigit[j] = (int8_t)dg;
         bit = 1 << dg;
       }
     }
+    if (P < 0 || ccount[P] > sub) kd |= kKindLone;
+    kind[j] = (uint8_t)kd;
   }
   or_into_parent(mask, P, bit, bit != 0);
-}
-
-__global__ void k_nchild(const int8_t *__restrict__ level, const int32_t *__restrict__ mask,
-                         const int32_t *__restrict__ ccount, int64_t n, int32_t *__restrict__ nchild) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const int l = level[j];
-  int c = 0;
-  if (l >= 0) c = (l == kKeyLevels) ? ccount[j] : __popc(mask[j]);
-  nchild[j] = c;
-}
-
-__device__ __forceinline__ int child_slot(int P, int dg, bool bucket_member, int i, const int32_t *__restrict__ cfc,
-                                          const int32_t *__restrict__ mask, int nsys) {
-  if (bucket_member) return nsys + cfc[P] + (i - P);
-  return nsys + cfc[P] + __popc(mask[P] & ((1 << dg) - 1));
-}
-
-// Slots of the cells; particle leaf records and their raw sums.
-__global__ void k_slots(const int8_t *__restrict__ level, const int32_t *__restrict__ cparent,
-                        const int8_t *__restrict__ cdigit, const int32_t *__restrict__ pparent,
-                        const int8_t *__restrict__ pdigit, const int32_t *__restrict__ cfc,
-                        const int32_t *__restrict__ mask, const double *__restrict__ spos,
-                        const double *__restrict__ smass, int64_t n, int nsys, int64_t cap,
-                        int32_t *__restrict__ cslot, NodeRec *__restrict__ nodes, double *__restrict__ msum,
-                        int8_t *__restrict__ meta, DevInfo *info) {
-  int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (jj >= n) return;
-  const int j = (int)jj;
-  if (level[j] >= 0) {
-    const int P = cparent[j];
-    int cs = (P < 0) ? (-1 - P) : child_slot(P, cdigit[j], false, j, cfc, mask, nsys);
-    if (cs < 0 || cs >= cap) {
-      atomicOr(&info->err, kErrBuild);
-      cs = 0;
-    }
-    cslot[j] = cs;
-  }
-  // particle j
-  const int P = pparent[j];
-  int slot;
-  if (P < 0) slot = -1 - P;
-  else slot = child_slot(P, pdigit[j], level[P] == kKeyLevels, j, cfc, mask, nsys);
-  if (slot < 0 || slot >= cap) {
-    atomicOr(&info->err, kErrBuild);
-    return;
-  }
-  const double m = smass[j];
-  NodeRec r;
-  r.com[0] = spos[3 * (int64_t)j];
-  r.com[1] = spos[3 * (int64_t)j + 1];
-  r.com[2] = spos[3 * (int64_t)j + 2];
-  r.m = m;
-  r.l = 0.0;
-  r.s = 0.0;
-  r.child = -1;
-  r.nchild = 0;
-  r.first = j;
-  r.count = 1;
-  nodes[slot] = r;
-  meta[slot] = (int8_t)(32 * kParticle + 31);
-  msum[4 * (int64_t)slot] = m;
-  msum[4 * (int64_t)slot + 1] = __dmul_rn(m, r.com[0]);
-  msum[4 * (int64_t)slot + 2] = __dmul_rn(m, r.com[1]);
-  msum[4 * (int64_t)slot + 3] = __dmul_rn(m, r.com[2]);
-}
-
-__global__ void k_empty_roots(const SysInfo *__restrict__ sys, int nsys, NodeRec *__restrict__ nodes,
-                              double *__restrict__ msum, int8_t *__restrict__ meta) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nsys || sys[s].count != 0) return;
-  NodeRec r;
-  r.com[0] = r.com[1] = r.com[2] = 0.0;
-  r.m = 0.0;
-  r.l = 0.0;
-  r.s = 0.0;
-  r.child = -1;
-  r.nchild = 0;
-  r.first = sys[s].first;
-  r.count = 0;
-  nodes[s] = r;
-  meta[s] = (int8_t)(32 * kEmpty + 31);
-  for (int k = 0; k < 4; ++k) msum[4 * (int64_t)s + k] = 0.0;
-}
-
-// Cells grouped by level: counts, offsets, then a scatter (order within a
-// level is irrelevant: every cell sums its own children in slot order).
-// Lanes of a wave with the same level are found with ballots (peer masks), so
-// that LDS and global counters see one atomic per wave and level.
-__device__ __forceinline__ unsigned long long level_peers(int l) {
-  unsigned long long peers = __ballot(l >= 0);
-#pragma unroll
-  for (int b = 0; b < 5; ++b) {
-    const unsigned long long m = __ballot(l >= 0 && ((l >> b) & 1));
-    peers &= ((l >> b) & 1) ? m : ~m;
-  }
-  return (l >= 0) ? peers : 0ull;
-}
-
-constexpr int kLevelTile = 16;  // positions per thread in the level kernels
-
-// The moments pass's record of the cell owned at position j (level lev).
-__device__ __forceinline__ CellRec cell_record(int j, int lev, const int8_t *__restrict__ level,
-                                               const int32_t *__restrict__ cparent, const int32_t *__restrict__ cslot,
-                                               const int32_t *__restrict__ cfc, const int32_t *__restrict__ nchild,
-                                               const int32_t *__restrict__ cfirst, const int32_t *__restrict__ ccount,
-                                               const double *__restrict__ spos, const SysInfo *__restrict__ sys,
-                                               int nsys) {
-  CellRec r;
-  r.c0 = nsys + cfc[j];
-  r.nc = nchild[j];
-  r.slot = cslot[j];
-  r.first = cfirst[j];
-  r.count = ccount[j];
-  // A bucket (level 21) is opened unless a chain of single-child cells sits
-  // above it: the opening bound shrinks down a chain (theta < 2/sqrt(3)), so
-  // the chain is accepted iff its deepest cell, at level 20, is; the bucket
-  // then carries that cell's side and s.
-  int geo = lev;
-  bool always_open = false;
-  if (lev == kKeyLevels) {
-    const int P = cparent[j];
-    const int lp = (P < 0) ? -1 : (int)level[P];
-    if (lp < kKeyLevels - 1) geo = kKeyLevels - 1;
-    else always_open = true;
-  }
-  // The cell's coordinates at level geo: the top geo bits of each quantised
-  // coordinate of any of its members (a cell of either curve is one aligned
-  // cube, a bucket one point), here the particle at the owning position,
-  // which lies in the cell.
-  const SysInfo &S = sys[system_of(sys, nsys, j)];
-  uint32_t q[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) q[k] = quantise(spos[3 * (int64_t)j + k], S.lo[k], S.scale) >> (kKeyLevels - geo);
-  r.cx = q[0];
-  r.cy = q[1];
-  r.cz_geo = q[2] | ((uint32_t)geo << 21) | (always_open ? (1u << 26) : 0u);
-  return r;
-}
-
-__global__ __launch_bounds__(256) void k_level_count(const int8_t *__restrict__ level, int64_t n,
-                                                     int32_t *__restrict__ lcount) {
-  __shared__ int32_t c[kKeyLevels + 1];
-  if (threadIdx.x <= kKeyLevels) c[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * kLevelTile;
-  for (int q = 0; q < kLevelTile; ++q) {
-    const int64_t j = base + (int64_t)q * blockDim.x + threadIdx.x;
-    const int l = (j < n) ? level[j] : -1;
-    const unsigned long long peers = level_peers(l);
-    if (l >= 0 && rank_below(peers) == 0) atomicAdd(&c[l], (int)__popcll(peers));
-  }
-  __syncthreads();
-  if (threadIdx.x <= kKeyLevels && c[threadIdx.x]) atomicAdd(&lcount[threadIdx.x], c[threadIdx.x]);
-}
-
-// Each block takes the level offsets from the counts (block 0 also stores
-// them, the cell count and the deepest level); rank = level offset + block
-// base (one global atomic per block and level on the zeroed cursors) + wave
-// base (one LDS atomic per wave, level and round) + lanes below with that
-// level.
-__global__ __launch_bounds__(256) void k_level_scatter(const int8_t *__restrict__ level, int64_t n,
-                                                       const int32_t *__restrict__ lcount, int32_t *__restrict__ loff,
-                                                       int32_t *__restrict__ lcursor, const int32_t *__restrict__ cparent,
-                                                       const int32_t *__restrict__ cslot, const int32_t *__restrict__ cfc,
-                                                       const int32_t *__restrict__ nchild,
-                                                       const int32_t *__restrict__ cfirst,
-                                                       const int32_t *__restrict__ ccount,
-                                                       const double *__restrict__ spos, const SysInfo *__restrict__ sys,
-                                                       int nsys, CellRec *__restrict__ lcells, DevInfo *info) {
-  __shared__ int32_t c[kKeyLevels + 1], base[kKeyLevels + 1], off[kKeyLevels + 2];
-  if (threadIdx.x <= kKeyLevels) c[threadIdx.x] = 0;
-  if (threadIdx.x == 0) {
-    int32_t sum = 0, deepest = 0;
-    for (int l = 0; l <= kKeyLevels; ++l) {
-      off[l] = sum;
-      sum += lcount[l];
-      if (lcount[l]) deepest = l;
-    }
-    off[kKeyLevels + 1] = sum;
-    if (blockIdx.x == 0) {
-      for (int l = 0; l <= kKeyLevels + 1; ++l) loff[l] = off[l];
-      info->n_cells = sum;
-      info->max_level = deepest;
-    }
-  }
-  __syncthreads();
-  const int64_t b0 = (int64_t)blockIdx.x * blockDim.x * kLevelTile;
-  int l[kLevelTile], pos[kLevelTile];
-  for (int q = 0; q < kLevelTile; ++q) {
-    const int64_t j = b0 + (int64_t)q * blockDim.x + threadIdx.x;
-    l[q] = (j < n) ? level[j] : -1;
-    const unsigned long long peers = level_peers(l[q]);
-    int wbase = 0;
-    if (l[q] >= 0 && rank_below(peers) == 0) wbase = atomicAdd(&c[l[q]], (int)__popcll(peers));
-    const int leader = (l[q] >= 0) ? (__ffsll((long long)peers) - 1) : 0;
-    wbase = __shfl(wbase, leader, kWave);
-    pos[q] = wbase + rank_below(peers);
-  }
-  __syncthreads();
-  if (threadIdx.x <= kKeyLevels && c[threadIdx.x])
-    base[threadIdx.x] = off[threadIdx.x] + atomicAdd(&lcursor[threadIdx.x], c[threadIdx.x]);
-  __syncthreads();
-  for (int q = 0; q < kLevelTile; ++q) {
-    const int64_t j = b0 + (int64_t)q * blockDim.x + threadIdx.x;
-    if (l[q] >= 0)
-      lcells[base[l[q]] + pos[q]] = cell_record((int)j, l[q], level, cparent, cslot, cfc, nchild, cfirst, ccount, spos,
-                                                sys, nsys);
-  }
-}
-
-// Moments of the cells of one level from their children's raw sums.  A
-// level's time is the latency of one cell's chain of reads: a cell reads its
-// record (written in position order by the level scatter), then its
-// children's sums, kMomChunk children at a time (indices clamped to the last
-// child, the extra values unused), before it adds any of them.  The sums add
-// the children in slot order starting from zero.
-constexpr int kMomChunk = 4;
-
-__global__ void k_moments(int lev, const CellRec *__restrict__ lcells, const int32_t *__restrict__ loff,
-                          const SysInfo *__restrict__ sys, int nsys, int64_t cap, NodeRec *__restrict__ nodes,
-                          double *__restrict__ msum, double *__restrict__ qmom, float4 *__restrict__ qpack,
-                          int8_t *__restrict__ meta, DevInfo *info) {
-  const int64_t end = loff[lev + 1];
-  // the system's frame: loaded once when there is one system
-  double slo[3] = {sys[0].lo[0], sys[0].lo[1], sys[0].lo[2]}, sside = sys[0].side;
-  for (int64_t k = (int64_t)loff[lev] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < end;
-       k += (int64_t)gridDim.x * blockDim.x) {
-  const CellRec cr = lcells[k];
-  const int c0 = cr.c0, nc = cr.nc, slot = cr.slot;
-  if (c0 < 0 || nc < 0 || (int64_t)c0 + nc > cap || slot < 0 || slot >= cap) {
-    atomicOr(&info->err, kErrBuild);
-    continue;
-  }
-  if (nsys > 1) {
-    const SysInfo &S = sys[system_of(sys, nsys, cr.first)];
-    slo[0] = S.lo[0];
-    slo[1] = S.lo[1];
-    slo[2] = S.lo[2];
-    sside = S.side;
-  }
-  double m = 0.0, mx = 0.0, my = 0.0, mz = 0.0;
-  for (int cb = 0; cb < nc; cb += kMomChunk) {
-    double2 a[kMomChunk], b[kMomChunk];
-#pragma unroll
-    for (int u = 0; u < kMomChunk; ++u) {
-      const double2 *q = reinterpret_cast<const double2 *>(msum + 4 * (int64_t)(c0 + min(cb + u, nc - 1)));
-      a[u] = q[0];
-      b[u] = q[1];
-    }
-#pragma unroll
-    for (int u = 0; u < kMomChunk; ++u) {
-      if (cb + u < nc) {
-        m = __dadd_rn(m, a[u].x);
-        mx = __dadd_rn(mx, a[u].y);
-        my = __dadd_rn(my, b[u].x);
-        mz = __dadd_rn(mz, b[u].y);
-      }
-    }
-  }
-  msum[4 * (int64_t)slot] = m;
-  msum[4 * (int64_t)slot + 1] = mx;
-  msum[4 * (int64_t)slot + 2] = my;
-  msum[4 * (int64_t)slot + 3] = mz;
-  const int geo = (int)((cr.cz_geo >> 21) & 31u);
-  const bool always_open = (cr.cz_geo >> 26) & 1u;
-  const double l = ldexp(sside, -geo);
-  const uint32_t q[3] = {cr.cx, cr.cy, cr.cz_geo & 0x1fffffu};
-  double c[3], com[3];
-  const double mv[3] = {mx, my, mz};
-  for (int k = 0; k < 3; ++k) {
-    double h = (double)q[k] + 0.5;
-    h = __dmul_rn(h, l);
-    c[k] = __dadd_rn(slo[k], h);
-    com[k] = (m > 0.0) ? mv[k] / m : c[k];
-  }
-  const double dx = __dsub_rn(c[0], com[0]), dy = __dsub_rn(c[1], com[1]), dz = __dsub_rn(c[2], com[2]);
-  const double d2 = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
-  NodeRec r;
-  r.com[0] = com[0];
-  r.com[1] = com[1];
-  r.com[2] = com[2];
-  r.m = m;
-  r.l = always_open ? INFINITY : l;
-  r.s = sqrt(d2);
-  r.child = c0;
-  r.nchild = nc;
-  r.first = cr.first;
-  r.count = cr.count;
-  nodes[slot] = r;
-  if (qmom) {
-    // second moments about the centre of mass from the children's own, each
-    // shifted to this centre (parallel axes); a particle's own are zero.  A
-    // child's mass and centre of mass come from its raw sums (its kind from
-    // meta), not from its 64-byte record; a massless child adds nothing.
-    double S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int ci = 0; ci < nc; ++ci) {
-      const int cs = c0 + ci;
-      const double *q = msum + 4 * (int64_t)cs;
-      const double mc = q[0];
-      if (!(mc > 0.0)) continue;
-      const double ex = __dsub_rn(q[1] / mc, com[0]), ey = __dsub_rn(q[2] / mc, com[1]),
-                   ez = __dsub_rn(q[3] / mc, com[2]);
-      const double sh[6] = {mc * ex * ex, mc * ey * ey, mc * ez * ez, mc * ex * ey, mc * ex * ez, mc * ey * ez};
-      const bool leaf = (meta[cs] >> 5) == kParticle;
-#pragma unroll
-      for (int k = 0; k < 6; ++k) S[k] = __dadd_rn(S[k], leaf ? sh[k] : __dadd_rn(qmom[6 * (int64_t)cs + k], sh[k]));
-    }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) qmom[6 * (int64_t)slot + k] = S[k];
-    // as the force sum reads them: 3 S and the trace T (and 1.5 T)
-    const double T = S[0] + S[1] + S[2];
-    qpack[2 * (int64_t)slot] = make_float4((float)(3.0 * S[0]), (float)(3.0 * S[1]), (float)(3.0 * S[2]),
-                                           (float)(3.0 * S[3]));
-    qpack[2 * (int64_t)slot + 1] = make_float4((float)(3.0 * S[4]), (float)(3.0 * S[5]), (float)T, (float)(1.5 * T));
-  }
-  meta[slot] = (int8_t)(lev == kKeyLevels ? 32 * kBucket + lev : lev);
-  }
 }
 
 inline unsigned blocks_for(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
@@ -822,7 +490,7 @@ static void launch_small(TreeBuffers &B, hipStream_t s) {
   const int n = (int)B.n;
   const size_t lds = sizeof(uint64_t) * (size_t)((n + kWave - 1) / kWave * kWave);
   k_small_sort<TILE><<<(unsigned)((n + TILE - 1) / TILE), kSmallThreads, lds, s>>>(
-      B.pos, B.mass, n, B.curve, B.sys, B.keys[0], B.spos, B.smass, B.perm, B.mask, B.lcount, B.info);
+      B.pos, B.mass, n, B.curve, B.sys, B.keys[0], B.spos, B.smass, B.perm, B.mask, B.info);
 }
 
 // Root cube, keys and the particles in key order.
@@ -852,7 +520,7 @@ static const uint64_t *sort_particles(TreeBuffers &B, hipStream_t s) {
       cur = radix_pass_by_system(B.keys[0], B.keys[1], B.vals[0], B.vals[1], cur, n, B.sys_in, shift, B.hist,
                                  B.scan_tmp, s);
   }
-  k_gather<<<blocks_for(n), 256, 0, s>>>(B.vals[cur], B.pm, n, B.spos, B.smass, B.perm, B.mask, B.lcount);
+  k_gather<<<blocks_for(n), 256, 0, s>>>(B.vals[cur], B.pm, n, B.spos, B.smass, B.perm, B.mask);
   return B.keys[cur];
 }
 
@@ -865,29 +533,16 @@ void build_tree_device(TreeBuffers &B, hipStream_t s) {
     k_bbox_partial<<<(unsigned)(nsys * bps), 256, 0, s>>>(B.pos, B.sys, bps, B.bbox_part, B.info);
     k_bbox_final<<<(unsigned)nsys, 256, 0, s>>>(B.bbox_part, bps, B.sys);
     B.sorted_keys = B.keys[0];
-    k_empty_roots<<<blocks_for(nsys), 256, 0, s>>>(B.sys, nsys, B.nodes, B.msum, B.meta);
+    empty_roots_device(B, s);
     return;
   }
   const uint64_t *keys = sort_particles(B, s);
   B.sorted_keys = const_cast<uint64_t *>(keys);
   k_owner<<<blocks_for(n), 256, 0, s>>>(keys, B.delta, n, B.sys, nsys, B.owner, B.level, B.cfirst, B.ccount);
-  k_cells<<<blocks_for(n), 256, 0, s>>>(keys, B.delta, B.owner, B.level, n, B.sys, nsys, B.cfirst, B.ccount,
-                                         B.cparent, B.cdigit, B.mask, B.info);
-  k_particle_parents<<<blocks_for(n), 256, 0, s>>>(keys, B.delta, B.owner, n, B.sys, nsys, B.pparent, B.pdigit,
-                                                    B.mask);
-  k_nchild<<<blocks_for(n), 256, 0, s>>>(B.level, B.mask, B.ccount, n, B.nchild);
-  scan_exclusive_i32(B.nchild, B.cfc, n, &B.info->n_slots, B.scan_tmp, s);
-  k_slots<<<blocks_for(n), 256, 0, s>>>(B.level, B.cparent, B.cdigit, B.pparent, B.pdigit, B.cfc, B.mask, B.spos,
-                                         B.smass, n, nsys, B.slot_cap, B.cslot, B.nodes, B.msum, B.meta, B.info);
-  if (B.any_empty) k_empty_roots<<<blocks_for(nsys), 256, 0, s>>>(B.sys, nsys, B.nodes, B.msum, B.meta);
-  k_level_count<<<blocks_for(n, 256 * kLevelTile), 256, 0, s>>>(B.level, n, B.lcount);
-  k_level_scatter<<<blocks_for(n, 256 * kLevelTile), 256, 0, s>>>(B.level, n, B.lcount, B.loff, B.lcursor,
-                                                                   B.cparent, B.cslot, B.cfc, B.nchild, B.cfirst,
-                                                                   B.ccount, B.spos, B.sys, nsys, B.lcells, B.info);
-  const unsigned mgrid = (unsigned)std::min<int64_t>(blocks_for(n), 512);
-  for (int lev = kKeyLevels; lev >= 0; --lev)
-    k_moments<<<mgrid, 256, 0, s>>>(lev, B.lcells, B.loff, B.sys, nsys, B.slot_cap, B.nodes, B.msum, B.qmom, B.qpack,
-                                    B.meta, B.info);
+  k_parents<<<blocks_for(n), 256, 0, s>>>(keys, B.delta, B.owner, B.level, n, B.sys, nsys, B.cfirst, B.ccount,
+                                           B.cparent, B.cdigit, B.pparent, B.pdigit, B.mask,
+                                           subtree_particles(B.qmom != nullptr), piece_particles(B.qmom != nullptr), B.kind);
+  moments_device(B, s);
 }
 
 }  // namespace bh
