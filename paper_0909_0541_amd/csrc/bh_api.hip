@@ -418,7 +418,7 @@ void bh_destroy(bh_ctx *c) {
                     &c->split_ctr, &c->gsplit, &c->gnseg, &c->gsegfirst, &c->skeys[0], &c->skeys[1], &c->svals[0],
                     &c->svals[1], &c->shist, &c->sscan, &c->srows, &c->spbase, &c->sgroups, &c->psum,
                     &c->wide_pool, &c->wide_slot, &c->wide_gblocks, &c->wide_gstat, &c->wide_binfo, &c->wide_psum,
-                    &c->out_groups, &c->out_info, &c->out_nodes, &c->out_tasks, &c->out_rows, &c->out_near, &c->out_mass,
+                    &c->tile_info, &c->tile_groups, &c->tile_psum, &c->out_groups, &c->out_info, &c->out_nodes, &c->out_tasks, &c->out_rows, &c->out_near, &c->out_mass,
                     &c->qmom, &c->qpack, &c->far_slot};
   for (DevBuf *b : bufs) free_buf(*b);
   if (c->graph) (void)hipGraphExecDestroy(c->graph);
@@ -555,12 +555,14 @@ constexpr int kOutBlock = 256;
 // Whether the force call takes the workgroup walk: the tuning options (split
 // cap, list tile, waves), each of which asks for the single-wave walk in a
 // given form, are at their defaults.  A context that integrates (a kick, a
-// drift or leapfrog steps ran on it) stays with the single waves at every
-// size: the FP32 sums then keep one list order and one length whatever the
-// particle count, and with them the rounding errors that add up along a
-// trajectory and in its energy.
-static bool wide_path(const bh_ctx *c) {
-  return !c->integrates && c->opt.split_visits == 0 && c->opt.list_tile == 0 && c->opt.waves_per_cu == 0 &&
+// drift or leapfrog steps ran on it) stays with the single waves' lists at
+// every size: the FP32 sums then keep one list order and one length whatever
+// the particle count, and with them the rounding errors that add up along a
+// trajectory and in its energy.  (Outliers hold too few members to matter
+// there: the energy of 30,011 Plummer particles moves by 3e-12.)  At these
+// sizes its lists are summed by tiles.
+static bool few_groups(const bh_ctx *c) {
+  return c->opt.split_visits == 0 && c->opt.list_tile == 0 && c->opt.waves_per_cu == 0 &&
          c->n_crit >= kWideMinCrit && c->n <= kWideGroups * c->n_crit && wide_fits(c->n);
 }
 
@@ -681,7 +683,7 @@ static bh_status forces_wide(bh_ctx *c, const float *theta_group, float *acc, fl
     st = timer_start(c, c->t_force);
     if (st) return st;
     force_blocks_device(A, c->num_cu, c->stream);
-    block_reduce_device(A, c->num_cu, c->stream);
+    block_reduce_device(A, c->num_cu, true, c->stream);
     if (outliers) task_reduce_device(A, c->stream);
     st = timer_stop(c, c->t_force);
     if (st) return st;
@@ -699,6 +701,61 @@ static bh_status forces_wide(bh_ctx *c, const float *theta_group, float *acc, fl
   c->last_segments = c->last_split_groups = c->last_depth = 0;
   c->have_forces = true;
   return BH_OK;
+}
+
+// The sums over the single waves' lists by tiles, and the outliers' (O).
+static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &O, bool outliers, float *acc,
+                              float *pot) {
+  // (a tile takes a chunk of a pool: no more rows than chunks)
+  const size_t rows = (size_t)W.far_cap + (size_t)W.near_cap;
+  bh_status st = ensure(c, c->tile_info, sizeof(int4) * rows, "list tiles");
+  if (!st) st = ensure(c, c->tile_groups, sizeof(int2) * (size_t)c->n, "list tiles");
+  if (!st) st = ensure(c, c->tile_psum, sizeof(double) * 4 * rows * (size_t)c->n_crit, "partial sums");
+  if (st) return st;
+  TileArgs T{};
+  T.ginfo = W.ginfo;
+  T.glist = W.glist;
+  T.gbox = W.gbox;
+  T.glists = W.glists;
+  T.far_next = W.far_next;
+  T.near_next = W.near_next;
+  T.far_pool = W.far_pool;
+  T.near_pool = W.near_pool;
+  T.far_slot = W.far_slot;
+  T.qpack = W.far_slot ? P<float4>(c->qpack) : nullptr;
+  T.far_tile = W.far_tile;
+  T.near_tile = W.near_tile;
+  T.n_crit = c->n_crit;
+  T.spos = P<double>(c->spos);
+  T.par = W.par;
+  T.info = W.info;
+  T.gblocks = P<int2>(c->tile_groups);
+  T.tinfo = P<int4>(c->tile_info);
+  T.psum = P<double>(c->tile_psum);
+  WideArgs R{};
+  R.ginfo = W.ginfo;
+  R.info = W.info;
+  R.n_crit = c->n_crit;
+  R.gblocks = T.gblocks;
+  R.psum = T.psum;
+  R.par = W.par;
+  R.smass = P<double>(c->smass);
+  R.perm = P<int32_t>(c->perm);
+  R.acc = acc;
+  R.pot = pot;
+  st = timer_start(c, c->t_force);
+  if (st) return st;
+  force_tiles_device(T, c->num_cu, c->stream);
+  block_reduce_device(R, c->num_cu, false, c->stream);
+  if (outliers) {
+    // (after the lists' sums, which leave an outlier's members with none)
+    force_blocks_device(O, c->num_cu, c->stream);
+    task_reduce_device(O, c->stream);
+  }
+  st = timer_stop(c, c->t_force);
+  if (!st) st = hip_check(c, hipGetLastError(), "kernel launch (force)");
+  c->have_forces = !st;
+  return st;
 }
 
 static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *theta_sys, const float *theta_group,
@@ -726,7 +783,8 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     c->have_forces = true;
     return BH_OK;
   }
-  if (wide_path(c)) return forces_wide(c, theta_group, acc, pot);
+  const bool few = few_groups(c);
+  if (few && !c->integrates) return forces_wide(c, theta_group, acc, pot);
   // list pools: start from an estimate (32 far and 4 near entries per
   // particle), grow to what a walk reports it needed; the capacities count
   // chunks of the current tile (recounted when the tile changes)
@@ -759,11 +817,11 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   // split walks (long lists walked and summed by several waves)
   const int grid = c->num_cu * (c->opt.waves_per_cu > 0 ? c->opt.waves_per_cu : c->walk_bpc);
   const int fgrid = c->num_cu * (c->opt.waves_per_cu > 0 ? c->opt.waves_per_cu : (quad ? c->force_bpc_q : c->force_bpc));
-  // Split walks only on request; by default outliers go to the workgroup
-  // walk (not on a context that integrates, see wide_path).
+  // Split walks only on request; by default outliers go to the workgroup walk.
   const int visit_cap = std::max(c->opt.split_visits, 0);
   if (!c->capturing) c->out_off = false;
-  bool outliers = c->opt.split_visits == 0 && !c->integrates && c->n <= kOutMaxN && 2 * c->n > kOutMin && !c->out_off;
+  const int out_min = few ? kOutMinWide : kOutMin;
+  bool outliers = c->opt.split_visits == 0 && c->n <= kOutMaxN && 2 * c->n > out_min && !c->out_off;
   if (outliers) wide_capacity(c, kOutBlock, 2 * c->n / kOutBlock + 4096);
   if (c->seg_cap == 0) {
     c->task_cap = 4096;
@@ -776,6 +834,10 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     order_clear_device(P<int32_t>(c->order_hist), c->stream);  // every later call leaves it zero
   }
   if (st) return st;
+  if (few && !c->info_event) {
+    st = hip_check(c, hipEventCreateWithFlags(&c->info_event, hipEventDisableTiming), "hipEventCreate");
+    if (st) return st;
+  }
   SplitBuffers S{};
   int32_t nsegs_host = 0;
   bool have_out = outliers;  // (a capture replays on other particles: it always has the outliers' launches)
@@ -826,7 +888,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     W.seg_cap = c->seg_cap;
     W.gsplit = P<int32_t>(c->gsplit);
     W.visit_cap = visit_cap;
-    W.out_min = outliers ? kOutMin : 0;
+    W.out_min = outliers ? out_min : 0;
     W.n_crit = c->n_crit;
     WideArgs A{};
     if (outliers) {
@@ -845,7 +907,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     walk_lists_device(W, grid, c->stream);
     c->xq_clean = false;
     // (outside a capture the host looks first whether there are outliers)
-    if (outliers && c->capturing) {
+    if (outliers && (c->capturing || few)) {
       walk_outliers_device(A, c->stream);
       walk_tasks_device(A, c->num_cu, c->stream);
     }
@@ -855,10 +917,25 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     if (st) return st;
     // the pools must have held every list before the sums may run; a captured
     // step cannot wait here: an overflow then leaves kErrPool for bh_sync
-    if (c->capturing) break;
-    st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
-                   "hipMemcpyAsync info");
-    if (st) return st;
+    if (c->capturing && !few) break;
+    if (!c->capturing) {
+      st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
+                     "hipMemcpyAsync info");
+      if (st) return st;
+    }
+    if (few) {
+      // (queued behind the walk; they leave at once when a list did not fit)
+      if (!c->capturing) {
+        st = hip_check(c, hipEventRecord(c->info_event, c->stream), "hipEventRecord");
+        if (st) return st;
+      }
+      st = forces_tiles(c, W, A, outliers, acc, pot);
+      if (st || c->capturing) return st;
+      st = hip_check(c, hipEventSynchronize(c->info_event), "hipEventSynchronize");
+      if (st) return st;
+      c->last_segments = c->last_split_groups = c->last_depth = 0;
+      if (!(c->info_host->err & (kErrPool | kErrWide))) return BH_OK;
+    }
     if (visit_cap > 0) {
       st = hip_check(c, hipMemcpyAsync(c->split_host, W.ctr, sizeof(SplitCounters), hipMemcpyDeviceToHost,
                                        c->stream), "hipMemcpyAsync split counters");
@@ -866,7 +943,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     }
     st = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
     if (st) return st;
-    have_out = outliers && c->info_host->n_out > 0;
+    have_out = outliers && !few && c->info_host->n_out > 0;
     if (have_out) {
       walk_outliers_device(A, c->stream);
       walk_tasks_device(A, c->num_cu, c->stream);

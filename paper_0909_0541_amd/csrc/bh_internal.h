@@ -83,6 +83,7 @@ struct DevInfo {
   int32_t rows;                 // list blocks it used (rows of partial sums)
   int32_t n_out;                // outlier groups (more than kOutMax: an error, the host walks another way)
   int32_t tasks;                // their walk tasks
+  int32_t tile_rows;            // tiles of the lists (k_tile_rows)
   alignas(128) int32_t far_chunks;   // runs of kChunkRun list chunks taken (may exceed the pool: then it is the need)
   alignas(128) int32_t near_chunks;
   alignas(128) int32_t xq[8 * kLineInts];  // walk queue heads, one per XCD: xq[x * kLineInts]
@@ -243,6 +244,7 @@ struct bh_ctx {
   // lists in blocks (sizes at which a group is walked by a workgroup)
   bh::DevBuf wide_pool, wide_slot, wide_gblocks, wide_gstat, wide_binfo, wide_psum;
   bh::DevBuf out_groups, out_info, out_nodes, out_tasks, out_rows, out_near, out_mass;  // outliers and their walk tasks
+  bh::DevBuf tile_info, tile_groups, tile_psum;  // sums by list tiles: rows, rows of a group, partial sums
   int32_t wide_cap = 0, wide_block = 0;  // blocks in the pool, entries per block
   bool counters_clean = false;           // the force counters are known to be 0 (reset by make_groups)
   hipEvent_t info_event = nullptr;       // completion of a read-back of the counters
@@ -513,6 +515,24 @@ struct ForceArgs {
   const int32_t *far_slot;    // quadrupole sums: node slot of each far entry (near entries: residue .w)
   const float4 *qpack;        // quadrupole sums: [slots][2] second moments
 };
+// The same sums by tiles (k_force_tiles): rows of partial sums, one per tile.
+struct TileArgs {
+  const int32_t *ginfo, *glist;
+  const double *gbox;
+  const int32_t *glists, *far_next, *near_next;
+  const float4 *far_pool, *near_pool;
+  const int32_t *far_slot;
+  const float4 *qpack;
+  int far_tile, near_tile;
+  int n_crit;
+  const double *spos;
+  const SysParam *par;
+  DevInfo *info;
+  int2 *gblocks;  // per group: first row, rows
+  int4 *tinfo;    // per row: group, tile, entries, near
+  double *psum;   // [rows][n_crit][4]
+};
+void force_tiles_device(const TileArgs &a, int num_cu, hipStream_t s);
 void force_lists_device(const ForceArgs &a, int grid, hipStream_t s);
 // The force items in queue order (k_order.hip), with the list statistics;
 // hist holds order_hist_bytes() and is zero on entry
@@ -578,7 +598,7 @@ void walk_wide_device(const WideArgs &a, int64_t n, int num_cu, hipStream_t s);
 void walk_outliers_device(const WideArgs &a, hipStream_t s);  // a.out over the large cells
 void walk_tasks_device(const WideArgs &a, int num_cu, hipStream_t s);
 void force_blocks_device(const WideArgs &a, int num_cu, hipStream_t s);
-void block_reduce_device(const WideArgs &a, int num_cu, hipStream_t s);  // members of ordinary groups
+void block_reduce_device(const WideArgs &a, int num_cu, bool stats, hipStream_t s);  // members of ordinary groups
 void task_reduce_device(const WideArgs &a, hipStream_t s);               // members of outliers
 
 // k_misc.hip

@@ -118,10 +118,10 @@ __device__ __forceinline__ void fold(Member &M) {
 // A stage of entries [lo, hi) in LDS against this lane's member: all of them
 // (R = 1, read as broadcasts), or with R lane partitions those of partition
 // sub.  qs: the entries' packed moments and cell: node slots (-1 a particle).
-template <bool NEAR, bool QUAD>
+// U entries' terms at a time: with QUAD the order in which they are added.
+template <bool NEAR, bool QUAD, int U = QUAD ? 2 : 4>
 __device__ __forceinline__ void stage_sum(Member &M, const float4 *e, const float4 *l, const int32_t *slot,
                                           const float4 *qs, int lo, int hi, int sub, int R, float eps2) {
-  constexpr int U = QUAD ? 2 : 4;
   int k = lo + sub;
   for (; k + (U - 1) * R < hi; k += U * R) {
     float4 ev[U], lv[U], qa[U], qb[U];

@@ -278,7 +278,169 @@ __global__ __launch_bounds__(kWave) void k_force_lists(ForceArgs a, const float4
   }
 }
 
+// Rows of the tile sums: one per tile of each group's list (far tiles, then
+// near ones), numbered by groups; list statistics.  One workgroup; bound by
+// following the tiles' links (a dozen reads).
+__global__ __launch_bounds__(1024) void k_tile_rows(TileArgs a) {
+  __shared__ int wsum[1024 / kWave];
+  const int t = threadIdx.x, w = t / kWave;
+  if (a.info->err & (kErrPool | kErrWide)) {  // lists incomplete: the host walks again
+    if (t == 0) a.info->tile_rows = 0;
+    return;
+  }
+  const int G = a.info->n_groups;
+  int base = 0, longest = 0;
+  unsigned long long inter = 0, entries = 0;
+  for (int g0 = 0; g0 < G; g0 += 1024) {
+    const int g = g0 + t;
+    int4 L = make_int4(-1, 0, -1, 0);
+    if (g < G) {
+      L = reinterpret_cast<const int4 *>(a.glists)[g];
+      const int len = max(a.glist[g], 0);
+      inter += (unsigned long long)a.ginfo[3 * g + 1] * (unsigned long long)max(len - 1, 0);
+      entries += (unsigned long long)len;
+      longest = max(longest, len);
+    }
+    const int nf = (L.y + a.far_tile - 1) / a.far_tile, rows = nf + (L.w + a.near_tile - 1) / a.near_tile;
+    const int inc = wave_inclusive_sum(rows);
+    if (lane_id() == kWave - 1) wsum[w] = inc;
+    __syncthreads();
+    int row = base + inc - rows;
+    for (int k = 0; k < 1024 / kWave; ++k) {
+      if (k < w) row += wsum[k];
+      base += wsum[k];
+    }
+    __syncthreads();
+    if (g < G) a.gblocks[g] = make_int2(row, rows);
+    int ch = L.x;
+    for (int left = L.y; left > 0; left -= a.far_tile) {
+      a.tinfo[row++] = make_int4(g, ch, min(left, a.far_tile), 0);
+      if (left > a.far_tile) ch = a.far_next[ch];
+    }
+    ch = L.z;
+    for (int left = L.w; left > 0; left -= a.near_tile) {
+      a.tinfo[row++] = make_int4(g, ch, min(left, a.near_tile), 1);
+      if (left > a.near_tile) ch = a.near_next[ch];
+    }
+  }
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    inter += __shfl_xor(inter, d, kWave);
+    entries += __shfl_xor(entries, d, kWave);
+    longest = max(longest, __shfl_xor(longest, d, kWave));
+  }
+  if (lane_id() == 0 && entries) {
+    atomicAdd(&a.info->interactions, inter);
+    atomicAdd(&a.info->list_entries, entries);
+    atomicMax(&a.info->max_list, longest);
+  }
+  if (t == 0) a.info->tile_rows = base;
+}
+
+// The sums of k_force_lists taken apart by tiles: a workgroup per tile, a wave
+// per block of 64 members, each member's FP32 chain over the tile's entries
+// (or its lane partition's) the same as there, so the values differ only in
+// the order in which tiles and partitions are added in FP64.  For contexts
+// that integrate with too few groups to fill the chip with a wave each: the
+// longest list no longer decides (30,011 Plummer particles: 602 us with a wave
+// per group, NUMS with a workgroup per tile).  Entries are staged in LDS, a
+// whole tile at once: a lone wave waits for every scalar load.
+template <bool QUAD>
+__global__ __launch_bounds__(256) void k_force_tiles(TileArgs a) {
+  constexpr int kStage = QUAD ? 256 : kDefaultTile;
+  __shared__ float4 e[kStage + (QUAD ? kStage : 0)];  // entries; the second half (QUAD: array) residues
+  __shared__ float4 qs[QUAD ? 2 * kStage : 1];
+  __shared__ int32_t sl[QUAD ? kStage : 1];
+  constexpr int kHalf = QUAD ? kStage : kStage / 2;
+  const int t = threadIdx.x, NT = blockDim.x, lane = lane_id(), blk = t / kWave;
+  const int rows = a.info->tile_rows;
+  for (int row = blockIdx.x; row < rows; row += gridDim.x) {
+    const int4 b = a.tinfo[row];
+    const int g = __builtin_amdgcn_readfirstlane(b.x), cnt = __builtin_amdgcn_readfirstlane(b.z);
+    const bool near = __builtin_amdgcn_readfirstlane(b.w) != 0;
+    const int ch = __builtin_amdgcn_readfirstlane(b.y);
+    const float4 *pool = near ? a.near_pool + (int64_t)ch * (2 * a.near_tile) : a.far_pool + (int64_t)ch * a.far_tile;
+    const int gf = a.ginfo[3 * g], gc = a.ginfo[3 * g + 1], gs = a.ginfo[3 * g + 2];
+    const int m = min(gc - blk * kWave, kWave);  // (may be <= 0)
+    int R = 1;
+    while (R < kWave && max(m, 1) * (2 * R) <= kWave) R *= 2;
+    const int W = kWave / R, part = lane / W, u = lane % W;
+    double cen[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      cen[k] = __dmul_rn(__dadd_rn(a.gbox[6 * (int64_t)g + k], a.gbox[6 * (int64_t)g + 3 + k]), 0.5);
+    const double eps = a.par[gs].eps;
+    const float eps2 = (float)(eps * eps);
+    Member M;
+    {
+      double x = 0.0, y = 0.0, z = 0.0;
+      if (u < m) {
+        const double *q = a.spos + 3 * (int64_t)(gf + blk * kWave + u);
+        x = __dsub_rn(q[0], cen[0]);
+        y = __dsub_rn(q[1], cen[1]);
+        z = __dsub_rn(q[2], cen[2]);
+      }
+      member_init(M, x, y, z);
+    }
+    const int step = near && !QUAD ? kHalf : kStage;
+    for (int s0 = 0; s0 < cnt; s0 += step) {
+      const int s = min(step, cnt - s0);
+      __syncthreads();
+      for (int k = t; k < s; k += NT) {
+        e[k] = pool[s0 + k];
+        int slot = -1;
+        if (near) {
+          const float4 r = pool[a.near_tile + s0 + k];
+          e[kHalf + k] = r;
+          if (QUAD) slot = __float_as_int(r.w);
+        } else if (QUAD) {
+          slot = a.far_slot[(int64_t)ch * a.far_tile + s0 + k];
+        }
+        if (QUAD) {
+          sl[k] = slot;
+          const int64_t q = 2 * (int64_t)max(slot, 0);
+          qs[2 * k] = a.qpack[q];
+          qs[2 * k + 1] = a.qpack[q + 1];
+        }
+      }
+      __syncthreads();
+      // (with second moments in the same blocks as chunk_sum and chunk_part)
+      if (m > 0) {
+        if (QUAD && R == 1) {
+          if (near)
+            stage_sum<true, QUAD, kUQuad>(M, e, e + kHalf, sl, qs, 0, s, part, R, eps2);
+          else
+            stage_sum<false, QUAD, kUQuad>(M, e, e, sl, qs, 0, s, part, R, eps2);
+        } else if (near) {
+          stage_sum<true, QUAD>(M, e, e + kHalf, sl, qs, 0, s, part, R, eps2);
+        } else {
+          stage_sum<false, QUAD>(M, e, e, sl, qs, 0, s, part, R, eps2);
+        }
+      }
+    }
+    fold(M);
+    double v[4] = {M.dx, M.dy, M.dz, M.dp};
+    for (int d = W; d < kWave; d <<= 1)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] += shfl_xor_d(v[k], d);
+    if (part == 0 && u < m) {
+      double2 *q = reinterpret_cast<double2 *>(a.psum + 4 * ((int64_t)row * a.n_crit + blk * kWave + u));
+      q[0] = make_double2(v[0], v[1]);
+      q[1] = make_double2(v[2], v[3]);
+    }
+  }
+}
+
 }  // namespace
+
+void force_tiles_device(const TileArgs &a, int num_cu, hipStream_t s) {
+  const int nt = a.n_crit <= 64 ? 64 : (a.n_crit <= 128 ? 128 : 256);
+  k_tile_rows<<<1, 1024, 0, s>>>(a);
+  if (a.far_slot && a.qpack)
+    k_force_tiles<true><<<(unsigned)(num_cu * 8), nt, 0, s>>>(a);
+  else
+    k_force_tiles<false><<<(unsigned)(num_cu * 8), nt, 0, s>>>(a);
+}
 
 int force_lists_blocks_per_cu(bool quad) {
   int b = 0;

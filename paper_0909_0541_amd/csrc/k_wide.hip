@@ -505,12 +505,14 @@ __global__ __launch_bounds__(256) void k_force_blocks(WideArgs a) {
 }
 
 // One member per thread: its rows in list order (far blocks, then near ones),
-// four loads in flight.  The last workgroup adds up the list statistics (an
-// atomic per group and counter, all on one line, took longer than the walk).
+// four loads in flight.  With STATS the last workgroup adds up the list
+// statistics (an atomic per group and counter, all on one line, took longer
+// than the walk).
+template <bool STATS>
 __global__ __launch_bounds__(256) void k_block_reduce(WideArgs a, int width) {
   if (a.info->err & (kErrPool | kErrWide)) return;
   const int G = a.info->n_groups;
-  if (blockIdx.x == gridDim.x - 1) {
+  if (STATS && blockIdx.x == gridDim.x - 1) {
     ListStats st;
     for (int g = threadIdx.x; g < G; g += 256) {
       if (a.gblocks[g].y < 0) continue;  // (an outlier: k_task_reduce)
@@ -522,7 +524,7 @@ __global__ __launch_bounds__(256) void k_block_reduce(WideArgs a, int width) {
   }
   const int per = 256 / width;  // groups per workgroup
   const int u = threadIdx.x % width;
-  for (int g = blockIdx.x * per + threadIdx.x / width; g < G; g += (gridDim.x - 1) * per) {
+  for (int g = blockIdx.x * per + threadIdx.x / width; g < G; g += (gridDim.x - STATS) * per) {
     const int gf = a.ginfo[3 * g], gc = a.ginfo[3 * g + 1], gs = a.ginfo[3 * g + 2];
     const int2 b = a.gblocks[g];
     if (u >= gc || b.y < 0) continue;
@@ -687,9 +689,12 @@ void force_blocks_device(const WideArgs &a, int num_cu, hipStream_t s) {
     k_force_blocks<false><<<grid, 256, 0, s>>>(a);
 }
 
-void block_reduce_device(const WideArgs &a, int num_cu, hipStream_t s) {
+void block_reduce_device(const WideArgs &a, int num_cu, bool stats, hipStream_t s) {
   const int width = a.n_crit <= 64 ? 64 : (a.n_crit <= 128 ? 128 : 256);
-  k_block_reduce<<<(unsigned)(num_cu * 8 + 1), 256, 0, s>>>(a, width);
+  if (stats)
+    k_block_reduce<true><<<(unsigned)(num_cu * 8 + 1), 256, 0, s>>>(a, width);
+  else
+    k_block_reduce<false><<<(unsigned)(num_cu * 8), 256, 0, s>>>(a, width);
 }
 
 void task_reduce_device(const WideArgs &a, hipStream_t s) {
