@@ -414,7 +414,7 @@ void bh_destroy(bh_ctx *c) {
                     &c->hist, &c->nodes, &c->msum, &c->meta, &c->kind, &c->tiles, &c->subs, &c->pieces, &c->tops, &c->highs, &c->highs2, &c->gflag, &c->gidx, &c->glen, &c->ginfo, &c->gbox, &c->glist,
                     &c->gmass, &c->bbox_part, &c->sys, &c->par, &c->info, &c->direct_part, &c->energy_part,
                     &c->glists, &c->far_pool, &c->near_pool, &c->far_next, &c->near_next,
-                    &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_next, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
+                    &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_stat, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
                     &c->split_ctr, &c->gsplit, &c->gnseg, &c->gsegfirst, &c->skeys[0], &c->skeys[1], &c->svals[0],
                     &c->svals[1], &c->shist, &c->sscan, &c->srows, &c->spbase, &c->sgroups, &c->psum,
                     &c->wide_pool, &c->wide_slot, &c->wide_gblocks, &c->wide_gstat, &c->wide_binfo, &c->wide_psum,
@@ -1091,21 +1091,14 @@ static bh_status particle_common(bh_ctx *c, const double *eps_sys, const double 
   if (st) return st;
   st = upload(c, c->par.p, c->par_host.data(), sizeof(SysParam) * (size_t)c->nsys);
   if (st) return st;
-  st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
-                 "hipMemcpyAsync info");
-  if (st) return st;
-  st = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
-  if (st) return st;
-  const int64_t nslots = (int64_t)c->nsys + c->info_host->n_slots;
-  st = ensure(c, c->pp_next, sizeof(int32_t) * (size_t)std::max<int64_t>(nslots, 1), "thread pointers");
+  st = ensure(c, c->pp_stat, particle_stat_bytes(c->n, c->nsys), "list statistics");
   if (st) return st;
   reset_list_counters(P<DevInfo>(c->info), c->stream);
   c->counters_clean = false;
   st = timer_start(c, c->t_particle);
   if (st) return st;
-  particle_forces_device(P<NodeRec>(c->nodes), (int)nslots, c->nsys, P<SysInfo>(c->sys), P<SysParam>(c->par),
-                         P<double>(c->spos), P<int32_t>(c->perm), c->n, P<int32_t>(c->pp_next), acc, pot,
-                         P<DevInfo>(c->info), c->stream);
+  particle_forces_device(P<NodeRec>(c->nodes), c->nsys, P<SysInfo>(c->sys), P<SysParam>(c->par), P<double>(c->spos),
+                         P<int32_t>(c->perm), c->n, acc, pot, P<int4>(c->pp_stat), P<DevInfo>(c->info), c->stream);
   st = timer_stop(c, c->t_particle);
   if (st) return st;
   st = hip_check(c, hipGetLastError(), "kernel launch (per-particle walk)");

@@ -239,6 +239,7 @@ struct bh_ctx {
   double *judge_scratch = nullptr;  // device address of the static judge scratch on this context's device
   bh::DevBuf energy_part;       // FP64 energy partials
   bh::DevBuf feps;              // FP64 [nsys] softening of the feature call
+  bh::DevBuf pp_stat;           // int4 per bundle: list statistics of the per-particle walk
   bh::DevBuf mlp_work;          // training batch workspace
   bh::DevBuf mlp_feat;          // FP32 [n][12] features of bh_group_theta
   // lists in blocks (sizes at which a group is walked by a workgroup)
@@ -248,7 +249,6 @@ struct bh_ctx {
   int32_t wide_cap = 0, wide_block = 0;  // blocks in the pool, entries per block
   bool counters_clean = false;           // the force counters are known to be 0 (reset by make_groups)
   hipEvent_t info_event = nullptr;       // completion of a read-back of the counters
-  bh::DevBuf pp_next;           // int32 per slot: thread pointers of the per-particle walk
   bh::DevBuf order_hist;        // int32 cost bins of the queue orders
   bh::DevBuf walk_order;        // int32 [n] order in which the list walk takes the groups (learned theta)
   bh::DevBuf walk_order_hist;   // int32 cost bins of the walk order (zero between calls)
@@ -440,9 +440,10 @@ struct NeighborArgs {
 void neighbors_device(const NeighborArgs &a, int n_crit, int grid, hipStream_t s);
 int neighbors_blocks_per_cu(int n_crit);
 // k_particle.hip: the per-particle walk and sum (no shared lists)
-void particle_forces_device(const NodeRec *nodes, int nslots, int nsys, const SysInfo *sys, const SysParam *par,
-                            const double *spos, const int32_t *perm, int64_t n, int32_t *nxt, float *acc,
-                            float *pot, DevInfo *info, hipStream_t s);
+void particle_forces_device(const NodeRec *nodes, int nsys, const SysInfo *sys, const SysParam *par,
+                            const double *spos, const int32_t *perm, int64_t n, float *acc, float *pot, int4 *stat,
+                            DevInfo *info, hipStream_t s);
+size_t particle_stat_bytes(int64_t n, int nsys);  // of stat
 // k_split.hip: ordering and reduction of split groups
 struct SplitBuffers {
   SplitCounters *ctr;
