@@ -167,7 +167,7 @@ struct bh_ctx {
   int num_cu = 0;
   std::string err;
   bh_options opt{0, 0, 0, 0, 0, 0};
-  int walk_bpc = 0, force_bpc = 0, force_bpc_q = 0, probe_bpc = 0, nb_bpc[3] = {0, 0, 0};  // resident blocks per CU of the persistent kernels
+  int walk_bpc = 0, force_bpc = 0, force_bpc_q = 0, probe_bpc = 0, nb_bpc[6] = {};  // resident blocks per CU of the persistent kernels
 
   // current tree
   int64_t n = 0;
@@ -430,6 +430,7 @@ struct NeighborArgs {
   const double *spos, *smass;
   const int32_t *perm;
   DevInfo *info;
+  int64_t n;
   int nsys;
   const double *h;        // [n] input order
   int32_t *count;         // nullable, [n] input order
@@ -438,7 +439,7 @@ struct NeighborArgs {
   int32_t *nbr;
 };
 void neighbors_device(const NeighborArgs &a, int n_crit, int grid, hipStream_t s);
-int neighbors_blocks_per_cu(int n_crit);
+int neighbors_blocks_per_cu(int n_crit, bool lists);
 // k_particle.hip: the per-particle walk and sum (no shared lists)
 void particle_forces_device(const NodeRec *nodes, int nsys, const SysInfo *sys, const SysParam *par,
                             const double *spos, const int32_t *perm, int64_t n, float *acc, float *pot, int4 *stat,

@@ -12,11 +12,9 @@
 // (sqrt(3)/2) l + s of its centre of mass (l the cube side, s the distance of
 // the centre of mass from the cube's centre).  A particle leaf within that
 // radius of the box is a candidate; candidates collect in LDS and are
-// tested against every member, one member per lane: an FP32 scan marks the
-// possible neighbours, and what is marked is decided in FP64 with the
+// tested against every member: an FP32 scan marks the possible neighbours, and what is marked is decided in FP64 with the
 // squared distance (dx^2 + dy^2) + dz^2 rounded as written, so the decision
-// r^2 < h_i^2 is the same as a plain CPU evaluation.  A candidate's index,
-// position and mass go to LDS from the node record its lane just read.  The pruning bounds
+// r^2 < h_i^2 is the same as a plain CPU evaluation.  The pruning bounds
 // carry margins far above FP64 rounding; they only skip work, the per-pair
 // test decides.
 //
@@ -32,6 +30,7 @@ namespace {
 
 constexpr int kNbStack = 512;                    // range stack entries
 constexpr int kNbReserve = 8 * 24;               // growth bound in one-range mode
+constexpr int kNbRun = 256;                      // particles of a cell that is not opened
 constexpr int kNbCand = 128;                     // candidate buffer: 64 to test and 64 that a batch may add
 constexpr double kHalfSqrt3 = 0.86602540378443865;
 
@@ -49,20 +48,18 @@ __device__ __forceinline__ double sph_shape(double q) {
 
 // sqrt(r2) / h from the hardware estimate of 1 / sqrt(r2) and hi = 1 / h, each
 // with one residual step, so that square root and quotient are rounded as the
-// library's to within a few hundredths of an ulp.  r2 = 0 gives 0; where the
-// estimate is not a number of ordinary size (r2 denormal or infinite), or hi
-// is not, the library's functions are used.
+// library's to within a few hundredths of an ulp.  For h in (2^-400, 2^400)
+// and r2 < h^2; below 2^-900, r2 counts as that (the kernel is flat to 1e-30
+// there).
 __device__ __forceinline__ double ratio(double r2, double h, double hi) {
+  r2 = fmax(r2, 0x1p-900);
   const double y0 = __builtin_amdgcn_rsq(r2);
   const double e = __builtin_fma(-(r2 * y0), y0, 1.0);
   const double y = __builtin_fma(y0 * e, __builtin_fma(0.375, e, 0.5), y0);
   double r = r2 * y;
   r = __builtin_fma(0.5 * y, __builtin_fma(-r, r, r2), r);
   double q = r * hi;
-  q = __builtin_fma(__builtin_fma(-q, h, r), hi, q);
-  const bool plain = r2 > 0x1p-900 && r2 < 0x1p900 && h > 0x1p-450 && h < 0x1p450;
-  if (!plain) q = sqrt(r2) / h;
-  return q;
+  return __builtin_fma(__builtin_fma(-q, h, r), hi, q);
 }
 
 __global__ void k_nb_reset(DevInfo *info) {
@@ -81,8 +78,20 @@ struct alignas(16) CandRec {
 };
 struct Cand {
   CandRec c[kNbCand];
-  float4 f[kNbCand];  // (.w: index bits)
+  float4 f[kNbCand];  // scan frame: -2 x, -2 y, -2 z, |x|^2
+  int32_t j[kNbCand]; // sorted index
+  unsigned long long words[kWave];  // marks of the scan
 };
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint16_t __attribute__((may_alias)) Piece;  // a quarter of a mark word
+
+// 2 v plus this lane's bit of mask, in one instruction.
+__device__ __forceinline__ uint32_t shift_in(uint32_t v, unsigned long long mask) {
+  uint32_t r;
+  asm("v_addc_co_u32_e64 %0, vcc, %1, %1, %2" : "=v"(r) : "v"(v), "s"(mask) : "vcc");
+  return r;
+}
 
 // Position of the r-th set bit (r counted from 0) of a word with more than r.
 __device__ __forceinline__ int nth_bit(unsigned long long w, int r) {
@@ -109,28 +118,27 @@ __device__ __forceinline__ int nth_bit(unsigned long long w, int r) {
 // first .. l (first <= l, the same on all lanes of a run).  The steps are
 // those of wave_inclusive_sum, each taken where the lanes it brings in belong
 // to the run.
-template <int CTRL, int ROWS>
+template <int CTRL>
 __device__ __forceinline__ double dpp_d(double v) {
   const int2 a = *reinterpret_cast<int2 *>(&v);
   int2 b;
-  b.x = __builtin_amdgcn_update_dpp(0, a.x, CTRL, ROWS, 0xf, false);
-  b.y = __builtin_amdgcn_update_dpp(0, a.y, CTRL, ROWS, 0xf, false);
+  b.x = __builtin_amdgcn_mov_dpp(a.x, CTRL, 0xf, 0xf, true);
+  b.y = __builtin_amdgcn_mov_dpp(a.y, CTRL, 0xf, 0xf, true);
   return *reinterpret_cast<double *>(&b);
 }
+template <int CTRL>
+__device__ __forceinline__ double run_step(double v, bool on) {
+  const double u = dpp_d<CTRL>(v);
+  return __dadd_rn(v, on ? u : 0.0);
+}
 __device__ __forceinline__ double run_sum(double v, int first, int lane) {
-  const int row = lane & 48;
-  double u = dpp_d<kDppRowShr1, 0xf>(v);
-  v = __dadd_rn(v, (lane - 1 >= first) ? u : 0.0);
-  u = dpp_d<kDppRowShr2, 0xf>(v);
-  v = __dadd_rn(v, (lane - 2 >= first) ? u : 0.0);
-  u = dpp_d<kDppRowShr4, 0xf>(v);
-  v = __dadd_rn(v, (lane - 4 >= first) ? u : 0.0);
-  u = dpp_d<kDppRowShr8, 0xf>(v);
-  v = __dadd_rn(v, (lane - 8 >= first) ? u : 0.0);
-  u = dpp_d<kDppRowBcast15, 0xa>(v);
-  v = __dadd_rn(v, (first < row) ? u : 0.0);
-  u = dpp_d<kDppRowBcast31, 0xc>(v);
-  return __dadd_rn(v, (first < 32) ? u : 0.0);
+  const int back = lane - first, in_row = min(back, lane & 15);  // lanes of the run below this one
+  v = run_step<kDppRowShr1>(v, in_row >= 1);
+  v = run_step<kDppRowShr2>(v, in_row >= 2);
+  v = run_step<kDppRowShr4>(v, in_row >= 4);
+  v = run_step<kDppRowShr8>(v, in_row >= 8);
+  v = run_step<kDppRowBcast15>(v, (lane & 16) && back > (lane & 15));
+  return run_step<kDppRowBcast31>(v, lane >= 32 && first < 32);
 }
 
 // Tests the first nc <= 64 staged candidates against every member block.
@@ -139,11 +147,11 @@ __device__ __forceinline__ double run_sum(double v, int first, int lane) {
 // some lane has one, and the lane with the most has several times the mean.
 // Testing and adding candidate by candidate (or each lane its own hits) made
 // the wave run the FP64 kernel function for nearly every candidate.  So:
-//   scan   each lane marks its possible neighbours in a 64-bit word by the
-//          FP32 distance in the group's frame, against a bound that the
-//          frame's rounding cannot exceed (a superset; NaN and overflow mark).
-//          With at most 32 members the two halves of the wave share the
-//          candidates.
+//   scan   marks the possible neighbours by |x|^2 - 2 x.y against a bound
+//          less |y|^2 (x candidate, y member, FP32 in the group's frame) that
+//          no rounding can exceed (a superset; NaN marks): 16 candidates times
+//          16 members, four terms, is one matrix instruction, so the vector
+//          units only compare and shift the marks in.
 //   rounds the marked (member, candidate) pairs, counted member by member, are
 //          taken 64 at a time, one per lane whoever's member it is: the FP64
 //          decision (r2 < h2, the sum rounded as written), the density term,
@@ -151,52 +159,43 @@ __device__ __forceinline__ double run_sum(double v, int first, int lane) {
 // 1,048,576 clustered particles, 133 neighbours and 1874 tests a particle:
 // 5.9 ms testing and adding candidate by candidate, 5.3 ms with the pairs
 // listed in LDS and each member adding its terms one after another, 2.99 ms
-// like this (1.54 ms of it the walk).
+// in rounds, 2.84 ms without visiting the leaves (then bound by vector issue at
+// 87 %; runs of 24 and 64 particles 3.43 and 2.94), 2.52 ms with the scan on
+// the matrix units (before, nine vector instructions a candidate and wave).
+// Now 70 % vector issue, most of it the rounds, about 180 instructions each.
 template <int kNbBlocks>
-__device__ __forceinline__ void flush(const NeighborArgs &a, const Cand &cd, int *mark, int nc, int gf, int gc, int nb, int lane,
-                                      const float (&fx)[kNbBlocks][3], const float (&ft)[kNbBlocks],
+__device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark, int nc, int gf, int gc, int nb, int lane,
+                                      const float (&fb)[kNbBlocks][4], const float (&ft)[kNbBlocks][4],
                                       const double (&hb)[kNbBlocks], int (&cb)[kNbBlocks], double (&rb)[kNbBlocks],
                                       const int64_t (&ob)[kNbBlocks], const int64_t (&lb)[kNbBlocks],
-                                      unsigned long long &tests) {
+                                      bool plain, unsigned long long &tests) {
 #pragma unroll
   for (int b = 0; b < kNbBlocks; ++b) {
     if (b < nb) {
       const int i = gf + b * kWave + lane;
       const int m = min(gc - b * kWave, kWave);  // members of this block
       const bool live = lane < m;
-      // scan
-      const bool halves = m <= 32;
-      float mx = fx[b][0], my = fx[b][1], mz = fx[b][2], mt = ft[b];
-      if (halves) {
-        mx = __shfl(mx, lane & 31, kWave);
-        my = __shfl(my, lane & 31, kWave);
-        mz = __shfl(mz, lane & 31, kWave);
-        mt = __shfl(mt, lane & 31, kWave);
-      }
-      uint32_t word[2] = {0u, 0u};
+      // scan: matrix row 4 q + i of tile t is candidate 16 q + 4 t + i, so
+      // that lane 16 q + c ends with candidates 16 q ... 16 q + 15 of member c
+      // of each member tile in order
+      const float *fr = reinterpret_cast<const float *>(cd.f) + 4 * (16 * ((lane >> 2) & 3) + (lane & 3)) + (lane >> 4);
+      const float row[4] = {fr[0], fr[16], fr[32], fr[48]};
+      Piece *words = reinterpret_cast<Piece *>(cd.words);
 #pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        if (w == 1 && (halves || nc <= 32)) break;
-        const int base = halves ? (lane & 32) : 32 * w;
-        const int top = halves ? min(nc, 32) : nc - 32 * w;
+      for (int w = 0; w < 4; ++w) {
+        if (16 * w >= m) break;
         uint32_t got = 0;
-#pragma unroll 1
-        for (int u0 = 0; u0 < min(top, 32); u0 += 8) {
-          uint32_t m8 = 0;
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const float4 q = cd.f[base + u0 + u];
-            const float dx = q.x - mx, dy = q.y - my, dz = q.z - mz;
-            const float r2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
-            m8 |= (r2 > mt) ? 0u : (1u << u);
-          }
-          got |= m8 << u0;
+        for (int t = 3; t >= 0; --t) {
+          const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(row[t], fb[b][w], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+          for (int k = 3; k >= 0; --k) got = shift_in(got, __ballot(!(d[k] > ft[b][w])));
         }
-        word[w] = got;
+        words[4 * (16 * w + (lane & 15)) + (lane >> 4)] = (Piece)got;
       }
-      if (halves) word[1] = (uint32_t)__shfl((int)word[0], (lane & 31) + 32, kWave);
+      wave_sync();
+      unsigned long long marks = cd.words[lane];
       // (places from nc on hold older candidates: their marks are cut off)
-      unsigned long long marks = ((unsigned long long)word[1] << 32) | word[0];
       if (nc < 64) marks &= (1ull << nc) - 1ull;
       if (!live) marks = 0ull;
       const int mine = __popcll(marks);
@@ -227,7 +226,7 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, const Cand &cd, int
         const unsigned long long um = (unsigned long long)shfl_i64((int64_t)marks, u);
         const int k = have ? nth_bit(um, lane - uoff) : 0;
         const CandRec q = cd.c[k];
-        const int j = __float_as_int(cd.f[k].w);
+        const int j = cd.j[k];
         const double dx = __dsub_rn(q.x, shfl_d(x0, u));
         const double dy = __dsub_rn(q.y, shfl_d(x1, u));
         const double dz = __dsub_rn(q.z, shfl_d(x2, u));
@@ -243,7 +242,10 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, const Cand &cd, int
           if (hit && n0 < len) a.nbr[row + n0] = a.perm[j];
         }
         if (a.rho) {
-          const double W = shfl_d(sigma, u) * sph_shape(ratio(r2, hu, shfl_d(hi, u)));
+          double x = 0.0;
+          if (plain) x = ratio(r2, hu, shfl_d(hi, u));
+          else x = sqrt(r2) / hu;
+          const double W = shfl_d(sigma, u) * sph_shape(x);
           const double sum = shfl_d(run_sum(hit ? __dmul_rn(q.m, W) : 0.0, max(uoff, 0), lane), max(e - 1, 0));
           if (e > s) r = __dadd_rn(r, sum);
         }
@@ -260,9 +262,14 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, const Cand &cd, int
 
 // kNbBlocks: member blocks of 64 held per lane (the largest group / 64),
 // chosen by the host from the grouping so that small groups keep registers
-// free.
-template <int kNbBlocks>
-__global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
+// free.  RUNS: a cell of at most kNbRun particles that is not pruned is not
+// opened; its particles, consecutive in key order and with those of its
+// neighbours in the batch one run, are read from the particle arrays, 64 at a
+// time, and tested against the radius as their leaves would be, so the
+// candidates are the same in another order.  Without (calls that ask for
+// lists, whose order is the walk's) every leaf's 64-byte record is visited.
+template <int kNbBlocks, bool RUNS>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_neighbors(NeighborArgs a) {
   __shared__ int2 stk[kNbStack];
   __shared__ Cand cd;
   __shared__ int mark[kWave];
@@ -284,7 +291,7 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
     int cb[kNbBlocks];
     int64_t ob[kNbBlocks], lb[kNbBlocks];
     double hmax = 0.0;
-    bool bad = false;
+    bool bad = false, odd = false;
 #pragma unroll
     for (int b = 0; b < kNbBlocks; ++b) {
       const int i = gf + b * kWave + lane;
@@ -292,6 +299,7 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
       const int o = live ? a.perm[i] : 0;
       hb[b] = live ? a.h[o] : 1.0;
       if (live && !(hb[b] > 0.0 && hb[b] < INFINITY)) bad = true;
+      if (!(hb[b] > 0x1p-400 && hb[b] < 0x1p400)) odd = true;
       if (live) hmax = fmax(hmax, hb[b]);
       cb[b] = 0;
       rb[b] = 0.0;
@@ -306,6 +314,7 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
       if (lane == 0) atomicOr(&a.info->err, kErrRadius);
       continue;
     }
+    const bool plain = __ballot(odd) == 0;  // radii of ordinary size
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) hmax = fmax(hmax, shfl_xor_d(hmax, d));
     // the group's box, widened by a margin above the rounding of the
@@ -322,37 +331,91 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
       cpad += pad;
     }
     const double rad = hmax * (1.0 + 1e-9) + cpad;
-    // The scan's frame: positions relative to the box centre, rounded to FP32.
-    // A candidate's and a member's coordinates there are at most `ext`, so the
-    // two roundings shift a distance by less than sqrt(3) 2^-23 ext; a lane
-    // marks what lies within its radius plus 2^-21 ext, squared and widened by
-    // 1e-5 for the FP32 sum.
+    // The scan's frame: positions relative to the box centre over a power of
+    // two, so that coordinates of candidates and members are at most 2, and
+    // FP32.  Of |x - y|^2 <= h^2 moved about as the scan has it, magnitudes
+    // are at most 36; the roundings of coordinates, squares, four products and
+    // their sum and the bound stay below 1.5e-5 (2^-15 is added).  A frame
+    // beyond the ordinary range marks everything.
     double cen[3], ext = 0.0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       cen[k] = 0.5 * (elo[k] + ehi[k]);
       ext = fmax(ext, 0.5 * (ehi[k] - elo[k]) + rad);
     }
-    float fx[kNbBlocks][3], ft[kNbBlocks];
+    const bool ordinary = ext > 0x1p-900 && ext < 0x1p900;
+    const double sc = ordinary ? ldexp(1.0, -ilogb(ext)) : 0.0;
+    float fb[kNbBlocks][4], ft[kNbBlocks][4];
 #pragma unroll
     for (int b = 0; b < kNbBlocks; ++b) {
       const int i = gf + b * kWave + lane;
       const bool live = b < nb && i < gf + gc;
+      double y[3], yy = 0.0;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) fx[b][k] = live ? (float)(a.spos[3 * (int64_t)i + k] - cen[k]) : 0.0f;
-      const double reach = hb[b] + 0x1p-21 * ext;
-      ft[b] = (float)(reach * reach * (1.0 + 1e-5));
+      for (int k = 0; k < 3; ++k) {
+        y[k] = live ? (a.spos[3 * (int64_t)i + k] - cen[k]) * sc : 0.0;
+        yy += y[k] * y[k];
+      }
+      const double hs = hb[b] * sc;
+      const float f0 = (float)y[0], f1 = (float)y[1], f2 = (float)y[2];
+      const float lim = ordinary ? (float)(hs * hs * (1.0 + 1e-9) + 0x1p-15 - yy) : INFINITY;
+      // member tile w's column: this lane holds component lane / 16 of member
+      // 16 w + lane % 16
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int u = 16 * w + (lane & 15);
+        const float c0 = __shfl(f0, u, kWave), c1 = __shfl(f1, u, kWave), c2 = __shfl(f2, u, kWave);
+        fb[b][w] = lane < 16 ? c0 : (lane < 32 ? c1 : (lane < 48 ? c2 : 1.0f));
+        ft[b][w] = __shfl(lim, u, kWave);
+      }
     }
 
     int sp = 1, ncand = 0;
     if (lane == 0) stk[0] = make_int2(gs, 1);
     wave_sync();
     int budget = 4 * nslots + 4;
-    while (sp > 0) {
+    // RUNS: a lane's particles [tf, te), the lanes that start a run, the lanes
+    // that carry one on, and the run being read
+    int tf = 0, te = 0, rp = 0, re = 0;
+    unsigned long long heads = 0, inner = 0;
+    while (sp > 0 || (RUNS && (heads || rp < re))) {
       if (--budget < 0) {
         if (lane == 0) atomicOr(&a.info->err, kErrStack);
         break;
       }
+      bool push = false, is_cand = false;
+      int2 rng = make_int2(0, 0);
+      int j = 0;
+      double px = 0.0, py = 0.0, pz = 0.0, pm = 0.0;
+      if (RUNS && (heads || rp < re)) {
+        if (rp >= re) {
+          const int l0 = __ffsll((long long)heads) - 1;
+          heads &= heads - 1;
+          const unsigned long long rest = ~(inner >> l0 >> 1);
+          rp = __builtin_amdgcn_readlane(tf, l0);
+          re = __builtin_amdgcn_readlane(te, min(l0 + __ffsll((long long)rest) - 1, kWave - 1));
+          if (rp < 0 || re > a.n) {
+            if (lane == 0) atomicOr(&a.info->err, kErrStack);
+            break;
+          }
+        }
+        j = rp + lane;
+        if (j < re) {
+          px = a.spos[3 * (int64_t)j];
+          py = a.spos[3 * (int64_t)j + 1];
+          pz = a.spos[3 * (int64_t)j + 2];
+          pm = a.smass[j];
+          const double x[3] = {px, py, pz};
+          double d2 = 0.0;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const double ek = fmax(0.0, fmax(elo[k] - x[k], x[k] - ehi[k]));
+            d2 += ek * ek;
+          }
+          is_cand = d2 <= rad * rad;
+        }
+        rp += kWave;
+      } else {
       // take up to 64 nodes from the top ranges (one range while the stack
       // is high: then the walk is depth first and the stack stays bounded)
       const bool starved = sp > kNbStack - kWave - kNbReserve;
@@ -383,10 +446,7 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
         if (lane == 0) atomicOr(&a.info->err, kErrStack);
         break;
       }
-      bool push = false, is_cand = false;
-      int2 rng = make_int2(0, 0);
-      int j = 0;
-      double px = 0.0, py = 0.0, pz = 0.0, pm = 0.0;
+      bool taken = false;
       if (lane < take) {
         const NodeRec r = a.nodes[node];
         double d2 = 0.0;
@@ -396,7 +456,8 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
           d2 += ek * ek;
         }
         if (r.child < 0) {
-          is_cand = r.count > 0 && d2 <= rad * rad;  // a particle within rad of the box
+          is_cand = !RUNS && r.count > 0 && d2 <= rad * rad;  // a particle within rad of the box
+          taken = RUNS && r.count > 0;
           j = r.first;
           px = r.com[0];
           py = r.com[1];
@@ -406,8 +467,22 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
           // every particle of the cell lies within R of its centre of mass
           const double R = (kHalfSqrt3 * r.l + r.s) * (1.0 + 1e-9) + rad;
           push = !(d2 > R * R);
+          taken = RUNS && push && r.count <= kNbRun;
+          push = push && !taken;
           rng = make_int2(r.child, r.nchild);
         }
+        if (RUNS && taken) {
+          tf = r.first;
+          te = r.first + r.count;
+        }
+      }
+      if (RUNS) {
+        const unsigned long long tm = __ballot(taken);
+        const int before = __shfl_up(te, 1, kWave);
+        const bool on = lane > 0 && taken && ((tm >> (lane - 1)) & 1ull) && before == tf;
+        inner = __ballot(on);
+        heads = tm & ~inner;
+      }
       }
       const unsigned long long pmask = __ballot(push), cm = __ballot(is_cand);
       const int npush = __popcll(pmask), nc = __popcll(cm);
@@ -420,24 +495,28 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
       if (is_cand) {
         const int q = ncand + rank_below(cm);
         cd.c[q] = CandRec{px, py, pz, pm};
-        cd.f[q] = make_float4((float)(px - cen[0]), (float)(py - cen[1]), (float)(pz - cen[2]), __int_as_float(j));
+        const double qx = (px - cen[0]) * sc, qy = (py - cen[1]) * sc, qz = (pz - cen[2]) * sc;
+        cd.f[q] = make_float4(-2.0f * (float)qx, -2.0f * (float)qy, -2.0f * (float)qz,
+                              (float)(qx * qx + qy * qy + qz * qz));
+        cd.j[q] = j;
       }
       sp += npush;
       ncand += nc;
       wave_sync();
       if (ncand >= kWave) {
-        flush<kNbBlocks>(a, cd, mark, kWave, gf, gc, nb, lane, fx, ft, hb, cb, rb, ob, lb, tests);
+        flush<kNbBlocks>(a, cd, mark, kWave, gf, gc, nb, lane, fb, ft, hb, cb, rb, ob, lb, plain, tests);
         // the rest (at most 64) move to the front
         ncand -= kWave;
         wave_sync();
         if (lane < ncand) {
           cd.c[lane] = cd.c[kWave + lane];
           cd.f[lane] = cd.f[kWave + lane];
+          cd.j[lane] = cd.j[kWave + lane];
         }
         wave_sync();
       }
     }
-    flush<kNbBlocks>(a, cd, mark, ncand, gf, gc, nb, lane, fx, ft, hb, cb, rb, ob, lb, tests);
+    flush<kNbBlocks>(a, cd, mark, ncand, gf, gc, nb, lane, fb, ft, hb, cb, rb, ob, lb, plain, tests);
     wave_sync();
     // outputs in input order
     bool short_list = false;
@@ -467,21 +546,32 @@ __global__ __launch_bounds__(kWave) void k_neighbors(NeighborArgs a) {
 
 }  // namespace
 
-int neighbors_blocks_per_cu(int n_crit) {
+template <bool RUNS>
+static int blocks_per_cu(int n_crit) {
   int b = 0;
   hipError_t e;
-  if (n_crit <= kWave) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<1>, kWave, 0);
-  else if (n_crit <= 2 * kWave) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<2>, kWave, 0);
-  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<BH_MAX_NCRIT / kWave>, kWave, 0);
+  if (n_crit <= kWave) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<1, RUNS>, kWave, 0);
+  else if (n_crit <= 2 * kWave) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<2, RUNS>, kWave, 0);
+  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<BH_MAX_NCRIT / kWave, RUNS>, kWave, 0);
   if (e != hipSuccess || b < 1) b = 8;
   return b;
 }
 
+int neighbors_blocks_per_cu(int n_crit, bool lists) {
+  return lists ? blocks_per_cu<false>(n_crit) : blocks_per_cu<true>(n_crit);
+}
+
+template <bool RUNS>
+static void launch(const NeighborArgs &a, int n_crit, int grid, hipStream_t s) {
+  if (n_crit <= kWave) k_neighbors<1, RUNS><<<(unsigned)grid, kWave, 0, s>>>(a);
+  else if (n_crit <= 2 * kWave) k_neighbors<2, RUNS><<<(unsigned)grid, kWave, 0, s>>>(a);
+  else k_neighbors<BH_MAX_NCRIT / kWave, RUNS><<<(unsigned)grid, kWave, 0, s>>>(a);
+}
+
 void neighbors_device(const NeighborArgs &a, int n_crit, int grid, hipStream_t s) {
   k_nb_reset<<<1, 64, 0, s>>>(a.info);
-  if (n_crit <= kWave) k_neighbors<1><<<(unsigned)grid, kWave, 0, s>>>(a);
-  else if (n_crit <= 2 * kWave) k_neighbors<2><<<(unsigned)grid, kWave, 0, s>>>(a);
-  else k_neighbors<BH_MAX_NCRIT / kWave><<<(unsigned)grid, kWave, 0, s>>>(a);
+  if (a.nbr) launch<false>(a, n_crit, grid, s);
+  else launch<true>(a, n_crit, grid, s);
 }
 
 }  // namespace bh
