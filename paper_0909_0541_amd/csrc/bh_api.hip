@@ -414,7 +414,7 @@ void bh_destroy(bh_ctx *c) {
                     &c->hist, &c->nodes, &c->msum, &c->meta, &c->kind, &c->tiles, &c->subs, &c->pieces, &c->tops, &c->highs, &c->highs2, &c->gflag, &c->gidx, &c->glen, &c->ginfo, &c->gbox, &c->glist,
                     &c->gmass, &c->bbox_part, &c->sys, &c->par, &c->info, &c->direct_part, &c->energy_part,
                     &c->glists, &c->far_pool, &c->near_pool, &c->far_next, &c->near_next,
-                    &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_stat, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
+                    &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_stat, &c->nb_out, &c->nb_count, &c->nb_rho, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
                     &c->split_ctr, &c->gsplit, &c->gnseg, &c->gsegfirst, &c->skeys[0], &c->skeys[1], &c->svals[0],
                     &c->svals[1], &c->shist, &c->sscan, &c->srows, &c->spbase, &c->sgroups, &c->psum,
                     &c->wide_pool, &c->wide_slot, &c->wide_gblocks, &c->wide_gstat, &c->wide_binfo, &c->wide_psum,
@@ -1524,6 +1524,19 @@ bh_status bh_neighbors(bh_ctx *c, const double *h, int32_t *count, double *rho, 
   A.info = P<DevInfo>(c->info);
   A.n = c->n;
   A.nsys = c->nsys;
+  A.n_crit = c->n_crit;
+  A.sys = P<SysInfo>(c->sys);
+  A.out_min = nbr ? INT32_MAX : neighbors_out_min(c->n);
+  if (A.out_min != INT32_MAX) {
+    const size_t parts = neighbors_parts(c->n_crit);
+    bh_status st = ensure(c, c->nb_out, sizeof(int32_t) * (size_t)c->n, "outlier groups");
+    if (!st) st = ensure(c, c->nb_count, sizeof(int32_t) * parts, "partial counts");
+    if (!st) st = ensure(c, c->nb_rho, sizeof(double) * parts, "partial densities");
+    if (st) return st;
+    A.out = P<int32_t>(c->nb_out);
+    A.part_count = P<int32_t>(c->nb_count);
+    A.part_rho = P<double>(c->nb_rho);
+  }
   A.h = h;
   A.count = count;
   A.rho = rho;
@@ -1532,7 +1545,7 @@ bh_status bh_neighbors(bh_ctx *c, const double *h, int32_t *count, double *rho, 
   bh_status st = timer_start(c, c->t_neighbor);
   if (st) return st;
   c->counters_clean = false;  // (the search shares the group queue)
-  neighbors_device(A, c->n_crit, grid, c->stream);
+  neighbors_device(A, grid, c->stream);
   st = timer_stop(c, c->t_neighbor);
   if (st) return st;
   return hip_check(c, hipGetLastError(), "kernel launch (neighbours)");

@@ -72,6 +72,7 @@ struct DevInfo {
   int32_t n_items;        // force work items (group, member block)
   unsigned long long nb_pairs;  // neighbour search: neighbours found (sum of the counts)
   unsigned long long nb_tests;  // neighbour search: candidate pairs whose distance was tested
+  int32_t nb_out, nb_queue;     // neighbour search: outlier groups, parts of them taken
   int32_t theta_fallback;  // groups of the last walk whose per-group theta was NaN (walked with the call's theta)
   int32_t pad0;
   unsigned long long node_visits;   // nodes the last walk tested (all its units)
@@ -239,6 +240,7 @@ struct bh_ctx {
   double *judge_scratch = nullptr;  // device address of the static judge scratch on this context's device
   bh::DevBuf energy_part;       // FP64 energy partials
   bh::DevBuf feps;              // FP64 [nsys] softening of the feature call
+  bh::DevBuf nb_out, nb_count, nb_rho;  // outliers of the neighbour search: groups, parts' counts and sums
   bh::DevBuf pp_stat;           // int4 per bundle: list statistics of the per-particle walk
   bh::DevBuf mlp_work;          // training batch workspace
   bh::DevBuf mlp_feat;          // FP32 [n][12] features of bh_group_theta
@@ -431,14 +433,21 @@ struct NeighborArgs {
   const int32_t *perm;
   DevInfo *info;
   int64_t n;
-  int nsys;
+  int nsys, n_crit;
+  const SysInfo *sys;
   const double *h;        // [n] input order
   int32_t *count;         // nullable, [n] input order
   double *rho;            // nullable
   const int64_t *offsets; // nullable, [n + 1]: lists are written when set
   int32_t *nbr;
+  int out_min;            // particles of cells inside the radius that make an outlier
+  int32_t *out;           // nullable (no outliers): outlier groups (info->nb_out of them)
+  int32_t *part_count;    // [neighbors_parts(n_crit)] counts and sums of outliers' parts
+  double *part_rho;
 };
-void neighbors_device(const NeighborArgs &a, int n_crit, int grid, hipStream_t s);
+void neighbors_device(const NeighborArgs &a, int grid, hipStream_t s);
+int neighbors_out_min(int64_t n);  // out_min (INT32_MAX: so few particles have no outliers)
+size_t neighbors_parts(int n_crit);
 int neighbors_blocks_per_cu(int n_crit, bool lists);
 // k_particle.hip: the per-particle walk and sum (no shared lists)
 void particle_forces_device(const NodeRec *nodes, int nsys, const SysInfo *sys, const SysParam *par,

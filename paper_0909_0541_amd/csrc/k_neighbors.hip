@@ -12,16 +12,28 @@
 // (sqrt(3)/2) l + s of its centre of mass (l the cube side, s the distance of
 // the centre of mass from the cube's centre).  A particle leaf within that
 // radius of the box is a candidate; candidates collect in LDS and are
-// tested against every member: an FP32 scan marks the possible neighbours, and what is marked is decided in FP64 with the
-// squared distance (dx^2 + dy^2) + dz^2 rounded as written, so the decision
-// r^2 < h_i^2 is the same as a plain CPU evaluation.  The pruning bounds
-// carry margins far above FP64 rounding; they only skip work, the per-pair
-// test decides.
+// tested against every member: an FP32 scan marks the possible neighbours, and
+// what is marked is decided in FP64 with the squared distance (dx^2 + dy^2) +
+// dz^2 rounded as written, so the decision r^2 < h_i^2 is the same as a plain
+// CPU evaluation.  The pruning bounds carry margins far above FP64 rounding;
+// they only skip work, the per-pair test decides.
+//
+// Outliers.  A group in a sparse place has a large search radius and may have
+// nearly every particle for a candidate, hundreds of times the median, while
+// the other waves are done.  A walk that finds cells inside its radius which
+// together hold out_min particles gives its group up at once to a second
+// launch, in which up to kNbSlices waves search a part of the particles each
+// (consecutive in key order; nodes without any are pruned); their counts and
+// sums are added in order.  30,000 Plummer particles: 6.4 ms with a wave for
+// each group, 0.99 ms like this; 300,000 in groups of 128 46 and 4.2 ms.  (Not
+// for calls that ask for lists, whose order is the walk's.)
 //
 // The SPH density sums m_j W(r_ij, h_i) over the neighbours, plus the
 // particle's own m_i W(0, h_i), with the cubic spline kernel of Monaghan and
 // Lattanzio with compact support h (the paper fixes no kernel).  Lists, when
 // asked for, hold the input indices of the neighbours in walk order.
+#include <algorithm>
+
 #include "bh_device.h"
 
 namespace bh {
@@ -31,6 +43,13 @@ namespace {
 constexpr int kNbStack = 512;                    // range stack entries
 constexpr int kNbReserve = 8 * 24;               // growth bound in one-range mode
 constexpr int kNbRun = 256;                      // particles of a cell that is not opened
+// Particles of cells inside the radius that make an outlier: a sixteenth of
+// all, at least kNbOutMin.  (8192 for 1M clustered particles makes outliers of
+// a few hundred groups that end in time: 3.14 ms against 2.61.)
+constexpr int kNbOutMin = 4096;
+constexpr int kNbSlices = 64;                    // parts of an outlier's search,
+constexpr int kNbSliceMin = 1024;                // of at least so many particles
+constexpr int kNbRows = 256 * kNbSlices;         // parts of all outliers
 constexpr int kNbCand = 128;                     // candidate buffer: 64 to test and 64 that a batch may add
 constexpr double kHalfSqrt3 = 0.86602540378443865;
 
@@ -67,6 +86,8 @@ __global__ void k_nb_reset(DevInfo *info) {
     info->queue = 0;
     info->nb_pairs = 0;
     info->nb_tests = 0;
+    info->nb_out = 0;
+    info->nb_queue = 0;
   }
 }
 
@@ -168,7 +189,7 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark
                                       const float (&fb)[kNbBlocks][4], const float (&ft)[kNbBlocks][4],
                                       const double (&hb)[kNbBlocks], int (&cb)[kNbBlocks], double (&rb)[kNbBlocks],
                                       const int64_t (&ob)[kNbBlocks], const int64_t (&lb)[kNbBlocks],
-                                      bool plain, unsigned long long &tests) {
+                                      bool plain, int &tests) {
 #pragma unroll
   for (int b = 0; b < kNbBlocks; ++b) {
     if (b < nb) {
@@ -206,7 +227,7 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark
         x0 = a.spos[3 * (int64_t)i];
         x1 = a.spos[3 * (int64_t)i + 1];
         x2 = a.spos[3 * (int64_t)i + 2];
-        tests += (unsigned long long)nc;
+        tests += nc;
       }
       const double h = hb[b], hi = 1.0 / h;
       const double sigma = a.rho ? sph_sigma(h) : 0.0;
@@ -268,7 +289,14 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark
 // time, and tested against the radius as their leaves would be, so the
 // candidates are the same in another order.  Without (calls that ask for
 // lists, whose order is the walk's) every leaf's 64-byte record is visited.
-template <int kNbBlocks, bool RUNS>
+//
+// SLICES: the launch for outliers, over the parts of info->nb_out groups.
+__device__ __forceinline__ int slices_per_outlier(int nout) {
+  return nout <= kNbRows / kNbSlices ? kNbSlices : max(1, kNbRows / nout);
+}
+__device__ __forceinline__ int slices_of(int per, int count) { return max(1, min(per, count / kNbSliceMin)); }
+
+template <int kNbBlocks, bool RUNS, bool SLICES>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_neighbors(NeighborArgs a) {
   __shared__ int2 stk[kNbStack];
   __shared__ Cand cd;
@@ -276,16 +304,31 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void
   const int lane = lane_id();
   const int G = a.info->n_groups;
   const int nslots = a.nsys + a.info->n_slots;
-  unsigned long long pairs = 0, tests = 0;
-  for (;;) {
-    const int g = take_one(&a.info->queue, lane);
-    if (g >= G) break;
+  unsigned long long pairs = 0, all_tests = 0;
+  const int per = SLICES ? slices_per_outlier(a.info->nb_out) : 1, units = SLICES ? a.info->nb_out * per : G;
+  // (the first unit is the workgroup's own number: 3000 waves asking for one
+  // on the same line take their time; 3000 particles 122 us against 86)
+  for (int unit = blockIdx.x; unit < units;
+       unit = (int)gridDim.x + take_one(SLICES ? &a.info->nb_queue : &a.info->queue, lane)) {
+    const int g = SLICES ? a.out[unit / per] : unit;
+    int tests = 0;
     const int gf = a.ginfo[3 * g], gc = a.ginfo[3 * g + 1], gs = a.ginfo[3 * g + 2];
     const int nb = min((gc + kWave - 1) / kWave, kNbBlocks);
     if ((gc + kWave - 1) / kWave > kNbBlocks || gs < 0 || gs >= a.nsys) {
       if (lane == 0) atomicOr(&a.info->err, kErrStack);
       continue;
     }
+    // this part's particles
+    int p0 = 0, p1 = 0, parts = 1;
+    if (SLICES) {
+      const int sf = a.sys[gs].first, sn = a.sys[gs].count, k = unit % per;
+      parts = slices_of(per, sn);
+      if (k >= parts) continue;
+      p0 = sf + (int)((int64_t)sn * k / parts);
+      p1 = sf + (int)((int64_t)sn * (k + 1) / parts);
+    }
+    int inside = 0;  // particles in cells found inside the radius
+    bool outlier = false;
     // members: radii, the group's largest, output offsets
     double hb[kNbBlocks], rb[kNbBlocks];
     int cb[kNbBlocks];
@@ -447,6 +490,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void
         break;
       }
       bool taken = false;
+      int mass = 0;
       if (lane < take) {
         const NodeRec r = a.nodes[node];
         double d2 = 0.0;
@@ -457,7 +501,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void
         }
         if (r.child < 0) {
           is_cand = !RUNS && r.count > 0 && d2 <= rad * rad;  // a particle within rad of the box
-          taken = RUNS && r.count > 0;
+          taken = RUNS && r.count > 0 && (!SLICES || (r.first >= p0 && r.first < p1));
           j = r.first;
           px = r.com[0];
           py = r.com[1];
@@ -467,13 +511,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void
           // every particle of the cell lies within R of its centre of mass
           const double R = (kHalfSqrt3 * r.l + r.s) * (1.0 + 1e-9) + rad;
           push = !(d2 > R * R);
+          if (SLICES) push = push && r.first < p1 && r.first + r.count > p0;
+          if (RUNS && !SLICES) {
+            const double in = rad - (R - rad);
+            mass = push && r.count > kNbRun && in > 0.0 && d2 <= in * in ? r.count : 0;
+          }
           taken = RUNS && push && r.count <= kNbRun;
           push = push && !taken;
           rng = make_int2(r.child, r.nchild);
         }
         if (RUNS && taken) {
-          tf = r.first;
-          te = r.first + r.count;
+          tf = SLICES ? max(r.first, p0) : r.first;
+          te = SLICES ? min(r.first + r.count, p1) : r.first + r.count;
         }
       }
       if (RUNS) {
@@ -482,6 +531,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void
         const bool on = lane > 0 && taken && ((tm >> (lane - 1)) & 1ull) && before == tf;
         inner = __ballot(on);
         heads = tm & ~inner;
+        if (!SLICES && __ballot(mass != 0)) {
+          inside += __builtin_amdgcn_readlane(wave_inclusive_sum(mass), kWave - 1);
+          outlier = inside >= a.out_min;
+          if (outlier) break;
+        }
       }
       }
       const unsigned long long pmask = __ballot(push), cm = __ballot(is_cand);
@@ -516,8 +570,27 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void
         wave_sync();
       }
     }
+    if (RUNS && outlier) {
+      if (lane == 0) a.out[atomicAdd(&a.info->nb_out, 1)] = g;
+      wave_sync();
+      continue;
+    }
     flush<kNbBlocks>(a, cd, mark, ncand, gf, gc, nb, lane, fb, ft, hb, cb, rb, ob, lb, plain, tests);
+    all_tests += (unsigned long long)tests;
     wave_sync();
+    if (SLICES && parts > 1) {
+#pragma unroll
+      for (int b = 0; b < kNbBlocks; ++b) {
+        const int u = b * kWave + lane;
+        if (b < nb && u < gc) {
+          const int64_t at = (int64_t)unit * a.n_crit + u;
+          a.part_count[at] = cb[b];
+          a.part_rho[at] = rb[b];
+          pairs += (unsigned long long)cb[b];
+        }
+      }
+      continue;
+    }
     // outputs in input order
     bool short_list = false;
 #pragma unroll
@@ -536,42 +609,79 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
     pairs += __shfl_xor(pairs, d, kWave);
-    tests += __shfl_xor(tests, d, kWave);
+    all_tests += __shfl_xor(all_tests, d, kWave);
   }
-  if (lane == 0 && (pairs || tests)) {
+  if (lane == 0 && (pairs || all_tests)) {
     atomicAdd(&a.info->nb_pairs, pairs);
-    atomicAdd(&a.info->nb_tests, tests);
+    atomicAdd(&a.info->nb_tests, all_tests);
+  }
+}
+
+// An outlier's members: its parts in order.
+__global__ __launch_bounds__(256) void k_nb_parts(NeighborArgs a) {
+  const int nout = a.info->nb_out, per = slices_per_outlier(nout);
+  for (int o = blockIdx.x; o < nout; o += gridDim.x) {
+    const int g = a.out[o];
+    const int gf = a.ginfo[3 * g], gc = a.ginfo[3 * g + 1], gs = a.ginfo[3 * g + 2];
+    const int parts = slices_of(per, a.sys[gs].count), u = threadIdx.x;
+    if (parts < 2 || u >= gc) continue;
+    int c = 0;
+    double r = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < parts; ++k) {
+      const int64_t at = ((int64_t)o * per + k) * a.n_crit + u;
+      c += a.part_count[at];
+      r = __dadd_rn(r, a.part_rho[at]);
+    }
+    const int i = gf + u, to = a.perm[i];
+    if (a.count) a.count[to] = c;
+    if (a.rho) a.rho[to] = __dadd_rn(__dmul_rn(a.smass[i], sph_sigma(a.h[to])), r);
   }
 }
 
 }  // namespace
 
-template <bool RUNS>
+template <bool RUNS, bool SLICES>
 static int blocks_per_cu(int n_crit) {
   int b = 0;
   hipError_t e;
-  if (n_crit <= kWave) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<1, RUNS>, kWave, 0);
-  else if (n_crit <= 2 * kWave) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<2, RUNS>, kWave, 0);
-  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<BH_MAX_NCRIT / kWave, RUNS>, kWave, 0);
+  if (n_crit <= kWave) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<1, RUNS, SLICES>, kWave, 0);
+  else if (n_crit <= 2 * kWave)
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<2, RUNS, SLICES>, kWave, 0);
+  else
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<BH_MAX_NCRIT / kWave, RUNS, SLICES>, kWave, 0);
   if (e != hipSuccess || b < 1) b = 8;
   return b;
 }
 
 int neighbors_blocks_per_cu(int n_crit, bool lists) {
-  return lists ? blocks_per_cu<false>(n_crit) : blocks_per_cu<true>(n_crit);
+  return lists ? blocks_per_cu<false, false>(n_crit)
+               : std::min(blocks_per_cu<true, false>(n_crit), blocks_per_cu<true, true>(n_crit));
 }
 
-template <bool RUNS>
-static void launch(const NeighborArgs &a, int n_crit, int grid, hipStream_t s) {
-  if (n_crit <= kWave) k_neighbors<1, RUNS><<<(unsigned)grid, kWave, 0, s>>>(a);
-  else if (n_crit <= 2 * kWave) k_neighbors<2, RUNS><<<(unsigned)grid, kWave, 0, s>>>(a);
-  else k_neighbors<BH_MAX_NCRIT / kWave, RUNS><<<(unsigned)grid, kWave, 0, s>>>(a);
+template <bool RUNS, bool SLICES>
+static void launch(const NeighborArgs &a, int grid, hipStream_t s) {
+  if (a.n_crit <= kWave) k_neighbors<1, RUNS, SLICES><<<(unsigned)grid, kWave, 0, s>>>(a);
+  else if (a.n_crit <= 2 * kWave) k_neighbors<2, RUNS, SLICES><<<(unsigned)grid, kWave, 0, s>>>(a);
+  else k_neighbors<BH_MAX_NCRIT / kWave, RUNS, SLICES><<<(unsigned)grid, kWave, 0, s>>>(a);
 }
 
-void neighbors_device(const NeighborArgs &a, int n_crit, int grid, hipStream_t s) {
+int neighbors_out_min(int64_t n) {
+  return n <= 2 * kNbOutMin ? INT32_MAX : (int)std::max<int64_t>(n / 16, kNbOutMin);
+}
+size_t neighbors_parts(int n_crit) { return (size_t)kNbRows * (size_t)n_crit; }
+
+void neighbors_device(const NeighborArgs &a, int grid, hipStream_t s) {
   k_nb_reset<<<1, 64, 0, s>>>(a.info);
-  if (a.nbr) launch<false>(a, n_crit, grid, s);
-  else launch<true>(a, n_crit, grid, s);
+  if (a.nbr) {
+    launch<false, false>(a, grid, s);
+    return;
+  }
+  launch<true, false>(a, grid, s);
+  if (a.out) {
+    launch<true, true>(a, grid, s);
+    k_nb_parts<<<256, 256, 0, s>>>(a);
+  }
 }
 
 }  // namespace bh
