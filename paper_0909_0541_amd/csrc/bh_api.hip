@@ -210,7 +210,7 @@ static bh_status ensure_particles(bh_ctx *c, int64_t n, int nsys) {
   const size_t hist = radix_hist_bytes((int64_t)N);
   const size_t scan_elems = std::max<size_t>(N, hist / sizeof(uint32_t)) + 1;
   // (cells above the subtrees are disjoint on each level)
-  const size_t lists = 4 * (kKeyLevels + 1) * (N / (size_t)subtree_particles(c->opt.quadrupole != 0) + 1);
+  const size_t lists = 4 * (kKeyLevels + 1) * (N / (size_t)subtree_particles((int64_t)N, c->opt.quadrupole != 0) + 1);
   struct Want {
     DevBuf *b;
     size_t bytes;
@@ -236,8 +236,7 @@ static bh_status ensure_particles(bh_ctx *c, int64_t n, int nsys) {
       {&c->subs, 2 * N + 4, "subtrees"},  {&c->pieces, lists, "pieces"},
       {&c->tops, lists, "top cells"},     {&c->highs, lists, "high cells"},
       {&c->highs2, lists, "high cells by level"},
-      {&c->gflag, 4 * N, "gflag"},        {&c->gidx, 4 * N, "gidx"},
-      {&c->glen, 4 * N, "glen"},          {&c->ginfo, 12 * N, "ginfo"},
+      {&c->glen, 4 * (N + 16), "glen"},   {&c->ginfo, 12 * N, "ginfo"},
       {&c->gbox, 48 * N, "gbox"},         {&c->glist, 4 * N, "glist"},
       {&c->gmass, 8 * N, "gmass"},
       {&c->bbox_part, (size_t)6 * 8 * (size_t)nsys * (size_t)bbox_blocks_per_system(nsys), "bbox"},
@@ -411,7 +410,7 @@ void bh_destroy(bh_ctx *c) {
   DevBuf *bufs[] = {&c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->sys_in, &c->spos, &c->smass,
                     &c->perm, &c->delta, &c->level, &c->cdigit, &c->pdigit, &c->owner, &c->cfirst, &c->ccount,
                     &c->cparent, &c->pparent, &c->mask, &c->nchild, &c->cfirst_child, &c->cslot, &c->scan_tmp,
-                    &c->hist, &c->nodes, &c->msum, &c->meta, &c->kind, &c->tiles, &c->subs, &c->pieces, &c->tops, &c->highs, &c->highs2, &c->gflag, &c->gidx, &c->glen, &c->ginfo, &c->gbox, &c->glist,
+                    &c->hist, &c->nodes, &c->msum, &c->meta, &c->kind, &c->tiles, &c->subs, &c->pieces, &c->tops, &c->highs, &c->highs2, &c->glen, &c->ginfo, &c->gbox, &c->glist,
                     &c->gmass, &c->bbox_part, &c->sys, &c->par, &c->info, &c->direct_part, &c->energy_part,
                     &c->glists, &c->far_pool, &c->near_pool, &c->far_next, &c->near_next,
                     &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_stat, &c->nb_out, &c->nb_count, &c->nb_rho, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
@@ -506,12 +505,14 @@ bh_status bh_make_groups(bh_ctx *c, int32_t n_crit, int64_t *n_groups_out) {
   B.sys = P<SysInfo>(c->sys);
   B.spos = P<double>(c->spos);
   B.info = P<DevInfo>(c->info);
-  B.gflag = P<int32_t>(c->gflag);
-  B.gidx = P<int32_t>(c->gidx);
   B.glen = P<int32_t>(c->glen);
+  B.tiles = P<int32_t>(c->tiles);
+  if (c->glen_zeroed != c->glen.bytes) {
+    fill_i32(B.glen, 0, (int64_t)(c->glen.bytes / sizeof(int32_t)), c->stream);
+    c->glen_zeroed = c->glen.bytes;
+  }
   B.ginfo = P<int32_t>(c->ginfo);
   B.gbox = P<double>(c->gbox);
-  B.scan_tmp = c->scan_tmp.p;
   B.num_cu = c->num_cu;
   make_groups_device(B, c->stream);
   c->xq_clean = c->counters_clean = true;

@@ -219,9 +219,8 @@ struct bh_ctx {
   bh::DevBuf subs;              // int32 roots of the subtrees
   bh::DevBuf pieces, tops;      // int32 pieces of the cells above them, and those cells
   bh::DevBuf highs, highs2;     // int32 cells above the pieces, and the same by level
-  bh::DevBuf gflag;             // int32 group start flags
-  bh::DevBuf gidx;              // int32 exclusive scan of the flags (group index)
-  bh::DevBuf glen;              // int32 group length at its start position
+  bh::DevBuf glen;              // int32 group length at its start position, 0 between calls
+  size_t glen_zeroed = 0;       // bytes of it cleared once (its size unless it has grown since)
   bh::DevBuf ginfo;             // int32 [G][3] first, count, system
   bh::DevBuf gbox;              // FP64 [G][6]
   bh::DevBuf glist;             // int32 [G] list length of the last force call
@@ -362,8 +361,8 @@ struct MomentArgs {
 // flags: a bucket is owned here; this particle's parent is above the subtrees.
 constexpr int kClassMask = 7, kClassSub = 1, kClassTop = 2, kClassPiece = 3, kClassHigh = 4;
 constexpr int kKindBucket = 8, kKindLone = 128;
-int subtree_particles(bool quad); // most particles of a subtree
-int piece_particles(bool quad);   // and of a piece of the cells above
+int subtree_particles(int64_t n, bool quad);  // most particles of a subtree
+int piece_particles(int64_t n, bool quad);    // and of a piece of the cells above
 void moments_device(const TreeBuffers &B, hipStream_t s);
 void empty_roots_device(const TreeBuffers &B, hipStream_t s);
 
@@ -378,9 +377,8 @@ struct GroupBuffers {
   const SysInfo *sys;
   const double *spos;
   DevInfo *info;
-  int32_t *gflag, *gidx, *glen, *ginfo;
+  int32_t *glen, *ginfo, *tiles;
   double *gbox;
-  void *scan_tmp;
   int num_cu;
 };
 void make_groups_device(GroupBuffers &B, hipStream_t s);

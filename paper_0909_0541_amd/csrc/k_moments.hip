@@ -275,25 +275,28 @@ __device__ __forceinline__ void store_moments(const MomentArgs &a, int slot, con
   a.qpack[2 * (int64_t)slot + 1] = make_float4((float)(3.0 * S[4]), (float)(3.0 * S[5]), (float)T, (float)(1.5 * T));
 }
 
-// Particles of a subtree, and threads of its workgroup.
-template <bool QUAD>
-constexpr int kSub = QUAD ? 256 : 512;
+// Particles of a subtree, and threads of its workgroup (with few particles
+// twice as many: up to 1024 of them then are one subtree; the build of 1024
+// and 8192 particles 62 and 81 us with 512, 47 and 78 with 1024; of 1M 484 and
+// 510).
+constexpr int kSub = 512, kSubFew = 1024, kSubQuad = 256;
+constexpr int64_t kFewParticles = 16384;
 
 // One workgroup per subtree; afterwards the particles whose parents are above
 // the subtrees.  A subtree of c particles at positions [f, f + c) owns its
 // cells at positions [f, f + c - 1) (the last position may own an ancestor),
 // and their children have the slots from cfc[f] on, at most 2 c - 2.  Bound by
 // latency for small trees (subtree, its arrays, levels, records) and by the
-// scattered 64-byte records for large ones: 13 us at 8192 particles, 380 us at
+// scattered 64-byte records for large ones: 11 us at 8192 particles, 380 us at
 // 4M (records and sums read and written once: 150 us), 132 us with second
 // moments at 300k.  One launch per tree level over sums in global memory, with
 // a pass for the slots and leaves and a counting sort of the cells by level
 // before: the whole build of 8192, 100k, 1M and 4M particles 158, 270, 544 and
-// 1443 us; with this 82, 201, 485 and 1343 us.  Subtrees of 256 with second
+// 1443 us; with this 78, 198, 481 and 1342 us.  Subtrees of 256 with second
 // moments: of 512 (one workgroup a compute unit) took 222 us.
-template <bool QUAD>
-__global__ __launch_bounds__(kSub<QUAD>) void k_subtrees(MomentArgs a) {
-  constexpr int SUB = kSub<QUAD>, LOCAL = 2 * SUB, ROOT = LOCAL - 1;
+template <int SUB, bool QUAD>
+__global__ __launch_bounds__(SUB) void k_subtrees(MomentArgs a) {
+  constexpr int LOCAL = 2 * SUB, ROOT = LOCAL - 1;
   __shared__ double sm[LOCAL][4];
   __shared__ double qm[QUAD ? LOCAL : 1][6];
   __shared__ int lcfc[SUB], lmask[SUB];
@@ -756,19 +759,21 @@ __global__ void k_empty_roots(const SysInfo *__restrict__ sys, int nsys, NodeRec
   for (int k = 0; k < 4; ++k) msum[4 * (int64_t)s + k] = 0.0;
 }
 
-template <bool QUAD>
+template <int SUB, bool QUAD>
 void launch(const MomentArgs &a, hipStream_t s) {
   // (a subtree holds 100 to 250 particles)
-  k_subtrees<QUAD><<<(unsigned)std::min<int64_t>((a.n + 127) / 128, 2048), kSub<QUAD>, 0, s>>>(a);
-  if (a.n > kSub<QUAD>)
+  k_subtrees<SUB, QUAD><<<(unsigned)std::min<int64_t>((a.n + 127) / 128, 2048), SUB, 0, s>>>(a);
+  if (a.n > SUB)
     k_top_cells<QUAD><<<(unsigned)std::min<int64_t>((a.n + 1023) / 1024, 1024), Piece<QUAD>::kThreads, 0, s>>>(a);
-  if (a.n > piece_particles(QUAD)) k_high_cells<QUAD><<<1, Piece<QUAD>::kThreads, 0, s>>>(a);
+  if (a.n > SUB * Piece<QUAD>::kFan) k_high_cells<QUAD><<<1, Piece<QUAD>::kThreads, 0, s>>>(a);
 }
 
 }  // namespace
 
-int subtree_particles(bool quad) { return quad ? kSub<true> : kSub<false>; }
-int piece_particles(bool quad) { return quad ? kSub<true> * Piece<true>::kFan : kSub<false> * Piece<false>::kFan; }
+int subtree_particles(int64_t n, bool quad) { return quad ? kSubQuad : (n <= kFewParticles ? kSubFew : kSub); }
+int piece_particles(int64_t n, bool quad) {
+  return subtree_particles(n, quad) * (quad ? Piece<true>::kFan : Piece<false>::kFan);
+}
 
 void empty_roots_device(const TreeBuffers &B, hipStream_t s) {
   k_empty_roots<<<(unsigned)((B.nsys + 255) / 256), 256, 0, s>>>(B.sys, B.nsys, B.nodes, B.msum, B.meta);
@@ -820,9 +825,11 @@ void moments_device(const TreeBuffers &B, hipStream_t s) {
   }
   if (B.any_empty) empty_roots_device(B, s);
   if (B.qmom)
-    launch<true>(a, s);
+    launch<kSubQuad, true>(a, s);
+  else if (B.n <= kFewParticles)
+    launch<kSubFew, false>(a, s);
   else
-    launch<false>(a, s);
+    launch<kSub, false>(a, s);
 }
 
 }  // namespace bh

@@ -1,4 +1,4 @@
-"""Slots and moments where the subtrees (512 particles), the pieces above them
+"""Slots and moments where the subtrees (512 or 1024 particles), the pieces above them
 (8192; 4096 with second moments), the list of cells above those (176 or 352 at
 once) and the scan's tiles end; with buckets above and below these sizes, deep
 chains, systems of one particle and empty systems.  Node records bit for bit
@@ -14,7 +14,7 @@ from paper_0909_0541_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 2, 3, 511, 512, 513, 1025, 4096, 4097, 8192, 8193, 16384, 16385, 40000, 100001]
+SIZES = [1, 2, 3, 511, 512, 513, 1023, 1024, 1025, 4096, 4097, 8192, 8193, 16384, 16385, 40000, 100001]
 
 
 def _inputs(kind, n):
