@@ -544,9 +544,13 @@ bh_status bh_make_groups(bh_ctx *c, int32_t n_crit, int64_t *n_groups_out) {
 constexpr int64_t kWideGroups = 2048;
 constexpr int kWideMinCrit = 16;
 // Fewest node tests that make a group an outlier (see outlier_cap): a walk
-// this long is a small part of a launch (32 iterations of 256 threads, 256
-// batches of a wave).
-constexpr int kOutMinWide = 8192;
+// this long is a small part of a launch (16 iterations of 256 threads, 256
+// batches of a wave).  In trees of up to kOutMinTree particles the walk of
+// everything is over before tasks could be (walk of 5000, 8192 Plummer
+// particles at theta 0.75: 47, 77 us with one workgroup a group, 64, 64 us with
+// tasks).
+constexpr int kOutMinWide = 4096;
+constexpr int kOutMinTree = 6500;
 constexpr int kOutMin = 16384;
 // Largest tree with outliers apart, and their block length: a task's list (at
 // most kTaskNodes cells of n / 2048 particles) then fits the block table.
@@ -661,8 +665,7 @@ static bh_status forces_wide(bh_ctx *c, const float *theta_group, float *acc, fl
     WideArgs A{};
     bh_status st = wide_args(c, true, theta_group, acc, pot, A);
     if (st) return st;
-    // (a walk tests at most 2 n nodes: small trees have no outliers)
-    const bool outliers = 2 * n > kOutMinWide && !c->out_off;
+    const bool outliers = n > kOutMinTree && !c->out_off;
     A.out_min = outliers ? kOutMinWide : 0;
     if (!c->counters_clean) reset_list_counters(P<DevInfo>(c->info), c->stream);
     c->counters_clean = false;
@@ -822,7 +825,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   const int visit_cap = std::max(c->opt.split_visits, 0);
   if (!c->capturing) c->out_off = false;
   const int out_min = few ? kOutMinWide : kOutMin;
-  bool outliers = c->opt.split_visits == 0 && c->n <= kOutMaxN && 2 * c->n > out_min && !c->out_off;
+  bool outliers = c->opt.split_visits == 0 && c->n <= kOutMaxN && (few ? c->n > kOutMinTree : 2 * c->n > out_min) && !c->out_off;
   if (outliers) wide_capacity(c, kOutBlock, 2 * c->n / kOutBlock + 4096);
   if (c->seg_cap == 0) {
     c->task_cap = 4096;
