@@ -557,15 +557,20 @@ constexpr int kOutMin = 16384;
 constexpr int64_t kOutMaxN = 1 << 26;
 constexpr int kOutBlock = 256;
 
-// Whether the force call takes the workgroup walk: the tuning options (split
-// cap, list tile, waves), each of which asks for the single-wave walk in a
-// given form, are at their defaults.  A context that integrates (a kick, a
-// drift or leapfrog steps ran on it) stays with the single waves' lists at
-// every size: the FP32 sums then keep one list order and one length whatever
-// the particle count, and with them the rounding errors that add up along a
-// trajectory and in its energy.  (Outliers hold too few members to matter
-// there: the energy of 30,011 Plummer particles moves by 3e-12.)  At these
-// sizes its lists are summed by tiles.
+// Whether there are too few groups to fill the chip with a wave each, and the
+// tuning options (split cap, list tile, waves), each of which asks for the
+// single-wave kernels in a given form, are at their defaults.  The lists are
+// then summed by tiles (forces_tiles).  Sums with quadrupoles take the
+// workgroup walk and list blocks throughout (forces_wide), unless the context
+// integrates (a kick, a drift or leapfrog steps ran on it).  Monopole sums keep
+// the single waves' list order and FP32 chains at every size, because an
+// integration may start from any of them: in other orders their roundings
+// differ by up to 4e-7 of the force, and 1.5e-8 of the velocities after four
+// leapfrog steps in a clustered box, although no sum is less exact.  That costs
+// (walk and sum of 1000 and 8192 Plummer particles and of 100,003 in a sphere,
+// us, by waves and tiles against workgroups: 140 against 42, 257 against 90,
+// 310 against 205).  Outliers hold too few members, and in places too sparse,
+// to matter: the energy of 30,011 Plummer particles moves by 3e-12.
 static bool few_groups(const bh_ctx *c) {
   return c->opt.split_visits == 0 && c->opt.list_tile == 0 && c->opt.waves_per_cu == 0 &&
          c->n_crit >= kWideMinCrit && c->n <= kWideGroups * c->n_crit && wide_fits(c->n);
@@ -788,7 +793,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     return BH_OK;
   }
   const bool few = few_groups(c);
-  if (few && !c->integrates) return forces_wide(c, theta_group, acc, pot);
+  if (few && quad && !c->integrates) return forces_wide(c, theta_group, acc, pot);
   // list pools: start from an estimate (32 far and 4 near entries per
   // particle), grow to what a walk reports it needed; the capacities count
   // chunks of the current tile (recounted when the tile changes)
