@@ -416,8 +416,7 @@ void bh_destroy(bh_ctx *c) {
                     &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_stat, &c->nb_out, &c->nb_count, &c->nb_rho, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
                     &c->split_ctr, &c->gsplit, &c->gnseg, &c->gsegfirst, &c->skeys[0], &c->skeys[1], &c->svals[0],
                     &c->svals[1], &c->shist, &c->sscan, &c->srows, &c->spbase, &c->sgroups, &c->psum,
-                    &c->wide_pool, &c->wide_slot, &c->wide_gblocks, &c->wide_gstat, &c->wide_binfo, &c->wide_psum,
-                    &c->tile_info, &c->tile_groups, &c->tile_psum, &c->out_groups, &c->out_info, &c->out_nodes, &c->out_tasks, &c->out_rows, &c->out_near, &c->out_mass,
+                    &c->tile_buf, &c->wide_buf,
                     &c->qmom, &c->qpack, &c->far_slot};
   for (DevBuf *b : bufs) free_buf(*b);
   if (c->graph) (void)hipGraphExecDestroy(c->graph);
@@ -567,14 +566,18 @@ constexpr int kOutBlock = 256;
 // integration may start from any of them: in other orders their roundings
 // differ by up to 4e-7 of the force, and 1.5e-8 of the velocities after four
 // leapfrog steps in a clustered box, although no sum is less exact.  That costs
-// (walk and sum of 1000 and 8192 Plummer particles and of 100,003 in a sphere,
-// us, by waves and tiles against workgroups: 140 against 42, 257 against 90,
-// 310 against 205).  Outliers hold too few members, and in places too sparse,
-// to matter: the energy of 30,011 Plummer particles moves by 3e-12.
+// (whole steps of 1000 and 8192 Plummer particles and of 100,003 in a sphere,
+// us, by waves and tiles against workgroups: 207 against 108, 359 against 184,
+// 563 against 417).  Outliers hold too few members, and in places too sparse,
+// to matter: velocities and energies of boxes and spheres of 1100 to 240,000
+// particles move by at most 1.2e-11 (with outliers from twice an ordinary walk
+// on, rather than four times, by 7e-9).
 static bool few_groups(const bh_ctx *c) {
   return c->opt.split_visits == 0 && c->opt.list_tile == 0 && c->opt.waves_per_cu == 0 &&
          c->n_crit >= kWideMinCrit && c->n <= kWideGroups * c->n_crit && wide_fits(c->n);
 }
+
+static size_t padded(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 
 // Arguments and buffers of the workgroup kernels (the pool holds c->wide_cap
 // blocks).  groups: the ordinary groups too, not only outliers.
@@ -582,26 +585,31 @@ static bh_status wide_args(bh_ctx *c, bool groups, const float *theta_group, flo
   const bool quad = c->opt.quadrupole != 0;
   const int block = c->wide_block;
   const size_t cap = (size_t)c->wide_cap;
+  // (one allocation: a dozen of them are a good part of a first call)
   struct {
-    DevBuf *b;
+    void **p;
     size_t bytes;
-  } want[] = {{&c->wide_pool, cap * block * sizeof(float4)},
-              {&c->wide_slot, quad ? cap * block * sizeof(int32_t) : 0},
-              {&c->wide_gblocks, groups ? sizeof(int2) * (size_t)c->n : 0},
-              {&c->wide_gstat, groups ? sizeof(int2) * (size_t)c->n : 0},
-              {&c->wide_binfo, cap * sizeof(int4)},
-              {&c->wide_psum, cap * (size_t)c->n_crit * 4 * sizeof(double)},
-              {&c->out_groups, sizeof(int32_t) * kOutMax},
-              {&c->out_info, sizeof(OutInfo) * kOutMax},
-              {&c->out_nodes, sizeof(int32_t) * (size_t)kOutMax * kOutNodes},
-              {&c->out_tasks, sizeof(int4) * (size_t)kTaskCap},
-              {&c->out_rows, sizeof(int4) * (size_t)kTaskCap},
-              {&c->out_near, sizeof(int32_t) * (size_t)kTaskCap},
-              {&c->out_mass, sizeof(double) * (size_t)kTaskCap}};
+  } want[] = {{(void **)&A.pool, cap * block * sizeof(float4)},
+              {(void **)&A.slot, quad ? cap * block * sizeof(int32_t) : 0},
+              {(void **)&A.gblocks, groups ? sizeof(int2) * (size_t)c->n : 0},
+              {(void **)&A.gstat, groups ? sizeof(int2) * (size_t)c->n : 0},
+              {(void **)&A.binfo, cap * sizeof(int4)},
+              {(void **)&A.psum, cap * (size_t)c->n_crit * 4 * sizeof(double)},
+              {(void **)&A.out, sizeof(int32_t) * kOutMax},
+              {(void **)&A.outinfo, sizeof(OutInfo) * kOutMax},
+              {(void **)&A.tnodes, sizeof(int32_t) * (size_t)kOutMax * kOutNodes},
+              {(void **)&A.tasks, sizeof(int4) * (size_t)kTaskCap},
+              {(void **)&A.trows, sizeof(int4) * (size_t)kTaskCap},
+              {(void **)&A.tnear, sizeof(int32_t) * (size_t)kTaskCap},
+              {(void **)&A.tmass, sizeof(double) * (size_t)kTaskCap}};
+  size_t total = 0;
+  for (auto &w : want) total += padded(w.bytes);
+  bh_status st = ensure(c, c->wide_buf, total, "list blocks");
+  if (st) return st;
+  char *at = P<char>(c->wide_buf);
   for (auto &w : want) {
-    if (w.bytes == 0) continue;
-    bh_status st = ensure(c, *w.b, w.bytes, "list blocks");
-    if (st) return st;
+    *w.p = w.bytes ? at : nullptr;
+    at += padded(w.bytes);
   }
   A.nodes = P<NodeRec>(c->nodes);
   A.sys = P<SysInfo>(c->sys);
@@ -615,27 +623,14 @@ static bh_status wide_args(bh_ctx *c, bool groups, const float *theta_group, flo
   A.block = block;
   for (A.block_log = 0; (1 << A.block_log) < block;) ++A.block_log;
   A.block_cap = c->wide_cap;
-  A.pool = P<float4>(c->wide_pool);
-  A.slot = quad ? P<int32_t>(c->wide_slot) : nullptr;
   A.qpack = quad ? P<float4>(c->qpack) : nullptr;
   A.glist = P<int32_t>(c->glist);
   A.gmass = P<double>(c->gmass);
-  A.gblocks = P<int2>(c->wide_gblocks);
-  A.gstat = P<int2>(c->wide_gstat);
-  A.binfo = P<int4>(c->wide_binfo);
-  A.psum = P<double>(c->wide_psum);
   A.spos = P<double>(c->spos);
   A.smass = P<double>(c->smass);
   A.perm = P<int32_t>(c->perm);
   A.acc = acc;
   A.pot = pot;
-  A.out = P<int32_t>(c->out_groups);
-  A.outinfo = P<OutInfo>(c->out_info);
-  A.tnodes = P<int32_t>(c->out_nodes);
-  A.tasks = P<int4>(c->out_tasks);
-  A.trows = P<int4>(c->out_rows);
-  A.tnear = P<int32_t>(c->out_near);
-  A.tmass = P<double>(c->out_mass);
   return BH_OK;
 }
 
@@ -717,9 +712,8 @@ static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &
                               float *pot) {
   // (a tile takes a chunk of a pool: no more rows than chunks)
   const size_t rows = (size_t)W.far_cap + (size_t)W.near_cap;
-  bh_status st = ensure(c, c->tile_info, sizeof(int4) * rows, "list tiles");
-  if (!st) st = ensure(c, c->tile_groups, sizeof(int2) * (size_t)c->n, "list tiles");
-  if (!st) st = ensure(c, c->tile_psum, sizeof(double) * 4 * rows * (size_t)c->n_crit, "partial sums");
+  const size_t b0 = padded(sizeof(double) * 4 * rows * (size_t)c->n_crit), b1 = padded(sizeof(int4) * rows);
+  bh_status st = ensure(c, c->tile_buf, b0 + b1 + sizeof(int2) * (size_t)c->n, "list tiles");
   if (st) return st;
   TileArgs T{};
   T.ginfo = W.ginfo;
@@ -738,9 +732,9 @@ static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &
   T.spos = P<double>(c->spos);
   T.par = W.par;
   T.info = W.info;
-  T.gblocks = P<int2>(c->tile_groups);
-  T.tinfo = P<int4>(c->tile_info);
-  T.psum = P<double>(c->tile_psum);
+  T.psum = P<double>(c->tile_buf);
+  T.tinfo = (int4 *)(P<char>(c->tile_buf) + b0);
+  T.gblocks = (int2 *)(P<char>(c->tile_buf) + b0 + b1);
   WideArgs R{};
   R.ginfo = W.ginfo;
   R.info = W.info;
@@ -831,7 +825,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   if (!c->capturing) c->out_off = false;
   const int out_min = few ? kOutMinWide : kOutMin;
   bool outliers = c->opt.split_visits == 0 && c->n <= kOutMaxN && (few ? c->n > kOutMinTree : 2 * c->n > out_min) && !c->out_off;
-  if (outliers) wide_capacity(c, kOutBlock, 2 * c->n / kOutBlock + 4096);
+  if (outliers) wide_capacity(c, kOutBlock, 2 * c->n / kOutBlock + (few ? 512 : 4096));
   if (c->seg_cap == 0) {
     c->task_cap = 4096;
     c->range_cap = 1 << 16;

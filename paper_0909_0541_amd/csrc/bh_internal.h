@@ -181,7 +181,7 @@ struct bh_ctx {
   bool have_quad = false;  // the current tree carries second moments
   bool have_neighbors = false;  // a neighbour search ran since the last build
   bool out_off = false;    // the last force call found more outliers than fit: every group walked whole
-  bool integrates = false; // a kick or drift ran on this context: force calls keep the single-wave list order
+  bool integrates = false; // a kick or drift ran on this context: its quadrupole sums keep the single-wave list order too
   bool capturing = false;         // recording a step into a HIP graph: no uploads, syncs or timers
   hipStream_t capture_stream = nullptr;
   hipGraphExec_t graph = nullptr; // the captured step
@@ -244,9 +244,8 @@ struct bh_ctx {
   bh::DevBuf mlp_work;          // training batch workspace
   bh::DevBuf mlp_feat;          // FP32 [n][12] features of bh_group_theta
   // lists in blocks (sizes at which a group is walked by a workgroup)
-  bh::DevBuf wide_pool, wide_slot, wide_gblocks, wide_gstat, wide_binfo, wide_psum;
-  bh::DevBuf out_groups, out_info, out_nodes, out_tasks, out_rows, out_near, out_mass;  // outliers and their walk tasks
-  bh::DevBuf tile_info, tile_groups, tile_psum;  // sums by list tiles: rows, rows of a group, partial sums
+  bh::DevBuf wide_buf;  // list blocks, rows of partial sums, outliers and their walk tasks
+  bh::DevBuf tile_buf;  // sums by list tiles: partial sums, rows, rows of a group
   int32_t wide_cap = 0, wide_block = 0;  // blocks in the pool, entries per block
   bool counters_clean = false;           // the force counters are known to be 0 (reset by make_groups)
   hipEvent_t info_event = nullptr;       // completion of a read-back of the counters

@@ -340,9 +340,8 @@ __global__ __launch_bounds__(1024) void k_tile_rows(TileArgs a) {
 // The sums of k_force_lists taken apart by tiles: a workgroup per tile, a wave
 // per block of 64 members, each member's FP32 chain over the tile's entries
 // (or its lane partition's) the same as there, so the values differ only in
-// the order in which tiles and partitions are added in FP64.  For contexts
-// that integrate with too few groups to fill the chip with a wave each: the
-// longest list no longer decides (30,011 Plummer particles: 602 us with a wave
+// the order in which tiles and partitions are added in FP64.  For too few
+// groups to fill the chip with a wave each: the longest list no longer decides (30,011 Plummer particles: 602 us with a wave
 // per group, NUMS with a workgroup per tile).  Entries are staged in LDS, a
 // whole tile at once: a lone wave waits for every scalar load.
 template <bool QUAD>

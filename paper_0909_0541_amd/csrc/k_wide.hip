@@ -1,6 +1,7 @@
-// Force call for sizes that leave the chip idle with one wave per group: the
-// group walk by a whole workgroup, and the list summed in equal blocks by
-// many workgroups.
+// Force call with quadrupoles for sizes that leave the chip idle with one wave
+// per group: the group walk by a whole workgroup, and the list summed in equal
+// blocks by many workgroups; and outliers at every size, with or without
+// quadrupoles.
 //
 // With a few hundred or thousand groups, the single-wave walk and sum
 // (k_walk_lists, k_force_lists) run as long as their longest chain: a wave
@@ -23,8 +24,8 @@
 // Outliers.  A few groups with sparse boxes (1 to 6 of a Plummer sphere's
 // thousands) have lists of nearly every particle, hundreds of times the
 // median, and one workgroup (or, on larger trees, one wave of k_walk_lists)
-// would hold the launch open for them.  A walk that has tested
-// outlier_cap nodes gives its group up to this path: the group is walked again from the
+// would hold the launch open for them.  A walk that has tested outlier_cap
+// nodes gives its group up to this path: the group is walked again from the
 // root over its large cells only, the subtrees below them that have to be
 // opened become tasks of kTaskNodes nodes each, and a second launch walks the
 // tasks, one workgroup each.  A task's rows follow the group's own in task
@@ -661,10 +662,14 @@ static int wide_threads(int64_t n, int n_crit, int num_cu) {
 
 template <int NT, int MODE>
 static void launch_walk_wide(const WideArgs &a, int grid, hipStream_t s) {
-  if (a.slot)
+  if constexpr (MODE == kUnitGroups) {  // (only with quadrupoles)
     k_walk_wide<NT, true, MODE><<<(unsigned)grid, NT, 0, s>>>(a);
-  else
-    k_walk_wide<NT, false, MODE><<<(unsigned)grid, NT, 0, s>>>(a);
+  } else {
+    if (a.slot)
+      k_walk_wide<NT, true, MODE><<<(unsigned)grid, NT, 0, s>>>(a);
+    else
+      k_walk_wide<NT, false, MODE><<<(unsigned)grid, NT, 0, s>>>(a);
+  }
 }
 
 void walk_wide_device(const WideArgs &a, int64_t n, int num_cu, hipStream_t s) {

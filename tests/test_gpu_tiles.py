@@ -1,5 +1,5 @@
-"""Sums by list tiles, which a context that integrates takes with few groups,
-against the sums of one wave per group (list tile asked for by option) over the
+"""Sums by list tiles, taken with few groups (with quadrupoles by a context that
+integrates), against the sums of one wave per group (list tile asked for by option) over the
 same lists: the FP32 chains are the same and only FP64 partial sums are added in
 another order, so a result differs by at most one rounding to FP32 (2^-23 of
 it, and of the self potential that is taken out).  Statistics are equal."""
