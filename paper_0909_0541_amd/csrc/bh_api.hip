@@ -567,8 +567,8 @@ constexpr int kOutBlock = 256;
 // differ by up to 4e-7 of the force, and 1.5e-8 of the velocities after four
 // leapfrog steps in a clustered box, although no sum is less exact.  That costs
 // (whole steps of 1000 and 8192 Plummer particles and of 100,003 in a sphere,
-// us, by waves and tiles against workgroups: 207 against 108, 359 against 184,
-// 563 against 417).  Outliers hold too few members, and in places too sparse,
+// us, by waves and tiles against workgroups: 207 against 108, 357 against 184,
+// 524 against 417).  Outliers hold too few members, and in places too sparse,
 // to matter: velocities and energies of boxes and spheres of 1100 to 240,000
 // particles move by at most 1.2e-11 (with outliers from twice an ordinary walk
 // on, rather than four times, by 7e-9).

@@ -341,12 +341,14 @@ __global__ __launch_bounds__(1024) void k_tile_rows(TileArgs a) {
 // per block of 64 members, each member's FP32 chain over the tile's entries
 // (or its lane partition's) the same as there, so the values differ only in
 // the order in which tiles and partitions are added in FP64.  For too few
-// groups to fill the chip with a wave each: the longest list no longer decides (30,011 Plummer particles: 602 us with a wave
-// per group, NUMS with a workgroup per tile).  Entries are staged in LDS, a
-// whole tile at once: a lone wave waits for every scalar load.
+// groups to fill the chip with a wave each: the longest list no longer decides
+// (30,011 Plummer particles: 602 us with a wave per group, 86 with a workgroup
+// per tile; 100,003 in a sphere 151, with 16 rather than 8 KiB of LDS and 4
+// rather than 8 entries at a time 188).  Entries are staged in LDS: a lone wave
+// waits for every scalar load.
 template <bool QUAD>
 __global__ __launch_bounds__(256) void k_force_tiles(TileArgs a) {
-  constexpr int kStage = QUAD ? 256 : kDefaultTile;
+  constexpr int kStage = QUAD ? 256 : 512;
   __shared__ float4 e[kStage + (QUAD ? kStage : 0)];  // entries; the second half (QUAD: array) residues
   __shared__ float4 qs[QUAD ? 2 * kStage : 1];
   __shared__ int32_t sl[QUAD ? kStage : 1];
@@ -411,9 +413,9 @@ __global__ __launch_bounds__(256) void k_force_tiles(TileArgs a) {
           else
             stage_sum<false, QUAD, kUQuad>(M, e, e, sl, qs, 0, s, part, R, eps2);
         } else if (near) {
-          stage_sum<true, QUAD>(M, e, e + kHalf, sl, qs, 0, s, part, R, eps2);
+          stage_sum<true, QUAD, QUAD ? 2 : kU>(M, e, e + kHalf, sl, qs, 0, s, part, R, eps2);
         } else {
-          stage_sum<false, QUAD>(M, e, e, sl, qs, 0, s, part, R, eps2);
+          stage_sum<false, QUAD, QUAD ? 2 : kU>(M, e, e, sl, qs, 0, s, part, R, eps2);
         }
       }
     }
@@ -438,7 +440,7 @@ void force_tiles_device(const TileArgs &a, int num_cu, hipStream_t s) {
   if (a.far_slot && a.qpack)
     k_force_tiles<true><<<(unsigned)(num_cu * 8), nt, 0, s>>>(a);
   else
-    k_force_tiles<false><<<(unsigned)(num_cu * 8), nt, 0, s>>>(a);
+    k_force_tiles<false><<<(unsigned)(num_cu * 16), nt, 0, s>>>(a);
 }
 
 int force_lists_blocks_per_cu(bool quad) {
