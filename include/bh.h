@@ -114,10 +114,12 @@ typedef struct {
                             whose walk is several times an ordinary one's at their theta
                             (outliers, a few per system) are walked and summed by many
                             workgroups, and with the other tuning options at their defaults
-                            trees of up to 2048 n_crit particles (n_crit >= 16) are walked by a
-                            workgroup per group.  Results do not depend on when or where a
-                            walk ran, only on the input and this option; up to FP32 rounding
-                            (the order in which a list is summed) not on the option either. */
+                            trees of up to 2048 n_crit particles (n_crit >= 16) have their lists
+                            summed by a workgroup per tile or, with quadrupoles, are walked and
+                            summed by a workgroup per group and list block.  Results do not
+                            depend on when or where a walk ran, only on the input and this
+                            option; up to FP32 rounding (the order in which a list is summed)
+                            not on the option either. */
   int32_t quadrupole;    /* 1: builds also compute every cell's second mass moments S about its
                             centre of mass (bottom-up, parallel axes, FP64), and bh_compute_forces
                             and bh_compute_forces_batch add to each cell entry of a list the
@@ -304,10 +306,11 @@ bh_status bh_direct_sampled_noalloc(bh_ctx *ctx, int64_t n, const double *pos, c
 /* ---- time integration (kick-drift-kick leapfrog, FP64 state) ----------- */
 
 /* vel += dt * acc (acc FP32 [n][3] from a force call, vel FP64 [n][3]).
- * From the first bh_kick, bh_drift or bh_leapfrog step on a context, its force
- * calls walk each group by one wave at every size (as with split_visits -1):
- * a trajectory then has one order of its FP32 sums from end to end, whether
- * its steps are issued by hand or by bh_leapfrog. */
+ * Monopole force calls add a list's FP32 terms in one order at every size (but
+ * for the few outlier groups), so that a trajectory has one order from end to
+ * end, whether its steps are issued by hand or by bh_leapfrog; from the first
+ * bh_kick, bh_drift or bh_leapfrog step on a context its quadrupole force calls
+ * do so too. */
 bh_status bh_kick(bh_ctx *ctx, int64_t n, double *vel, const float *acc, double dt);
 
 /* pos += dt * vel (both FP64 [n][3]). */

@@ -1,6 +1,6 @@
-"""The workgroup walk with list blocks (default options, up to 2048 n_crit
-particles) and the outliers' walk tasks (both below and above that size),
-against the FP64 oracle: list lengths and interaction counts exactly, forces to
+"""The workgroup walk with list blocks (quadrupoles, default options, up to 2048
+n_crit particles), the sums by tiles (the same without quadrupoles) and the
+outliers' walk tasks (both below and above that size), against the FP64 oracle: list lengths and interaction counts exactly, forces to
 the parity bar, list masses to the bound of two orders of one FP64 sum.
 
 Sizes sit at the edges of the path: member blocks of 64 (64/65, 128/129, 256),
@@ -39,15 +39,17 @@ def _check(bh, pos, mass, eps, theta, n_crit, **opts):
 
 @pytest.mark.parametrize("n", [1, 2, 3, 255, 256, 257, 1000])
 @pytest.mark.parametrize("n_crit", [16, 64, 256])
-def test_small_trees(gpu, n, n_crit):
+@pytest.mark.parametrize("quad", [False, True])
+def test_small_trees(gpu, n, n_crit, quad):
     pos, mass = inputs.uniform_cube(n, 3 + n)[:2]
-    _check(gpu, pos, mass, 1e-2, 0.6, n_crit)
+    _check(gpu, pos, mass, 1e-2, 0.6, n_crit, quadrupole=quad)
 
 
 @pytest.mark.parametrize("n_crit", [16, 63, 64, 65, 128, 129, 200, 256])
-def test_member_blocks(gpu, n_crit):
+@pytest.mark.parametrize("quad", [False, True])
+def test_member_blocks(gpu, n_crit, quad):
     pos, mass = inputs.clustered(6000, 11, n_halos=5)[:2]
-    _check(gpu, pos, mass, 1e-4, 0.6, n_crit)
+    _check(gpu, pos, mass, 1e-4, 0.6, n_crit, quadrupole=quad)
 
 
 @pytest.mark.parametrize("quad,curve", [(True, 0), (True, 1), (False, 1)])
@@ -146,19 +148,20 @@ def test_outliers_in_a_batch(gpu):
 
 
 @pytest.mark.parametrize("n,n_crit", [(9000, 64), (40000, 16)])
-def test_replays_and_repeats_agree(gpu, n, n_crit):
+@pytest.mark.parametrize("quad", [False, True])
+def test_replays_and_repeats_agree(gpu, n, n_crit, quad):
     """Outliers included: eager calls and graph replays, with other work on the
     context's buffers between them, give the same bits."""
     bh = gpu
     pos, mass = _spread(n, 4)
     dpos, dmass = to_dev(pos), to_dev(mass)
-    e = bh.Context()
+    e = bh.Context(quadrupole=quad)
     a0, p0 = bh.tree_forces(dpos, dmass, 1e-2, 0.7, n_crit, ctx=e)
     a1, p1 = bh.tree_forces(dpos, dmass, 1e-2, 0.7, n_crit, ctx=e)
     assert torch.equal(a0, a1) and torch.equal(p0, p1)
     a2, p2 = e.compute_forces(1e-2, 0.7)  # the same tree and groups again
     assert torch.equal(a0, a2) and torch.equal(p0, p2)
-    c = bh.Context()
+    c = bh.Context(quadrupole=quad)
     acc, pot = c.graph_capture([0, n], dpos, dmass, n_crit, [1e-2], [0.7])
     for _ in range(3):
         acc.zero_()
@@ -170,12 +173,13 @@ def test_replays_and_repeats_agree(gpu, n, n_crit):
         torch.cuda.synchronize()
 
 
-def test_block_pool_grows(gpu):
+@pytest.mark.parametrize("quad", [False, True])
+def test_block_pool_grows(gpu, quad):
     """Lists far longer than the first estimate (theta small): the walk is run
     again, with the same result as a second call's."""
     bh = gpu
     pos, mass = inputs.clustered(60000, 21, n_halos=30)[:2]
-    c = bh.Context()
+    c = bh.Context(quadrupole=quad)
     c.build_tree(to_dev(pos), to_dev(mass))
     c.make_groups(64)
     a1, p1 = (v.clone() for v in c.compute_forces(1e-4, 0.15))
@@ -185,7 +189,7 @@ def test_block_pool_grows(gpu):
     assert torch.equal(a1, a2) and torch.equal(p1, p2)
     t = oracle.Tree(pos, mass)
     t.groups(64)
-    check_forces(a1.cpu().numpy().astype(np.float64), p1.cpu().numpy().astype(np.float64), t.forces(1e-4, 0.15))
+    check_forces(a1.cpu().numpy().astype(np.float64), p1.cpu().numpy().astype(np.float64), t.forces(1e-4, 0.15, quadrupole=quad))
 
 
 def test_path_boundary(gpu):
