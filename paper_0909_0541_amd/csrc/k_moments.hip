@@ -288,17 +288,21 @@ constexpr int64_t kFewParticles = 16384;
 // and their children have the slots from cfc[f] on, at most 2 c - 2.  Bound by
 // latency for small trees (subtree, its arrays, levels, records) and by the
 // scattered 64-byte records for large ones: 11 us at 8192 particles, 380 us at
-// 4M (records and sums read and written once: 150 us), 132 us with second
-// moments at 300k.  One launch per tree level over sums in global memory, with
+// 4M (records and sums read and written once: 150 us).  One launch per tree level over sums in global memory, with
 // a pass for the slots and leaves and a counting sort of the cells by level
 // before: the whole build of 8192, 100k, 1M and 4M particles 158, 270, 544 and
 // 1443 us; with this 78, 198, 481 and 1342 us.  Subtrees of 256 with second
-// moments: of 512 (one workgroup a compute unit) took 222 us.
+// moments: of 512 (one workgroup a compute unit) took 222 us.  They are bound by
+// the workgroups in flight: with moments in LDS for cells only, not leaves, and
+// five waves a SIMD the build of 300k, 1M and 4M particles takes 386, 800 and
+// 2416 us, with room for three workgroups 405, 873 and 2759 (launches by level:
+// 505, 759 and 1990).
 template <int SUB, bool QUAD>
-__global__ __launch_bounds__(SUB) void k_subtrees(MomentArgs a) {
+__global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 1))) void k_subtrees(MomentArgs a) {
   constexpr int LOCAL = 2 * SUB, ROOT = LOCAL - 1;
   __shared__ double sm[LOCAL][4];
-  __shared__ double qm[QUAD ? LOCAL : 1][6];
+  __shared__ double qm[QUAD ? SUB : 1][6];   // of the cell owned at a position
+  __shared__ int16_t cell[QUAD ? LOCAL : 1];  // that position, -1: a particle
   __shared__ int lcfc[SUB], lmask[SUB];
   __shared__ int8_t llev[SUB];
   __shared__ uint32_t levels;
@@ -359,8 +363,7 @@ __global__ __launch_bounds__(SUB) void k_subtrees(MomentArgs a) {
         for (int k = 0; k < 4; ++k) sm[at][k] = sum[k];
         if (QUAD) {
           leaf = at;
-#pragma unroll
-          for (int k = 0; k < 6; ++k) qm[at][k] = 0.0;
+          cell[at] = -1;
         }
       }
     }
@@ -426,6 +429,7 @@ __global__ __launch_bounds__(SUB) void k_subtrees(MomentArgs a) {
       if (lev >= 0)
 #pragma unroll
         for (int k = 0; k < 3; ++k) sm[own][1 + k] = com[k];
+      if (lev >= 0) cell[own] = (int16_t)t;
       __syncthreads();
       double M[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
       for (uint32_t L = all; L;) {
@@ -434,10 +438,11 @@ __global__ __launch_bounds__(SUB) void k_subtrees(MomentArgs a) {
         if (lev == cur) {
           for (int k = 0; k < c.nc; ++k) {
             const double mc = sm[lc0 + k][0];
-            if (mc > 0.0) shift_moments(M, com, mc, &sm[lc0 + k][1], qm[lc0 + k]);
+            const int at = cell[lc0 + k];
+            if (mc > 0.0) shift_moments(M, com, mc, &sm[lc0 + k][1], at >= 0 ? qm[at] : nullptr);
           }
 #pragma unroll
-          for (int k = 0; k < 6; ++k) qm[own][k] = M[k];
+          for (int k = 0; k < 6; ++k) qm[t][k] = M[k];
         }
         __syncthreads();
       }
