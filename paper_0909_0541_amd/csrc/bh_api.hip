@@ -1186,6 +1186,7 @@ static bh_status capture_common(bh_ctx *c, int32_t n_systems, const int64_t *off
     hipError_t e = hipStreamEndCapture(c->stream, &g);
     c->capturing = false;
     c->stream = saved;
+    c->counters_clean = c->xq_clean = false;  // (what was recorded has not run)
     if (sr) {
       if (g) (void)hipGraphDestroy(g);
       return sr;
@@ -1225,6 +1226,7 @@ bh_status bh_graph_launch(bh_ctx *c) {
   if (!c) return BH_EINVAL;
   c->err.clear();
   if (!c->graph) return fail(c, BH_ESTATE, "no captured step");
+  c->counters_clean = c->xq_clean = false;  // the replay uses the queues up
   return hip_check(c, hipGraphLaunch(c->graph, c->stream), "hipGraphLaunch");
 }
 

@@ -175,7 +175,7 @@ struct bh_ctx {
   int32_t nsys = 0;
   bool have_tree = false;
   bool have_groups = false;
-  bool xq_clean = false;  // the per-XCD group queues are known to be 0 (reset by make_groups, used by walks)
+  bool xq_clean = false;  // the per-XCD group queues are known to be 0 (reset by make_groups, used by walks, replays)
   bool walk_order_valid = false;  // walk_order holds a permutation of the current groups (bh_group_theta)
   bool have_forces = false;
   bool have_quad = false;  // the current tree carries second moments
@@ -247,7 +247,7 @@ struct bh_ctx {
   bh::DevBuf wide_buf;  // list blocks, rows of partial sums, outliers and their walk tasks
   bh::DevBuf tile_buf;  // sums by list tiles: partial sums, rows, rows of a group
   int32_t wide_cap = 0, wide_block = 0;  // blocks in the pool, entries per block
-  bool counters_clean = false;           // the force counters are known to be 0 (reset by make_groups)
+  bool counters_clean = false;           // the force counters are known to be 0 (reset by make_groups, used by forces, replays)
   hipEvent_t info_event = nullptr;       // completion of a read-back of the counters
   bh::DevBuf order_hist;        // int32 cost bins of the queue orders
   bh::DevBuf walk_order;        // int32 [n] order in which the list walk takes the groups (learned theta)
