@@ -266,8 +266,10 @@ bh_status bh_graph_capture(bh_ctx *ctx, int32_t n_systems, const int64_t *offset
                            const double *mass, int32_t n_crit, const double *eps_sys, const double *theta_sys,
                            const float *theta_group, float *acc, float *pot);
 
-/* Replay the captured step on the context's stream (asynchronous).
- * BH_ESTATE without a capture. */
+/* Replay the captured step on the context's stream (asynchronous).  The
+ * context's current tree, groups and forces are then the step's, whatever calls
+ * came before (with theirs in between, the replay first uploads its own systems
+ * and parameters again).  BH_ESTATE without a capture. */
 bh_status bh_graph_launch(bh_ctx *ctx);
 
 /* Counters of the current tree, groups and last force call, and the timings

@@ -336,7 +336,7 @@ class Context:
         self._check(self._L.bh_graph_capture(self._h, ns, off.ctypes.data_as(C.c_void_p), _ptr(pos), _ptr(mass),
                                              int(n_crit), e.ctypes.data_as(C.c_void_p), t.ctypes.data_as(C.c_void_p),
                                              _ptr(theta_group), _ptr(acc), _ptr(pot)))
-        self.n, self.n_systems = n, ns
+        self.n, self.n_systems = self._graph_size = n, ns
         self._graph_io = (pos, mass, acc, pot, theta_group)  # keep the captured buffers alive
         return acc, pot
 
@@ -370,13 +370,14 @@ class Context:
                                                      _ptr(mass), int(n_crit), e.ctypes.data_as(C.c_void_p),
                                                      t.ctypes.data_as(C.c_void_p), C.byref(net), float(shift),
                                                      _ptr(theta_group), _ptr(acc), _ptr(pot)))
-        self.n, self.n_systems = n, ns
+        self.n, self.n_systems = self._graph_size = n, ns
         # keep the captured buffers (and the network) alive
         self._graph_io = (pos, mass, acc, pot, theta_group, params, mu, sigma)
         return acc, pot, theta_group
 
     def graph_launch(self):
         self._check(self._L.bh_graph_launch(self._h))
+        self.n, self.n_systems = self._graph_size
 
     def get_stats(self) -> Stats:
         s = _Stats()

@@ -175,11 +175,12 @@ static double timer_take(Timer &t, int32_t *calls) {
   return total;
 }
 
-// Copy host data to the device through a pinned staging buffer; the staging
-// buffer is reused only after the previous upload has completed.
+// Copy systems or parameters to the device through a pinned staging buffer,
+// which is reused only after the previous upload has completed.
 static bh_status upload(bh_ctx *c, void *dst, const void *src, size_t bytes) {
   if (bytes == 0) return BH_OK;
   if (c->capturing) return BH_OK;  // the eager run before the capture left the same data on the device
+  c->data_moved = true;            // (a replay brings its own back)
   bh_status st;
   if (c->stage_event_used) {
     st = hip_check(c, hipEventSynchronize(c->stage_event), "hipEventSynchronize");
@@ -1194,8 +1195,27 @@ static bh_status capture_common(bh_ctx *c, int32_t n_systems, const int64_t *off
     st = hip_check(c, e, "hipStreamEndCapture");
     if (!st) st = hip_check(c, hipGraphInstantiate(&c->graph, g, nullptr, nullptr, 0), "hipGraphInstantiate");
     if (g) (void)hipGraphDestroy(g);
-    if (st) c->graph = nullptr;
-    return st;
+    if (st) {
+      c->graph = nullptr;
+      return st;
+    }
+    Captured &k = c->captured;
+    k.n = c->n;
+    k.nsys = c->nsys;
+    k.n_crit = c->n_crit;
+    k.quad = c->have_quad;
+    k.learned = net != nullptr;
+    k.sorted_keys = c->sorted_keys;
+    k.sys = c->sys_host;
+    k.par = c->par_host;
+    k.feps.clear();
+    if (net) k.feps = c->feps_host;
+    k.split_groups = c->last_split_groups;
+    k.segments = c->last_segments;
+    k.depth = c->last_depth;
+    k.attempts = c->last_attempts;
+    c->data_moved = false;
+    return BH_OK;
   }
   c->capturing = false;
   c->stream = saved;
@@ -1226,8 +1246,32 @@ bh_status bh_graph_launch(bh_ctx *c) {
   if (!c) return BH_EINVAL;
   c->err.clear();
   if (!c->graph) return fail(c, BH_ESTATE, "no captured step");
+  // the step's systems and parameters, where other calls have brought theirs
+  // (the buffers are those of the capture: growing one would have ended it)
+  const Captured &k = c->captured;
+  if (c->data_moved) {
+    bh_status st = upload(c, c->sys.p, k.sys.data(), sizeof(SysInfo) * k.sys.size());
+    if (!st) st = upload(c, c->par.p, k.par.data(), sizeof(SysParam) * k.par.size());
+    if (!st) st = upload(c, c->feps.p, k.feps.data(), sizeof(double) * k.feps.size());
+    if (st) return st;
+    c->data_moved = false;
+  }
   c->counters_clean = c->xq_clean = false;  // the replay uses the queues up
-  return hip_check(c, hipGraphLaunch(c->graph, c->stream), "hipGraphLaunch");
+  bh_status st = hip_check(c, hipGraphLaunch(c->graph, c->stream), "hipGraphLaunch");
+  if (st) return st;
+  c->n = k.n;
+  c->nsys = k.nsys;
+  c->n_crit = k.n_crit;
+  c->have_tree = c->have_groups = c->have_forces = true;
+  c->have_quad = k.quad;
+  c->have_neighbors = false;
+  c->walk_order_valid = k.learned;
+  c->sorted_keys = k.sorted_keys;
+  c->last_split_groups = k.split_groups;
+  c->last_segments = k.segments;
+  c->last_depth = k.depth;
+  c->last_attempts = k.attempts;
+  return BH_OK;
 }
 
 bh_status bh_get_stats(bh_ctx *c, bh_stats *out) {

@@ -160,6 +160,19 @@ struct Timer {
   bool open = false;
 };
 
+// What the host knows of the captured step: a replay makes its tree, groups
+// and forces the context's, and reads the systems and parameters on the device.
+struct Captured {
+  int64_t n = 0;
+  int32_t nsys = 0, n_crit = 0;
+  bool quad = false, learned = false;
+  uint64_t *sorted_keys = nullptr;
+  std::vector<SysInfo> sys;
+  std::vector<SysParam> par;
+  std::vector<double> feps;
+  int32_t split_groups = 0, segments = 0, depth = 0, attempts = 0;  // of its eager run
+};
+
 }  // namespace bh
 
 struct bh_ctx {
@@ -185,6 +198,8 @@ struct bh_ctx {
   bool capturing = false;         // recording a step into a HIP graph: no uploads, syncs or timers
   hipStream_t capture_stream = nullptr;
   hipGraphExec_t graph = nullptr; // the captured step
+  bh::Captured captured;          // (with graph)
+  bool data_moved = false;        // systems or parameters were uploaded since the capture or its last replay
   int32_t n_crit = 0;
   int64_t cap_n = 0;  // particle capacity of the per-particle buffers
 

@@ -36,15 +36,18 @@ def test_forces_after_a_replay(gpu, n, n_crit, quad):
     bh = gpu
     pos, mass = _case(n, 7)
     want = _fresh(bh, pos, mass, n_crit, 0.8, quadrupole=quad)
+    replayed = _fresh(bh, pos, mass, n_crit, 0.6, quadrupole=quad)
     c = bh.Context(quadrupole=quad)
-    c.graph_capture([0, n], pos, mass, n_crit, EPS, 0.6)
+    acc, pot = c.graph_capture([0, n], pos, mass, n_crit, EPS, 0.6)
     for k in range(2):
+        acc.zero_()
         c.build_tree(pos, mass)
         c.make_groups(n_crit)
         c.graph_launch()
         a, p = c.compute_forces(EPS, 0.8, acc=_nan(n)[0], pot=_nan(n)[1])
         c.sync()
         assert torch.equal(a, want[0]) and torch.equal(p, want[1]), k
+        assert torch.equal(acc, replayed[0]) and torch.equal(pot, replayed[1]), k
 
 
 def test_features_after_a_replay(gpu):
@@ -60,3 +63,107 @@ def test_features_after_a_replay(gpu):
     c.make_groups(64)
     c.graph_launch()
     assert torch.equal(c.group_features(EPS, groups), want)
+
+
+def test_other_parameters_between_replays(gpu):
+    """Replays keep the theta and softening of the capture."""
+    bh = gpu
+    n = 20000
+    pos, mass = _case(n, 9)
+    want = _fresh(bh, pos, mass, 64, 0.6)
+    c = bh.Context()
+    acc, pot = c.graph_capture([0, n], pos, mass, 64, EPS, 0.6)
+    for k in range(3):
+        c.compute_forces(7 * EPS, 0.9)
+        acc.zero_()
+        c.graph_launch()
+        c.sync()
+        assert torch.equal(acc, want[0]) and torch.equal(pot, want[1]), k
+
+
+@pytest.mark.parametrize("quad", [False, True])
+def test_other_tree_between_replays(gpu, quad):
+    """A smaller tree, in smaller groups, built between replays: a replay's tree
+    and groups are again the context's, with all that can be asked of them."""
+    bh = gpu
+    n, m = 20000, 5000
+    pos, mass = _case(n, 10)
+    opos, omass = _case(m, 11)
+    want = _fresh(bh, pos, mass, 200, 0.6, quadrupole=quad)
+    other = _fresh(bh, opos, omass, 16, 0.7, quadrupole=quad)
+    f = bh.Context(quadrupole=quad)
+    f.build_tree(pos, mass)
+    groups = f.make_groups(200)
+    later = f.compute_forces(EPS, 0.8)
+    lists = f.export_groups(lists=True)
+    keys = f.export_sorted()
+    h = torch.full((n,), 0.02, dtype=torch.float64, device="cuda")
+    counts = f.neighbors(h)[0]
+    c = bh.Context(quadrupole=quad)
+    c.build_tree(pos, mass)
+    c.make_groups(200)
+    c.neighbors(h)  # (its buffers, before the capture)
+    acc, pot = c.graph_capture([0, n], pos, mass, 200, EPS, 0.6)
+    for k in range(2):
+        a, p = bh.tree_forces(opos, omass, EPS, 0.7, 16, ctx=c)
+        assert torch.equal(a, other[0]) and torch.equal(p, other[1]), k
+        acc.zero_()
+        c.graph_launch()
+        c.sync()
+        assert torch.equal(acc, want[0]) and torch.equal(pot, want[1]), k
+        st = c.get_stats()
+        assert (st.n, st.n_crit, st.n_groups, st.error_flags) == (n, 200, groups, 0)
+        assert all(torch.equal(x, y) for x, y in zip(c.export_sorted(), keys))
+        assert torch.equal(c.neighbors(h)[0], counts)
+        a, p = c.compute_forces(EPS, 0.8)
+        assert torch.equal(a, later[0]) and torch.equal(p, later[1]), k
+        assert all(torch.equal(x, y) for x, y in zip(c.export_groups(lists=True), lists))
+
+
+def test_single_tree_between_replays_of_a_batch(gpu):
+    bh = gpu
+    sizes = [3000, 1, 7000, 0, 500]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(off[-1])
+    pos, mass = _case(n, 12)
+    eps, theta = [EPS * (k + 1) for k in range(5)], [0.5 + 0.1 * k for k in range(5)]
+    f = bh.Context()
+    f.build_batch(off, pos, mass)
+    f.make_groups(64)
+    want = f.compute_forces_batch(eps, theta)
+    c = bh.Context()
+    acc, pot = c.graph_capture(off, pos, mass, 64, eps, theta)
+    opos, omass = _case(6000, 13)
+    for k in range(2):
+        bh.tree_forces(opos, omass, EPS, 0.7, 32, ctx=c)
+        acc.zero_()
+        c.graph_launch()
+        c.sync()
+        assert torch.equal(acc, want[0]) and torch.equal(pot, want[1]), k
+        a, p = c.compute_forces_batch(eps, theta)
+        assert torch.equal(a, want[0]) and torch.equal(p, want[1]), k
+
+
+def test_other_tree_between_learned_replays(gpu):
+    bh = gpu
+    from paper_0909_0541_amd import learned
+
+    net = learned.ThetaNet.load(learned.DEFAULT_NET)
+    n = 20000
+    pos, mass = _case(n, 14)
+    opos, omass = _case(5000, 15)
+    c = bh.Context()
+    acc, pot, theta = c.graph_capture_learned([0, n], pos, mass, 64, EPS, 0.6, net.params, net.mu, net.sigma)
+    groups = c.get_stats().n_groups
+    want = acc.clone(), pot.clone(), theta[:groups].clone()
+    for k in range(2):
+        c.build_tree(opos, omass)
+        c.make_groups(32)
+        c.compute_forces(EPS, 0.7, theta_group=c.group_theta(net.params, net.mu, net.sigma, 5 * EPS))
+        acc.zero_()
+        c.graph_launch()
+        c.sync()
+        assert torch.equal(acc, want[0]) and torch.equal(pot, want[1]) and torch.equal(theta[:groups], want[2]), k
+        # the replay's groups, theta and walk order together
+        a, p = c.compute_forces(EPS, 0.6, theta_group=theta)
+        assert torch.equal(a, want[0]) and torch.equal(p, want[1]), k
