@@ -645,6 +645,9 @@ static void wide_capacity(bh_ctx *c, int block, int64_t want) {
   if (!c->capturing && c->wide_cap < want) c->wide_cap = (int32_t)std::min<int64_t>(want, INT32_MAX / 2);
 }
 
+// The walk's counters have arrived: rows of list blocks beyond their arrays.
+static bool wide_overrun(const bh_ctx *c) { return c->info_host->rows > c->wide_cap; }
+
 static void wide_grow(bh_ctx *c) {
   const int64_t need = c->info_host->blocks;
   if (need > c->wide_cap) c->wide_cap = (int32_t)std::min<int64_t>(need + need / 4 + 64, INT32_MAX / 2);
@@ -698,6 +701,7 @@ static bh_status forces_wide(bh_ctx *c, const float *theta_group, float *acc, fl
     if (c->capturing) break;
     st = hip_check(c, hipEventSynchronize(c->info_event), "hipEventSynchronize");
     if (st) return st;
+    if (wide_overrun(c)) return fail(c, BH_EINTERNAL, "more rows of list blocks than blocks");
     if (!(c->info_host->err & (kErrPool | kErrWide))) break;
     if (attempt > 5) return fail(c, BH_EINTERNAL, "interaction list pool still too small after growing");
     if (c->info_host->err & kErrWide) c->out_off = true;  // every group by one workgroup
@@ -938,6 +942,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
       st = hip_check(c, hipEventSynchronize(c->info_event), "hipEventSynchronize");
       if (st) return st;
       c->last_segments = c->last_split_groups = c->last_depth = 0;
+      if (outliers && wide_overrun(c)) return fail(c, BH_EINTERNAL, "more rows of list blocks than blocks");
       if (!(c->info_host->err & (kErrPool | kErrWide))) return BH_OK;
     }
     if (visit_cap > 0) {
@@ -955,6 +960,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
                      "hipMemcpyAsync info");
       if (!st) st = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
       if (st) return st;
+      if (wide_overrun(c)) return fail(c, BH_EINTERNAL, "more rows of list blocks than blocks");
     }
     if (visit_cap > 0) nsegs_host = c->split_host->segs;
     c->last_segments = nsegs_host;

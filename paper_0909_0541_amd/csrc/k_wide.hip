@@ -312,8 +312,10 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
     for (int d = 1; d < kWave; d <<= 1) lmass += shfl_xor_d(lmass, d);
     if (lane == 0) wm[wv] = lmass;
     __syncthreads();
-    // The list's blocks, far then near, get consecutive rows.
-    const int nused = corrupt ? 0 : fblocks + nblocks;
+    // The list's blocks, far then near, get consecutive rows.  A list that did
+    // not fit gets none: rows then number blocks of the pool, each once, and
+    // never exceed its capacity, that of the arrays over rows.
+    const int nused = corrupt || !ok ? 0 : fblocks + nblocks;
     if (t == 0) {
       double m = wm[0];
       for (int w = 1; w < NW; ++w) m += wm[w];
@@ -352,9 +354,7 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
       }
     }
     __syncthreads();
-    if (ok && !corrupt) {
-      // (every used block has one row, so the rows are within their capacity,
-      // the pool's, when the blocks are)
+    if (nused > 0) {
       const int row = __builtin_amdgcn_readfirstlane(sh_id);
       for (int k = t; k < nused; k += NT) {
         const bool nr = k >= fblocks;
