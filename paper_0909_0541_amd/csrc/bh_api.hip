@@ -417,7 +417,7 @@ void bh_destroy(bh_ctx *c) {
                     &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_stat, &c->nb_out, &c->nb_count, &c->nb_rho, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
                     &c->split_ctr, &c->gsplit, &c->gnseg, &c->gsegfirst, &c->skeys[0], &c->skeys[1], &c->svals[0],
                     &c->svals[1], &c->shist, &c->sscan, &c->srows, &c->spbase, &c->sgroups, &c->psum,
-                    &c->tile_buf, &c->wide_buf,
+                    &c->tile_buf, &c->wide_buf, &c->out_list,
                     &c->qmom, &c->qpack, &c->far_slot};
   for (DevBuf *b : bufs) free_buf(*b);
   if (c->graph) (void)hipGraphExecDestroy(c->graph);
@@ -551,7 +551,15 @@ constexpr int kWideMinCrit = 16;
 // tasks).
 constexpr int kOutMinWide = 4096;
 constexpr int kOutMinTree = 6500;
-constexpr int kOutMin = 16384;
+constexpr int64_t kOutMin = 16384;
+// Beyond 4.2 million particles an outlier makes at least as many tests as a
+// wave of the walk does for 16 particles of its share: where the ordinary groups
+// keep the waves busy that long, the launch does not wait for it.  The walk that
+// is given up counts too, whenever it started, so the line lies low: Plummer
+// spheres, n_crit 64, forces in us with 16 and with 40 in this place: 20 spheres
+// of 400,000 13711 and 14999, 40 of 100,000 6740 and 7180, 256 of 20,000 8725 and
+// 7277, 512 13749 and 13858 (with the line at kOutMin, 1088 outliers, 17351).
+constexpr int kOutMinShare = 16;
 // Largest tree with outliers apart, and their block length: a task's list (at
 // most kTaskNodes cells of n / 2048 particles) then fits the block table.
 constexpr int64_t kOutMaxN = 1 << 26;
@@ -596,7 +604,6 @@ static bh_status wide_args(bh_ctx *c, bool groups, const float *theta_group, flo
               {(void **)&A.gstat, groups ? sizeof(int2) * (size_t)c->n : 0},
               {(void **)&A.binfo, cap * sizeof(int4)},
               {(void **)&A.psum, cap * (size_t)c->n_crit * 4 * sizeof(double)},
-              {(void **)&A.out, sizeof(int32_t) * kOutMax},
               {(void **)&A.outinfo, sizeof(OutInfo) * kOutMax},
               {(void **)&A.tnodes, sizeof(int32_t) * (size_t)kOutMax * kOutNodes},
               {(void **)&A.tasks, sizeof(int4) * (size_t)kTaskCap},
@@ -606,7 +613,10 @@ static bh_status wide_args(bh_ctx *c, bool groups, const float *theta_group, flo
   size_t total = 0;
   for (auto &w : want) total += padded(w.bytes);
   bh_status st = ensure(c, c->wide_buf, total, "list blocks");
+  if (!st) st = ensure(c, c->out_list, sizeof(int32_t) * kOutPlaces, "outlier groups");
   if (st) return st;
+  A.out = P<int32_t>(c->out_list);
+  A.out_places = kOutPlaces;
   char *at = P<char>(c->wide_buf);
   for (auto &w : want) {
     *w.p = w.bytes ? at : nullptr;
@@ -649,7 +659,7 @@ static void wide_capacity(bh_ctx *c, int block, int64_t want) {
 static bool wide_overrun(const bh_ctx *c) { return c->info_host->rows > c->wide_cap; }
 
 static void wide_grow(bh_ctx *c) {
-  const int64_t need = c->info_host->blocks;
+  const int64_t need = std::max(c->info_host->blocks, c->info_host->blocks_done);
   if (need > c->wide_cap) c->wide_cap = (int32_t)std::min<int64_t>(need + need / 4 + 64, INT32_MAX / 2);
 }
 
@@ -766,8 +776,53 @@ static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &
   return st;
 }
 
+// The outliers of the lists' walk, kOutMax at a time from the `first` such
+// lot on, their sums after the lists' (which leave an outlier's members with
+// none).  *whole: one of their lists does not fit, every group has to be walked
+// whole.  A captured step records as many lots as its eager run's outliers and a
+// quarter more would fill.  (128 Plummer spheres of 20,000 particles, 272
+// outliers, forces: 7169 us with every group walked a second time, whole, where
+// they are more than 256, 4731 in lots.)
+static bh_status outlier_rounds(bh_ctx *c, const float *theta_group, float *acc, float *pot, int first, bool *whole) {
+  *whole = false;
+  if (!c->capturing) {
+    const int n_out = std::min(c->info_host->n_out, kOutPlaces);
+    c->out_rounds = std::max((n_out + n_out / 4 + kOutMax - 1) / kOutMax, 1);
+  }
+  const int rounds = c->capturing ? c->out_rounds : (std::min(c->info_host->n_out, kOutPlaces) + kOutMax - 1) / kOutMax;
+  for (int r = first; r < rounds; ++r) {
+    WideArgs A{};
+    for (int attempt = 0;; ++attempt) {
+      bh_status st = wide_args(c, false, theta_group, acc, pot, A);
+      if (st) return st;
+      A.out_first = r * kOutMax;
+      A.out_limit = c->capturing ? c->out_rounds * kOutMax : 0;
+      if (r > 0 || attempt > 0) next_outliers_device(A.info, attempt > 0, c->stream);
+      walk_outliers_device(A, c->stream);
+      walk_tasks_device(A, c->num_cu, c->stream);
+      if (c->capturing) break;
+      st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
+                     "hipMemcpyAsync info");
+      if (!st) st = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
+      if (st) return st;
+      if (wide_overrun(c)) return fail(c, BH_EINTERNAL, "more rows of list blocks than blocks");
+      if (c->info_host->err & kErrWide) {
+        *whole = true;
+        return BH_OK;
+      }
+      if (!(c->info_host->err & kErrPool)) break;
+      if (attempt > 5) return fail(c, BH_EINTERNAL, "interaction list pool still too small after growing");
+      wide_grow(c);
+    }
+    force_blocks_device(A, c->num_cu, c->stream);
+    task_reduce_device(A, c->stream);
+  }
+  return hip_check(c, hipGetLastError(), "kernel launch (outliers)");
+}
+
+// walk_whole: no outliers apart (they had lists that do not fit).
 static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *theta_sys, const float *theta_group,
-                               float *acc, float *pot) {
+                               float *acc, float *pot, bool walk_whole = false) {
   if (!c->have_groups) return fail(c, BH_ESTATE, "forces requested before bh_make_groups");
   if (c->n > 0 && (!acc || !pot)) return fail(c, BH_EINVAL, "acc and pot must not be NULL");
   const bool quad = c->opt.quadrupole != 0;
@@ -827,8 +882,13 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   const int fgrid = c->num_cu * (c->opt.waves_per_cu > 0 ? c->opt.waves_per_cu : (quad ? c->force_bpc_q : c->force_bpc));
   // Split walks only on request; by default outliers go to the workgroup walk.
   const int visit_cap = std::max(c->opt.split_visits, 0);
-  if (!c->capturing) c->out_off = false;
-  const int out_min = few ? kOutMinWide : kOutMin;
+  if (!c->capturing) {
+    c->out_off = walk_whole;
+    c->out_rounds = 1;
+  }
+  const int out_min =
+      few ? kOutMinWide
+          : (int)std::min<int64_t>(std::max(kOutMin, kOutMinShare * c->n / (c->num_cu * c->walk_bpc)), INT32_MAX);
   bool outliers = c->opt.split_visits == 0 && c->n <= kOutMaxN && (few ? c->n > kOutMinTree : 2 * c->n > out_min) && !c->out_off;
   if (outliers) wide_capacity(c, kOutBlock, 2 * c->n / kOutBlock + (few ? 512 : 4096));
   if (c->seg_cap == 0) {
@@ -903,6 +963,8 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
       st = wide_args(c, false, theta_group, acc, pot, A);
       if (st) return st;
       W.out = A.out;
+      W.out_places = A.out_places;
+      A.out_limit = c->capturing ? c->out_rounds * kOutMax : 0;
     }
     W.order = (theta_group && c->walk_order_valid) ? P<int32_t>(c->walk_order) : nullptr;
     W.wait_ticks = c->wait_ticks;
@@ -914,8 +976,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     c->last_attempts = attempt + 1;
     walk_lists_device(W, grid, c->stream);
     c->xq_clean = false;
-    // (outside a capture the host looks first whether there are outliers)
-    if (outliers && (c->capturing || few)) {
+    if (outliers && few) {  // (the first of them)
       walk_outliers_device(A, c->stream);
       walk_tasks_device(A, c->num_cu, c->stream);
     }
@@ -938,12 +999,18 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
         if (st) return st;
       }
       st = forces_tiles(c, W, A, outliers, acc, pot);
+      if (!st && c->capturing && outliers) st = outlier_rounds(c, theta_group, acc, pot, 1, &have_out);
       if (st || c->capturing) return st;
       st = hip_check(c, hipEventSynchronize(c->info_event), "hipEventSynchronize");
       if (st) return st;
       c->last_segments = c->last_split_groups = c->last_depth = 0;
       if (outliers && wide_overrun(c)) return fail(c, BH_EINTERNAL, "more rows of list blocks than blocks");
-      if (!(c->info_host->err & (kErrPool | kErrWide))) return BH_OK;
+      if (!(c->info_host->err & (kErrPool | kErrWide))) {
+        if (!outliers) return BH_OK;
+        bool whole;
+        st = outlier_rounds(c, theta_group, acc, pot, 1, &whole);
+        return whole ? forces_common(c, eps_sys, theta_sys, theta_group, acc, pot, true) : st;
+      }
     }
     if (visit_cap > 0) {
       st = hip_check(c, hipMemcpyAsync(c->split_host, W.ctr, sizeof(SplitCounters), hipMemcpyDeviceToHost,
@@ -952,16 +1019,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     }
     st = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
     if (st) return st;
-    have_out = outliers && !few && c->info_host->n_out > 0;
-    if (have_out) {
-      walk_outliers_device(A, c->stream);
-      walk_tasks_device(A, c->num_cu, c->stream);
-      st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
-                     "hipMemcpyAsync info");
-      if (!st) st = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
-      if (st) return st;
-      if (wide_overrun(c)) return fail(c, BH_EINTERNAL, "more rows of list blocks than blocks");
-    }
+    have_out = outliers && c->info_host->n_out > 0;
     if (visit_cap > 0) nsegs_host = c->split_host->segs;
     c->last_segments = nsegs_host;
     c->last_split_groups = visit_cap > 0 ? c->split_host->n_split : 0;
@@ -1046,12 +1104,10 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   if (st) return st;
   force_lists_device(F, fgrid, c->stream);
   if (have_out) {
-    // (after the lists' sums, which leave an outlier's members with none)
-    WideArgs A{};
-    st = wide_args(c, false, theta_group, acc, pot, A);
+    bool whole;
+    st = outlier_rounds(c, theta_group, acc, pot, 0, &whole);
     if (st) return st;
-    force_blocks_device(A, c->num_cu, c->stream);
-    task_reduce_device(A, c->stream);
+    if (whole) return forces_common(c, eps_sys, theta_sys, theta_group, acc, pot, true);
   }
   st = timer_stop(c, c->t_force);
   if (st) return st;
@@ -1300,9 +1356,9 @@ bh_status bh_get_stats(bh_ctx *c, bh_stats *out) {
     out->interactions = (int64_t)d.interactions;
     out->list_entries = (int64_t)d.list_entries;
     out->max_list = d.max_list;
-    const int32_t outs = std::min(d.n_out, kOutMax);
+    const int32_t outs = std::min(d.n_out, kOutPlaces);
     out->n_split_groups = c->last_split_groups + outs;
-    out->n_segments = c->last_segments + outs + d.tasks;
+    out->n_segments = c->last_segments + outs + d.tasks_done + d.tasks;
     out->n_split_levels = outs ? 1 : c->last_depth;
     out->n_walk_attempts = c->last_attempts;
     out->n_theta_fallback = d.theta_fallback;

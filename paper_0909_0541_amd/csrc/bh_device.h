@@ -101,9 +101,9 @@ __device__ __forceinline__ int outlier_cap(int out_min, int n_crit, int count, d
 
 // Place among the outliers; beyond the last one an error that makes the host
 // walk every group whole.  One lane.
-__device__ __forceinline__ int take_outlier(DevInfo *info) {
+__device__ __forceinline__ int take_outlier(DevInfo *info, int places) {
   const int o = atomicAdd(&info->n_out, 1);
-  if (o < kOutMax) return o;
+  if (o < places) return o;
   atomicOr(&info->err, kErrWide);
   return -1;
 }

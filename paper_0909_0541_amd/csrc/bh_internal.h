@@ -82,8 +82,10 @@ struct DevInfo {
   alignas(128) int32_t queue2;  // force work queue head
   alignas(128) int32_t blocks;  // list blocks taken by the workgroup walk (may exceed the pool: then it is the need)
   int32_t rows;                 // list blocks it used (rows of partial sums)
-  int32_t n_out;                // outlier groups (more than kOutMax: an error, the host walks another way)
-  int32_t tasks;                // their walk tasks
+  int32_t n_out;                // outlier groups (more than there are places: an error, the host walks another way)
+  int32_t tasks;                // walk tasks of the outliers in hand
+  int32_t tasks_done;           // of those before them
+  int32_t blocks_done;          // most list blocks taken for those before them
   int32_t tile_rows;            // tiles of the lists (k_tile_rows)
   alignas(128) int32_t far_chunks;   // runs of kChunkRun list chunks taken (may exceed the pool: then it is the need)
   alignas(128) int32_t near_chunks;
@@ -111,7 +113,7 @@ enum : int32_t {
   kErrPool = 32,
   kErrWait = 64,          // a bounded wait ended without its condition (walk tasks, sort look-back)
   kErrRadius = 128,      // neighbour search: a radius not positive and finite
-  kErrWide = 512,        // too many outliers, or a list too long for the block table (the host walks another way)
+  kErrWide = 512,        // more outliers than places, or a list too long for the block table (the host walks another way)
   kErrListSpace = 256,   // neighbour search: offsets leave a list too little or too much room
 };
 
@@ -193,7 +195,8 @@ struct bh_ctx {
   bool have_forces = false;
   bool have_quad = false;  // the current tree carries second moments
   bool have_neighbors = false;  // a neighbour search ran since the last build
-  bool out_off = false;    // the last force call found more outliers than fit: every group walked whole
+  bool out_off = false;    // the last force call found more outliers than places: every group walked whole
+  int out_rounds = 1;      // times kOutMax outliers of the last force call
   bool integrates = false; // a kick or drift ran on this context: its quadrupole sums keep the single-wave list order too
   bool capturing = false;         // recording a step into a HIP graph: no uploads, syncs or timers
   hipStream_t capture_stream = nullptr;
@@ -259,7 +262,8 @@ struct bh_ctx {
   bh::DevBuf mlp_work;          // training batch workspace
   bh::DevBuf mlp_feat;          // FP32 [n][12] features of bh_group_theta
   // lists in blocks (sizes at which a group is walked by a workgroup)
-  bh::DevBuf wide_buf;  // list blocks, rows of partial sums, outliers and their walk tasks
+  bh::DevBuf wide_buf;  // list blocks, rows of partial sums, outliers' walk tasks
+  bh::DevBuf out_list;  // outlier groups
   bh::DevBuf tile_buf;  // sums by list tiles: partial sums, rows, rows of a group
   int32_t wide_cap = 0, wide_block = 0;  // blocks in the pool, entries per block
   bool counters_clean = false;           // the force counters are known to be 0 (reset by make_groups, used by forces, replays)
@@ -431,7 +435,8 @@ struct WalkListArgs {
   int32_t *gsplit;           // per group: 1 when its list is in segments
   int out_min;               // smallest number of node tests that makes a group an outlier (0: never, see outlier_cap)
   int n_crit;
-  int32_t *out;              // [kOutMax] outlier groups (info->n_out of them)
+  int32_t *out;              // [out_places] outlier groups (info->n_out of them)
+  int out_places;
   const int32_t *order;      // nullable: the groups in the order the walk takes them; each eighth of
                              // [0, G) a permutation of itself (walk_order_device)
 };
@@ -573,7 +578,8 @@ int force_lists_blocks_per_cu(bool quad);
 void reset_list_counters(DevInfo *info, hipStream_t s);
 
 // k_wide.hip: walk by workgroups, sums over list blocks
-constexpr int kOutMax = 256;      // outlier groups of one walk
+constexpr int kOutMax = 256;      // outlier groups walked and summed together
+constexpr int kOutPlaces = 1 << 16;  // outlier groups of a call, kOutMax at a time
 constexpr int kOutNodes = 8192;   // task nodes of one outlier
 constexpr int kTaskNodes = 8;     // nodes per task
 constexpr int kTaskCap = kOutMax * (kOutNodes / kTaskNodes);
@@ -607,7 +613,10 @@ struct WideArgs {
   const int32_t *perm;
   float *acc, *pot;
   int out_min;           // smallest number of node tests that makes a group an outlier (0: never, see outlier_cap)
-  int32_t *out;          // [kOutMax] outlier groups
+  int32_t *out;          // [out_places] outlier groups
+  int out_places;
+  int out_first;         // those in hand: [out_first, out_first + kOutMax)
+  int out_limit;         // more than this many: an error (0: the host looks)
   OutInfo *outinfo;      // [kOutMax]
   int32_t *tnodes;       // [kOutMax][kOutNodes] task nodes
   int4 *tasks;           // [kTaskCap] group, first task node, nodes
@@ -619,6 +628,7 @@ int wide_block_length(int64_t n);  // of a tree of n particles
 bool wide_fits(int64_t n);         // whether the longest list of n particles fits the walk's block table
 void walk_wide_device(const WideArgs &a, int64_t n, int num_cu, hipStream_t s);
 void walk_outliers_device(const WideArgs &a, hipStream_t s);  // a.out over the large cells
+void next_outliers_device(DevInfo *info, bool again, hipStream_t s);  // counters, before the next of them (again: the same ones)
 void walk_tasks_device(const WideArgs &a, int num_cu, hipStream_t s);
 void force_blocks_device(const WideArgs &a, int num_cu, hipStream_t s);
 void block_reduce_device(const WideArgs &a, int num_cu, bool stats, hipStream_t s);  // members of ordinary groups

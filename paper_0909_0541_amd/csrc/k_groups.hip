@@ -168,6 +168,8 @@ __device__ __forceinline__ void reset_counters(DevInfo *info) {
   info->rows = 0;
   info->n_out = 0;
   info->tasks = 0;
+  info->tasks_done = 0;
+  info->blocks_done = 0;
   info->far_chunks = 0;
   info->near_chunks = 0;
   info->interactions = 0;

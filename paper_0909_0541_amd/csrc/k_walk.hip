@@ -471,11 +471,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) v
       ncur = node;
       if (bcur == 0 && sp == 0) break;
       // An outlier: its list so far is dropped and the workgroup walk takes
-      // the group (unless it has its share already: then walk on).
+      // the group (unless there is no place left: then walk on).
       if (!SPLIT && out_cap > 0 && visits >= out_cap) {
         int o = -1;
         if (lane == 0) {
-          o = take_outlier(a.info);
+          o = take_outlier(a.info, a.out_places);
           if (o >= 0) a.out[o] = g;
         }
         o = __builtin_amdgcn_readfirstlane(o);

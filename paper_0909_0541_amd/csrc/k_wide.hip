@@ -81,8 +81,10 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
   int run = 0;  // (thread 0) the run asked for
   int *queue = MODE == kUnitTasks ? &a.info->queue2 : &a.info->queue;
   const int units = MODE == kUnitGroups     ? G
-                    : MODE == kUnitOutliers ? min(a.info->n_out, kOutMax)
+                    : MODE == kUnitOutliers ? min(a.info->n_out - a.out_first, kOutMax)
                                             : min(a.info->tasks, kTaskCap);
+  if (MODE == kUnitOutliers && a.out_limit > 0 && a.info->n_out > a.out_limit && blockIdx.x == 0 && t == 0)
+    atomicOr(&a.info->err, kErrWide);
   int unit = blockIdx.x;  // the first unit by place, the next ones from the queue
   if (unit < units && t == 0) run = atomicAdd(&a.info->blocks, kSpare);
   while (unit < units) {
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
     if (t == 0 && gridDim.x < units) unext = atomicAdd(queue, 1);  // (read at the end of this unit)
     int g = unit, oidx = unit;
     int4 task = make_int4(0, 0, 0, 0);
-    if (MODE == kUnitOutliers) g = a.out[unit];
+    if (MODE == kUnitOutliers) g = a.out[a.out_first + unit];
     if (MODE == kUnitTasks) {
       task = a.tasks[unit];
       g = task.x;
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
         // an outlier: start again over the large cells
         cap = 0;
         if (t == 0) {
-          const int o = take_outlier(a.info);
+          const int o = take_outlier(a.info, kOutMax);
           if (o >= 0) a.out[o] = g;
           sh_id = o;
         }
@@ -551,6 +553,20 @@ __global__ __launch_bounds__(256) void k_block_reduce(WideArgs a, int width) {
   }
 }
 
+// Before the next outliers: their counters.  again: the same ones in a larger
+// pool.
+__global__ void k_next_outliers(DevInfo *info, bool again) {
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  info->queue = 0;
+  info->queue2 = 0;
+  info->blocks_done = max(info->blocks_done, info->blocks);
+  info->blocks = 0;
+  info->rows = 0;
+  if (again) info->err &= ~kErrPool;
+  else info->tasks_done += info->tasks;
+  info->tasks = 0;
+}
+
 // Outliers: 4 members per workgroup, 64 threads per member, each adding the
 // rows of a 64th of the tasks in order; the parts are added in order after the
 // group's own rows.  The first workgroup of an outlier also adds up its list
@@ -561,7 +577,7 @@ __global__ __launch_bounds__(256) void k_task_reduce(WideArgs a) {
   __shared__ double pm[256];
   __shared__ int4 pl[4];
   if (a.info->err & (kErrPool | kErrWide)) return;
-  const int nout = min(a.info->n_out, kOutMax);
+  const int nout = min(a.info->n_out - a.out_first, kOutMax);
   const int u = threadIdx.x & 3, sl = threadIdx.x >> 2;
   const int64_t step = 4 * (int64_t)a.n_crit;
   for (int o = blockIdx.y; o < nout; o += gridDim.y) {
@@ -681,6 +697,8 @@ void walk_wide_device(const WideArgs &a, int64_t n, int num_cu, hipStream_t s) {
 }
 
 void walk_outliers_device(const WideArgs &a, hipStream_t s) { launch_walk_wide<1024, kUnitOutliers>(a, kOutMax, s); }
+
+void next_outliers_device(DevInfo *info, bool again, hipStream_t s) { k_next_outliers<<<1, 64, 0, s>>>(info, again); }
 
 void walk_tasks_device(const WideArgs &a, int num_cu, hipStream_t s) {
   launch_walk_wide<256, kUnitTasks>(a, 5 * num_cu, s);
