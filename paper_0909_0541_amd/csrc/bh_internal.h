@@ -374,6 +374,7 @@ struct MomentArgs {
   int32_t *tiles;
   int32_t *subs, *pieces, *tops;  // roots of subtrees; of pieces (indices into tops); cells of pieces
   int32_t *highs, *highs2;        // cells above the pieces, and the same by level
+  int32_t *by_level, *level_count;  // all cells by level (large trees' second moments), [3][32] counts, cursors, ends
 };
 // Classes of cells by their particles and their parents' (k_moments.hip), and
 // flags: a bucket is owned here; this particle's parent is above the subtrees.

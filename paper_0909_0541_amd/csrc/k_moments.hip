@@ -281,6 +281,11 @@ __device__ __forceinline__ void store_moments(const MomentArgs &a, int slot, con
 // 510).
 constexpr int kSub = 512, kSubFew = 1024, kSubQuad = 256;
 constexpr int64_t kFewParticles = 16384;
+// Largest tree whose second moments are made with its subtrees: builds in us that
+// way and with launches by level, clustered boxes of 300k, 500k, 600k, 1M, 4M and
+// 8M particles 404, 497, 573, 849, 2421, 4375 and 436, 494, 551, 750, 1966, 3538,
+// uniform spheres of 300k, 500k and 600k 328, 394, 560 and 413, 469, 518.
+constexpr int64_t kQuadParticles = 1 << 19;
 
 // One workgroup per subtree; afterwards the particles whose parents are above
 // the subtrees.  A subtree of c particles at positions [f, f + c) owns its
@@ -293,10 +298,9 @@ constexpr int64_t kFewParticles = 16384;
 // before: the whole build of 8192, 100k, 1M and 4M particles 158, 270, 544 and
 // 1443 us; with this 78, 198, 481 and 1342 us.  Subtrees of 256 with second
 // moments: of 512 (one workgroup a compute unit) took 222 us.  They are bound by
-// the workgroups in flight: with moments in LDS for cells only, not leaves, and
-// five waves a SIMD the build of 300k, 1M and 4M particles takes 386, 800 and
-// 2416 us, with room for three workgroups 405, 873 and 2759 (launches by level:
-// 505, 759 and 1990).
+// the workgroups in flight, with moments in LDS for cells only, not leaves, and
+// five waves a SIMD (the build of 300k particles 386 us, with room for three
+// workgroups 405); larger trees take them level by level (k_second_moments).
 template <int SUB, bool QUAD>
 __global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 1))) void k_subtrees(MomentArgs a) {
   constexpr int LOCAL = 2 * SUB, ROOT = LOCAL - 1;
@@ -764,6 +768,126 @@ __global__ void k_empty_roots(const SysInfo *__restrict__ sys, int nsys, NodeRec
   for (int k = 0; k < 4; ++k) msum[4 * (int64_t)s + k] = 0.0;
 }
 
+// Second moments of large trees, in launches by level over the records that the
+// monopole passes have written: the cells listed by level (order within a level
+// does not matter), then from the deepest level up.  At 1M particles 20 us for the
+// list and 230 for the levels, 4 for each empty one and 20 for the fullest.
+constexpr int kLevels = kKeyLevels + 1, kLevelTile = 16;  // positions per thread
+
+// Lanes whose cells have this lane's level (l < 0: none), so that counters see
+// one atomic per wave and level.
+__device__ __forceinline__ unsigned long long level_peers(int l) {
+  unsigned long long peers = __ballot(l >= 0);
+#pragma unroll
+  for (int b = 0; b < 5; ++b) {
+    const unsigned long long m = __ballot(l >= 0 && ((l >> b) & 1));
+    peers &= ((l >> b) & 1) ? m : ~m;
+  }
+  return l >= 0 ? peers : 0ull;
+}
+
+__global__ __launch_bounds__(256) void k_level_count(MomentArgs a) {
+  __shared__ int32_t c[kLevels];
+  const int t = threadIdx.x;
+  if (t < kLevels) c[t] = 0;
+  __syncthreads();
+  const int64_t base = (int64_t)blockIdx.x * 256 * kLevelTile + t;
+#pragma unroll 4
+  for (int q = 0; q < kLevelTile; ++q) {
+    const int64_t j = base + 256 * q;
+    const int l = j < a.n ? a.level[j] : -1;
+    const unsigned long long peers = level_peers(l);
+    if (l >= 0 && rank_below(peers) == 0) atomicAdd(&c[l], (int)__popcll(peers));
+  }
+  __syncthreads();
+  if (t < kLevels && c[t]) atomicAdd(&a.level_count[t], c[t]);
+}
+
+// A level's places follow those of the levels above (the last one's end in
+// level_count[64 + level]).
+__global__ __launch_bounds__(256) void k_level_lists(MomentArgs a) {
+  __shared__ int32_t c[kLevels], base[kLevels];
+  const int t = threadIdx.x;
+  if (t < kLevels) c[t] = 0;
+  __syncthreads();
+  const int64_t b0 = (int64_t)blockIdx.x * 256 * kLevelTile + t;
+  int lev[kLevelTile], at[kLevelTile];
+#pragma unroll
+  for (int q = 0; q < kLevelTile; ++q) {
+    const int64_t j = b0 + 256 * q;
+    lev[q] = j < a.n ? a.level[j] : -1;
+    const unsigned long long peers = level_peers(lev[q]);
+    const int rank = rank_below(peers);
+    int first = 0;
+    if (lev[q] >= 0 && rank == 0) first = atomicAdd(&c[lev[q]], (int)__popcll(peers));
+    at[q] = __shfl(first, peers ? __ffsll((long long)peers) - 1 : 0, kWave) + rank;
+  }
+  __syncthreads();
+  if (t < kWave) {
+    const int count = t < kLevels ? a.level_count[t] : 0, end = wave_inclusive_sum(count);
+    if (t < kLevels) {
+      if (blockIdx.x == 0) a.level_count[64 + t] = end;
+      if (c[t]) base[t] = end - count + atomicAdd(&a.level_count[32 + t], c[t]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kLevelTile; ++q)
+    if (lev[q] >= 0) a.by_level[base[lev[q]] + at[q]] = (int32_t)(b0 + 256 * q);
+}
+
+// One cell per thread, a level's time the chain of its reads: its children's
+// records and moments (a particle's: never written, unused) are neighbours,
+// kMomChunk of them read together (indices clamped to the last).
+__global__ __launch_bounds__(256) void k_second_moments(MomentArgs a, int lev) {
+  const int end = a.level_count[64 + lev], first = end - a.level_count[lev];
+  for (int64_t k = first + (int64_t)blockIdx.x * 256 + threadIdx.x; k < end; k += (int64_t)gridDim.x * 256) {
+    const int j = a.by_level[k];
+    const int slot = a.cslot[j], c0 = a.nsys + a.cfc[j], nc = a.nchild[j];
+    if (bad_slot(a, slot)) continue;
+    if (c0 < 0 || nc < 1 || (int64_t)c0 + nc > a.cap) {
+      atomicOr(&a.info->err, kErrBuild);
+      continue;
+    }
+    const double com[3] = {a.nodes[slot].com[0], a.nodes[slot].com[1], a.nodes[slot].com[2]};
+    double M[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int cb = 0; cb < nc; cb += kMomChunk) {
+      double x[kMomChunk][3], m[kMomChunk], own[kMomChunk][6];
+      bool leaf[kMomChunk];
+#pragma unroll
+      for (int u = 0; u < kMomChunk; ++u) {
+        const int64_t at = c0 + min(cb + u, nc - 1);
+        const NodeRec &r = a.nodes[at];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) own[u][q] = a.qmom[6 * at + q];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[u][q] = r.com[q];
+        m[u] = r.m;
+        leaf[u] = r.child < 0;
+      }
+#pragma unroll
+      for (int u = 0; u < kMomChunk; ++u) {
+        if (cb + u >= nc || !(m[u] > 0.0)) continue;
+        // (a particle's centre of mass as from its raw sums, as in the other passes)
+        if (leaf[u])
+#pragma unroll
+          for (int q = 0; q < 3; ++q) x[u][q] = __dmul_rn(m[u], x[u][q]) / m[u];
+        shift_moments(M, com, m[u], x[u], leaf[u] ? nullptr : own[u]);
+      }
+    }
+    store_moments(a, slot, M);
+  }
+}
+
+void second_moments(const MomentArgs &a, hipStream_t s) {
+  const unsigned tiles = (unsigned)((a.n + 256 * kLevelTile - 1) / (256 * kLevelTile));
+  fill_i32(a.level_count, 0, 64, s);
+  k_level_count<<<tiles, 256, 0, s>>>(a);
+  k_level_lists<<<tiles, 256, 0, s>>>(a);
+  const unsigned grid = (unsigned)std::min<int64_t>((a.n + 255) / 256, 1024);
+  for (int lev = kKeyLevels; lev >= 0; --lev) k_second_moments<<<grid, 256, 0, s>>>(a, lev);
+}
+
 template <int SUB, bool QUAD>
 void launch(const MomentArgs &a, hipStream_t s) {
   // (a subtree holds 100 to 250 particles)
@@ -775,9 +899,13 @@ void launch(const MomentArgs &a, hipStream_t s) {
 
 }  // namespace
 
-int subtree_particles(int64_t n, bool quad) { return quad ? kSubQuad : (n <= kFewParticles ? kSubFew : kSub); }
+static bool quad_subtrees(int64_t n, bool quad) { return quad && n <= kQuadParticles; }
+
+int subtree_particles(int64_t n, bool quad) {
+  return quad_subtrees(n, quad) ? kSubQuad : (n <= kFewParticles ? kSubFew : kSub);
+}
 int piece_particles(int64_t n, bool quad) {
-  return subtree_particles(n, quad) * (quad ? Piece<true>::kFan : Piece<false>::kFan);
+  return subtree_particles(n, quad) * (quad_subtrees(n, quad) ? Piece<true>::kFan : Piece<false>::kFan);
 }
 
 void empty_roots_device(const TreeBuffers &B, hipStream_t s) {
@@ -817,6 +945,8 @@ void moments_device(const TreeBuffers &B, hipStream_t s) {
   a.tops = B.tops;
   a.highs = B.highs;
   a.highs2 = B.highs2;
+  a.by_level = reinterpret_cast<int32_t *>(B.vals[0]);  // (the sort is done with both)
+  a.level_count = reinterpret_cast<int32_t *>(B.hist);
   // The scan: one workgroup alone for up to 16384 particles; tiles of 16384
   // again where tiles of 4096 would be more than 4096.
   if (B.n <= 16 * 1024 || B.n > ((int64_t)1 << 24)) {
@@ -829,12 +959,13 @@ void moments_device(const TreeBuffers &B, hipStream_t s) {
     k_child_scan<256><<<nt, 256, 0, s>>>(a);
   }
   if (B.any_empty) empty_roots_device(B, s);
-  if (B.qmom)
+  if (quad_subtrees(B.n, B.qmom != nullptr))
     launch<kSubQuad, true>(a, s);
   else if (B.n <= kFewParticles)
     launch<kSubFew, false>(a, s);
   else
     launch<kSub, false>(a, s);
+  if (B.qmom && !quad_subtrees(B.n, true)) second_moments(a, s);
 }
 
 }  // namespace bh
