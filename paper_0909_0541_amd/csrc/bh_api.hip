@@ -211,7 +211,7 @@ static bh_status ensure_particles(bh_ctx *c, int64_t n, int nsys) {
   const size_t hist = radix_hist_bytes((int64_t)N);
   const size_t scan_elems = std::max<size_t>(N, hist / sizeof(uint32_t)) + 1;
   // (cells above the subtrees are disjoint on each level)
-  const size_t lists = 4 * (kKeyLevels + 1) * (N / (size_t)subtree_particles((int64_t)N, c->opt.quadrupole != 0) + 1);
+  const size_t lists = 4 * (kKeyLevels + 1) * (N / (size_t)subtree_particles((int64_t)N, c->opt.quadrupole != 0, INT32_MAX) + 1);
   struct Want {
     DevBuf *b;
     size_t bytes;
@@ -335,10 +335,11 @@ static bh_status build_common(bh_ctx *c, int32_t nsys, const int64_t *offsets, c
   B.slot_cap = (int64_t)std::min({c->nodes.bytes / sizeof(NodeRec), c->msum.bytes / 32, c->meta.bytes});
   B.curve = c->opt.curve;
   B.any_empty = false;
-  B.nonempty = 0;
+  B.nonempty = B.largest = 0;
   for (int s = 0; s < nsys; ++s) {
     B.any_empty |= c->sys_host[s].count == 0;
     B.nonempty += c->sys_host[s].count > 0;
+    B.largest = std::max(B.largest, (int)c->sys_host[s].count);
   }
   const bool quad = c->opt.quadrupole != 0;
   if (quad) {

@@ -347,6 +347,7 @@ struct TreeBuffers {
   int curve;              // key order: 0 Morton, 1 Peano-Hilbert
   bool any_empty;         // some system holds no particle (its root record is written apart)
   int nonempty;           // systems that hold particles
+  int largest;            // particles of the largest system
   uint8_t *kind;          // class of the owned cell in the moments pass, flags (kKind...)
   int32_t *tiles;         // tile sums of the child scan
   int32_t *subs, *pieces, *tops, *highs, *highs2;  // lists of the moments pass
@@ -358,7 +359,7 @@ void build_tree_device(TreeBuffers &B, hipStream_t s);
 // k_moments.hip: slots, node records and moments from the topology
 struct MomentArgs {
   int64_t n;
-  int nsys, nonempty;
+  int nsys, nonempty, largest;
   int64_t cap;  // capacity in slots
   const SysInfo *sys;
   const int8_t *level, *cdigit, *pdigit;
@@ -380,8 +381,9 @@ struct MomentArgs {
 // flags: a bucket is owned here; this particle's parent is above the subtrees.
 constexpr int kClassMask = 7, kClassSub = 1, kClassTop = 2, kClassPiece = 3, kClassHigh = 4;
 constexpr int kKindBucket = 8, kKindLone = 128;
-int subtree_particles(int64_t n, bool quad);  // most particles of a subtree
-int piece_particles(int64_t n, bool quad);    // and of a piece of the cells above
+// (largest: particles of the largest system; INT32_MAX: the least of any)
+int subtree_particles(int64_t n, bool quad, int largest);  // most particles of a subtree
+int piece_particles(int64_t n, bool quad, int largest);    // and of a piece of the cells above
 void moments_device(const TreeBuffers &B, hipStream_t s);
 void empty_roots_device(const TreeBuffers &B, hipStream_t s);
 

@@ -286,6 +286,13 @@ constexpr int64_t kFewParticles = 16384;
 // 8M particles 404, 497, 573, 849, 2421, 4375 and 436, 494, 551, 750, 1966, 3538,
 // uniform spheres of 300k, 500k and 600k 328, 394, 560 and 413, 469, 518.
 constexpr int64_t kQuadParticles = 1 << 19;
+// Batches of at least so many systems take their subtrees of up to 64 particles
+// by a wave each: a workgroup of 512 threads for each of 65,536 systems of 4 or 16
+// particles made the build 1619 and 1882 us (launches by level 1213 and 1434, now
+// 1140 and 1347; 256 systems of 4 139).  And systems of 513 to 1024 particles are
+// one subtree each, with nothing above: 4000 of 1000 1557 us, in subtrees of 512
+// 1828.
+constexpr int kManySystems = 256;
 
 // One workgroup per subtree; afterwards the particles whose parents are above
 // the subtrees.  A subtree of c particles at positions [f, f + c) owns its
@@ -301,8 +308,13 @@ constexpr int64_t kQuadParticles = 1 << 19;
 // the workgroups in flight, with moments in LDS for cells only, not leaves, and
 // five waves a SIMD (the build of 300k particles 386 us, with room for three
 // workgroups 405); larger trees take them level by level (k_second_moments).
+//
+// A launch takes the subtrees of more than `above` and at most SUB particles,
+// one of them (lone) those particles.
 template <int SUB, bool QUAD>
-__global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 1))) void k_subtrees(MomentArgs a) {
+__global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 1))) void k_subtrees(MomentArgs a,
+                                                                                                   int above,
+                                                                                                   bool lone) {
   constexpr int LOCAL = 2 * SUB, ROOT = LOCAL - 1;
   __shared__ double sm[LOCAL][4];
   __shared__ double qm[QUAD ? SUB : 1][6];   // of the cell owned at a position
@@ -314,7 +326,8 @@ __global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 
   const int nsub = a.info->n_subs;
   for (int i = blockIdx.x; i < nsub; i += gridDim.x) {
     const int r = a.subs[i];
-    const int f = a.cfirst[r], cnt = min(a.ccount[r], SUB);
+    const int f = a.cfirst[r], cnt = a.ccount[r];
+    if (cnt <= above || cnt > SUB) continue;
     const SysInfo &S = a.sys[system_of(a.sys, a.nsys, f)];
     const int j = f + t;
     if (t == 0) levels = 0;
@@ -455,6 +468,7 @@ __global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 
     if (t == 0 && all) note_level(a, 31 - __clz(all));
     __syncthreads();
   }
+  if (!lone) return;
   for (int64_t b = ((int64_t)blockIdx.x * SUB + t) * 16; b < a.n; b += (int64_t)gridDim.x * SUB * 16) {
     const uint4 kd = *reinterpret_cast<const uint4 *>(a.kind + b);
     const uint32_t w[4] = {kd.x, kd.y, kd.z, kd.w};
@@ -890,22 +904,29 @@ void second_moments(const MomentArgs &a, hipStream_t s) {
 
 template <int SUB, bool QUAD>
 void launch(const MomentArgs &a, hipStream_t s) {
-  // (a subtree holds 100 to 250 particles)
-  k_subtrees<SUB, QUAD><<<(unsigned)std::min<int64_t>((a.n + 127) / 128, 2048), SUB, 0, s>>>(a);
-  if (a.n > SUB)
+  // many systems: the smallest subtrees by a wave each
+  const int tiny = a.nonempty >= kManySystems ? kWave : 0;
+  const bool larger = a.largest > tiny;
+  if (tiny)
+    k_subtrees<kWave, QUAD><<<(unsigned)std::min(a.nonempty, 1 << 14), kWave, 0, s>>>(a, 0, !larger);
+  // (a subtree holds 100 to 250 particles, or a system)
+  const int64_t subs = std::max<int64_t>((a.n + 127) / 128, tiny ? 0 : a.nonempty);
+  if (larger) k_subtrees<SUB, QUAD><<<(unsigned)std::min<int64_t>(subs, 2048), SUB, 0, s>>>(a, tiny, true);
+  if (a.largest > SUB)
     k_top_cells<QUAD><<<(unsigned)std::min<int64_t>((a.n + 1023) / 1024, 1024), Piece<QUAD>::kThreads, 0, s>>>(a);
-  if (a.n > SUB * Piece<QUAD>::kFan) k_high_cells<QUAD><<<1, Piece<QUAD>::kThreads, 0, s>>>(a);
+  if (a.largest > SUB * Piece<QUAD>::kFan) k_high_cells<QUAD><<<1, Piece<QUAD>::kThreads, 0, s>>>(a);
 }
 
 }  // namespace
 
 static bool quad_subtrees(int64_t n, bool quad) { return quad && n <= kQuadParticles; }
 
-int subtree_particles(int64_t n, bool quad) {
-  return quad_subtrees(n, quad) ? kSubQuad : (n <= kFewParticles ? kSubFew : kSub);
+int subtree_particles(int64_t n, bool quad, int largest) {
+  if (quad_subtrees(n, quad)) return kSubQuad;
+  return n <= kFewParticles || (largest > kSub && largest <= kSubFew) ? kSubFew : kSub;
 }
-int piece_particles(int64_t n, bool quad) {
-  return subtree_particles(n, quad) * (quad_subtrees(n, quad) ? Piece<true>::kFan : Piece<false>::kFan);
+int piece_particles(int64_t n, bool quad, int largest) {
+  return subtree_particles(n, quad, largest) * (quad_subtrees(n, quad) ? Piece<true>::kFan : Piece<false>::kFan);
 }
 
 void empty_roots_device(const TreeBuffers &B, hipStream_t s) {
@@ -917,6 +938,7 @@ void moments_device(const TreeBuffers &B, hipStream_t s) {
   a.n = B.n;
   a.nsys = B.nsys;
   a.nonempty = B.nonempty;
+  a.largest = B.largest;
   a.cap = B.slot_cap;
   a.sys = B.sys;
   a.level = B.level;
@@ -961,7 +983,7 @@ void moments_device(const TreeBuffers &B, hipStream_t s) {
   if (B.any_empty) empty_roots_device(B, s);
   if (quad_subtrees(B.n, B.qmom != nullptr))
     launch<kSubQuad, true>(a, s);
-  else if (B.n <= kFewParticles)
+  else if (subtree_particles(B.n, B.qmom != nullptr, B.largest) == kSubFew)
     launch<kSubFew, false>(a, s);
   else
     launch<kSub, false>(a, s);

@@ -541,7 +541,8 @@ void build_tree_device(TreeBuffers &B, hipStream_t s) {
   k_owner<<<blocks_for(n), 256, 0, s>>>(keys, B.delta, n, B.sys, nsys, B.owner, B.level, B.cfirst, B.ccount);
   k_parents<<<blocks_for(n), 256, 0, s>>>(keys, B.delta, B.owner, B.level, n, B.sys, nsys, B.cfirst, B.ccount,
                                            B.cparent, B.cdigit, B.pparent, B.pdigit, B.mask,
-                                           subtree_particles(n, B.qmom != nullptr), piece_particles(n, B.qmom != nullptr), B.kind);
+                                           subtree_particles(n, B.qmom != nullptr, B.largest),
+                                           piece_particles(n, B.qmom != nullptr, B.largest), B.kind);
   moments_device(B, s);
 }
 
