@@ -33,6 +33,7 @@
 // Lattanzio with compact support h (the paper fixes no kernel).  Lists, when
 // asked for, hold the input indices of the neighbours in walk order.
 #include <algorithm>
+#include <type_traits>
 
 #include "bh_device.h"
 
@@ -42,7 +43,10 @@ namespace {
 
 constexpr int kNbStack = 512;                    // range stack entries
 constexpr int kNbReserve = 8 * 24;               // growth bound in one-range mode
-constexpr int kNbRun = 256;                      // particles of a cell that is not opened
+// Particles of a cell that is not opened (1M clustered particles in groups of 8,
+// 32 and 64, radii of the mean distance, us: 64 2472, 1019, 732; 128 2468, 983,
+// 712; 256 2706, 1052, 746; 512 3031, 1143, 790).
+constexpr int kNbRun = 128;
 // Particles of cells inside the radius that make an outlier: a sixteenth of
 // all, at least kNbOutMin.  (8192 for 1M clustered particles makes outliers of
 // a few hundred groups that end in time: 3.14 ms against 2.61.)
@@ -51,6 +55,12 @@ constexpr int kNbSlices = 64;                    // parts of an outlier's search
 constexpr int kNbSliceMin = 1024;                // of at least so many particles
 constexpr int kNbRows = 256 * kNbSlices;         // parts of all outliers
 constexpr int kNbCand = 128;                     // candidate buffer: 64 to test and 64 that a batch may add
+// Marks per candidate beyond which the members test the candidates one after
+// another instead (flush): with densities, and counts only.  30,000 clustered
+// particles with 1855 neighbours each in groups of 64, us: 1718 and 703, always in
+// rounds 5016 and 3237; a sphere of 1M, 209 neighbours: 1834 and 1217, with 10
+// and 4 here 1911 and 1239, with 20 and 12 1847 and 1252.
+constexpr int kDenseSum = 14, kDenseCount = 8;
 constexpr double kHalfSqrt3 = 0.86602540378443865;
 
 __device__ __forceinline__ void wave_sync() { __syncthreads(); }
@@ -162,6 +172,50 @@ __device__ __forceinline__ double run_sum(double v, int first, int lane) {
   return run_step<kDppRowBcast31>(v, lane >= 32 && first < 32);
 }
 
+// The candidates one after another, a member per lane (h2 = 0 and no index on a
+// lane without one), U at a time.  Where most pairs are neighbours: 13
+// instructions a candidate for the count and 40 with the density, whatever the
+// number of hits, against some 110 and 180 a round of 64 marked pairs.
+template <int U, bool RHO, bool LISTS>
+__device__ __forceinline__ void direct(const NeighborArgs &a, const Cand &cd, int nc, int i, double x0, double x1,
+                                       double x2, double h, double h2, double hi, double sigma, bool plain, int64_t row,
+                                       int64_t len, int &c, double &r) {
+  auto terms = [&](auto n, int k0) {
+    constexpr int N = decltype(n)::value;
+    CandRec q[N];
+    int j[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      q[u] = cd.c[k0 + u];
+      j[u] = cd.j[k0 + u];
+    }
+    double r2[N];
+    bool hit[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const double dx = __dsub_rn(q[u].x, x0), dy = __dsub_rn(q[u].y, x1), dz = __dsub_rn(q[u].z, x2);
+      r2[u] = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
+      hit[u] = r2[u] < h2 && j[u] != i;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      if (LISTS && hit[u] && c < len) a.nbr[row + c] = a.perm[j[u]];
+      c += hit[u] ? 1 : 0;
+    }
+    if (RHO) {
+      double W[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        W[u] = __dmul_rn(q[u].m, sigma * sph_shape(plain ? ratio(r2[u], h, hi) : sqrt(r2[u]) / h));
+#pragma unroll
+      for (int u = 0; u < N; ++u) r = __dadd_rn(r, hit[u] ? W[u] : 0.0);
+    }
+  };
+  int k = 0;
+  for (; k + U <= nc; k += U) terms(std::integral_constant<int, U>{}, k);
+  for (; k < nc; ++k) terms(std::integral_constant<int, 1>{}, k);
+}
+
 // Tests the first nc <= 64 staged candidates against every member block.
 //
 // About one pair in fifteen is a neighbour pair, in nearly every candidate
@@ -176,14 +230,15 @@ __device__ __forceinline__ double run_sum(double v, int first, int lane) {
 //   rounds the marked (member, candidate) pairs, counted member by member, are
 //          taken 64 at a time, one per lane whoever's member it is: the FP64
 //          decision (r2 < h2, the sum rounded as written), the density term,
-//          and the sum over each member's run of lanes.
+//          and the sum over each member's run of lanes.  Many marks: the
+//          candidates one after another (direct).
 // 1,048,576 clustered particles, 133 neighbours and 1874 tests a particle:
 // 5.9 ms testing and adding candidate by candidate, 5.3 ms with the pairs
 // listed in LDS and each member adding its terms one after another, 2.99 ms
 // in rounds, 2.84 ms without visiting the leaves (then bound by vector issue at
-// 87 %; runs of 24 and 64 particles 3.43 and 2.94), 2.52 ms with the scan on
-// the matrix units (before, nine vector instructions a candidate and wave).
-// Now 70 % vector issue, most of it the rounds, about 180 instructions each.
+// 87 %), 2.52 ms with the scan on the matrix units (before, nine vector
+// instructions a candidate and wave).  Now 70 % vector issue, most of it the
+// rounds, about 180 instructions each.
 template <int kNbBlocks>
 __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark, int nc, int gf, int gc, int nb, int lane,
                                       const float (&fb)[kNbBlocks][4], const float (&ft)[kNbBlocks][4],
@@ -233,6 +288,22 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark
       const double sigma = a.rho ? sph_sigma(h) : 0.0;
       int c = cb[b];
       double r = rb[b];
+      if (total > (a.rho ? kDenseSum : kDenseCount) * nc) {
+        constexpr int kU = 2, kUCount = kNbBlocks > 2 ? 2 : 4;  // (registers)
+        const int own = live ? i : -1;
+        const double h2 = live ? __dmul_rn(h, h) : 0.0;
+        if (a.nbr && a.rho)
+          direct<kU, true, true>(a, cd, nc, own, x0, x1, x2, h, h2, hi, sigma, plain, ob[b], lb[b], c, r);
+        else if (a.nbr)
+          direct<kUCount, false, true>(a, cd, nc, own, x0, x1, x2, h, h2, hi, sigma, plain, ob[b], lb[b], c, r);
+        else if (a.rho)
+          direct<kU, true, false>(a, cd, nc, own, x0, x1, x2, h, h2, hi, sigma, plain, ob[b], lb[b], c, r);
+        else
+          direct<kUCount, false, false>(a, cd, nc, own, x0, x1, x2, h, h2, hi, sigma, plain, ob[b], lb[b], c, r);
+        cb[b] = c;
+        rb[b] = r;
+        continue;
+      }
       for (int q0 = 0; q0 < total; q0 += kWave) {
         // this lane's own pairs of the round are on lanes [s, e)
         const int s = min(max(off - q0, 0), kWave), e = min(max(off + mine - q0, 0), kWave);
@@ -297,7 +368,7 @@ __device__ __forceinline__ int slices_per_outlier(int nout) {
 __device__ __forceinline__ int slices_of(int per, int count) { return max(1, min(per, count / kNbSliceMin)); }
 
 template <int kNbBlocks, bool RUNS, bool SLICES>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_neighbors(NeighborArgs a) {
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kNbBlocks == 1 ? 3 : 2))) void k_neighbors(NeighborArgs a) {
   __shared__ int2 stk[kNbStack];
   __shared__ Cand cd;
   __shared__ int mark[kWave];
