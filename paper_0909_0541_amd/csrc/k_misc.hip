@@ -14,8 +14,8 @@ constexpr int kJudgeU = 4;       // j particles whose terms are in flight togeth
 
 // 1 / sqrt(r2) in FP64: the hardware estimate y (about 2^-23 relative) and
 // one third-order step y (1 + e/2 + 3/8 e^2), e = 1 - r2 y^2 (the next term,
-// 5/16 e^3, is below 2^-68).  Its error is the final rounding and an eighth
-// of an ulp or so from e, where a square root and a division round twice.  Where the
+// 5/16 e^3, is about 2^-68 for e = 2^-22).  Its error is the final rounding and an
+// eighth of an ulp or so from e, where a square root and a division round twice.  Where the
 // estimate is zero or infinite (r2 infinite or 0) it is the result.
 __device__ __forceinline__ double rsqrt_d(double r2) {
   const double y = __builtin_amdgcn_rsq(r2);
@@ -224,9 +224,11 @@ hipError_t judge_scratch_address(int device, double **ptr) {
 size_t direct_part_bytes(int64_t n, int64_t s, int num_cu, int64_t *chunk, int64_t *nchunk) {
   // enough j chunks for 16 one-wave blocks per compute unit, four waves a SIMD
   // (4096 samples against 1,048,576: 3.63 ms, with half as many blocks 3.98),
-  // as far as the partial sums of a sample fit the static scratch
+  // as far as the partial sums of a sample fit the static scratch; half as many
+  // for few samples, whose partial sums a thread each adds in a row (64 samples
+  // against a million 597 us and with 16 1055, 512 533 and 548, 1000 932 and 881)
   const int64_t iblocks = (s + kJudgeI - 1) / kJudgeI;
-  int64_t want = (int64_t)num_cu * 16 / (iblocks > 0 ? iblocks : 1);
+  int64_t want = (int64_t)num_cu * (iblocks < 16 ? 8 : 16) / (iblocks > 0 ? iblocks : 1);
   want = std::min(want, (int64_t)(kJudgeScratchBytes / (4 * sizeof(double))) / (s > 0 ? s : 1));
   if (want < 1) want = 1;
   int64_t c = (n + want - 1) / want;
