@@ -533,16 +533,25 @@ bh_status bh_make_groups(bh_ctx *c, int32_t n_crit, int64_t *n_groups_out) {
   return BH_OK;
 }
 
-// The workgroup walk and list blocks (k_wide.hip) against the single-wave
-// walk and lists (k_walk.hip, k_force.hip): up to about 3000 groups, that is
-// 2048 n_crit particles, the former are faster, being even in their work;
-// beyond, the single waves fill the chip and read each list with scalar loads
-// (walk and sum, us, workgroups against waves: clustered box of 200,000
-// particles 637 against 884 at n_crit 64 and 561 against 881 at 256, of
-// 400,000 1132 against 1053 and 993 against 1211, of 700,000 1932 against 1348
-// and 1696 against 1889).  Every list takes at least one far and one near
-// block, so groups smaller than kWideMinCrit stay with the waves.
+// Sums by list tiles, and with quadrupoles the workgroup walk and list blocks
+// (k_wide.hip), against a wave per group (k_walk.hip, k_force.hip): up to about
+// 3000 groups, that is 2048 n_crit particles, the waves do not fill the chip and
+// the longest list decides.  Quadrupole steps in us, workgroups against waves:
+// clustered box of 300,000 particles at n_crit 256 1520 and 1690, of 500,000 2372
+// and 2527, of 100,000 at n_crit 64 697 and 1026.  Monopole force calls, time by
+// waves over time by tiles at theta 0.3 and 0.6 (sphere; clustered box; Plummer):
+//   n_crit 16, 32,000    1.20 1.28   1.25 1.28   1.29 1.19
+//   n_crit 64, 131,000   1.07 0.97   1.29 1.23   1.18 1.30
+//   n_crit 128, 262,000  0.99 0.94   1.28 1.35   1.00 1.04
+//   n_crit 256, 300,000  0.97 1.01   1.10 1.20   1.00 1.00
+//               350,000  0.87 0.95   0.97 1.14   0.94 0.96
+//               400,000  0.88 0.96   0.96 1.02   0.96 0.98
+//               500,000  0.97 0.91   0.90 1.04   0.91 0.90
+// The waves take blocks of 64 members, so beyond kTileParticles, some 6000
+// blocks, they are enough at any n_crit.  Every list takes at least one far and
+// one near block, so groups smaller than kWideMinCrit stay with the waves.
 constexpr int64_t kWideGroups = 2048;
+constexpr int64_t kTileParticles = 400000;
 constexpr int kWideMinCrit = 16;
 // Fewest node tests that make a group an outlier (see outlier_cap): a walk
 // this long is a small part of a launch (16 iterations of 256 threads, 256
@@ -584,7 +593,8 @@ constexpr int kOutBlock = 256;
 // on, rather than four times, by 7e-9).
 static bool few_groups(const bh_ctx *c) {
   return c->opt.split_visits == 0 && c->opt.list_tile == 0 && c->opt.waves_per_cu == 0 &&
-         c->n_crit >= kWideMinCrit && c->n <= kWideGroups * c->n_crit && wide_fits(c->n);
+         c->n_crit >= kWideMinCrit && c->n <= kWideGroups * c->n_crit &&
+         (c->opt.quadrupole || c->n <= kTileParticles) && wide_fits(c->n);
 }
 
 static size_t padded(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
