@@ -124,6 +124,7 @@ bh_status ensure(bh_ctx *c, DevBuf &b, size_t bytes, const char *what) {
   hipError_t e = hipMalloc(&b.p, want);
   if (e != hipSuccess) {
     b.p = nullptr;
+    (void)hipGetLastError();  // (reported here, not by the next launch's check)
     return fail(c, BH_ENOMEM, std::string("hipMalloc failed for ") + what);
   }
   b.bytes = want;
@@ -418,7 +419,7 @@ void bh_destroy(bh_ctx *c) {
                     &c->items, &c->pmass, &c->feps, &c->mlp_work, &c->mlp_feat, &c->pp_stat, &c->nb_out, &c->nb_count, &c->nb_rho, &c->order_hist, &c->walk_order, &c->walk_order_hist, &c->tasks, &c->ranges, &c->segs,
                     &c->split_ctr, &c->gsplit, &c->gnseg, &c->gsegfirst, &c->skeys[0], &c->skeys[1], &c->svals[0],
                     &c->svals[1], &c->shist, &c->sscan, &c->srows, &c->spbase, &c->sgroups, &c->psum,
-                    &c->tile_buf, &c->wide_buf, &c->out_list,
+                    &c->tile_buf, &c->wide_buf,
                     &c->qmom, &c->qpack, &c->far_slot};
   for (DevBuf *b : bufs) free_buf(*b);
   if (c->graph) (void)hipGraphExecDestroy(c->graph);
@@ -597,7 +598,14 @@ static bool few_groups(const bh_ctx *c) {
          (c->opt.quadrupole || c->n <= kTileParticles) && wide_fits(c->n);
 }
 
+// Outliers walked and summed together: 80 KiB of tables each.
+static int out_lot(const bh_ctx *c) { return c->nsys == 1 ? kOutSingle : kOutMax; }
+
 static size_t padded(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+
+// The outliers of the lists' walk (behind the queue order bins; not with the
+// tables, which may move between lots).
+static int32_t *out_list(const bh_ctx *c) { return (int32_t *)((char *)c->order_hist.p + padded(order_hist_bytes())); }
 
 // Arguments and buffers of the workgroup kernels (the pool holds c->wide_cap
 // blocks).  groups: the ordinary groups too, not only outliers.
@@ -605,6 +613,8 @@ static bh_status wide_args(bh_ctx *c, bool groups, const float *theta_group, flo
   const bool quad = c->opt.quadrupole != 0;
   const int block = c->wide_block;
   const size_t cap = (size_t)c->wide_cap;
+  A.lot = groups ? kOutMax : out_lot(c);
+  const size_t lot = (size_t)A.lot;
   // (one allocation: a dozen of them are a good part of a first call)
   struct {
     void **p;
@@ -615,24 +625,24 @@ static bh_status wide_args(bh_ctx *c, bool groups, const float *theta_group, flo
               {(void **)&A.gstat, groups ? sizeof(int2) * (size_t)c->n : 0},
               {(void **)&A.binfo, cap * sizeof(int4)},
               {(void **)&A.psum, cap * (size_t)c->n_crit * 4 * sizeof(double)},
-              {(void **)&A.outinfo, sizeof(OutInfo) * kOutMax},
-              {(void **)&A.tnodes, sizeof(int32_t) * (size_t)kOutMax * kOutNodes},
-              {(void **)&A.tasks, sizeof(int4) * (size_t)kTaskCap},
-              {(void **)&A.trows, sizeof(int4) * (size_t)kTaskCap},
-              {(void **)&A.tnear, sizeof(int32_t) * (size_t)kTaskCap},
-              {(void **)&A.tmass, sizeof(double) * (size_t)kTaskCap}};
+              {(void **)&A.out, groups ? sizeof(int32_t) * lot : 0},
+              {(void **)&A.outinfo, sizeof(OutInfo) * lot},
+              {(void **)&A.tnodes, sizeof(int32_t) * lot * kOutNodes},
+              {(void **)&A.tasks, sizeof(int4) * lot * kOutTasks},
+              {(void **)&A.trows, sizeof(int4) * lot * kOutTasks},
+              {(void **)&A.tnear, sizeof(int32_t) * lot * kOutTasks},
+              {(void **)&A.tmass, sizeof(double) * lot * kOutTasks}};
   size_t total = 0;
   for (auto &w : want) total += padded(w.bytes);
   bh_status st = ensure(c, c->wide_buf, total, "list blocks");
-  if (!st) st = ensure(c, c->out_list, sizeof(int32_t) * kOutPlaces, "outlier groups");
   if (st) return st;
-  A.out = P<int32_t>(c->out_list);
-  A.out_places = kOutPlaces;
   char *at = P<char>(c->wide_buf);
   for (auto &w : want) {
     *w.p = w.bytes ? at : nullptr;
     at += padded(w.bytes);
   }
+  if (!groups) A.out = out_list(c);
+  A.out_places = groups ? (int)lot : kOutPlaces;
   A.nodes = P<NodeRec>(c->nodes);
   A.sys = P<SysInfo>(c->sys);
   A.ginfo = P<int32_t>(c->ginfo);
@@ -664,6 +674,14 @@ static void wide_capacity(bh_ctx *c, int block, int64_t want) {
     c->wide_block = block;
   }
   if (!c->capturing && c->wide_cap < want) c->wide_cap = (int32_t)std::min<int64_t>(want, INT32_MAX / 2);
+}
+
+// List blocks of outliers to start from.  A captured step has to have room for
+// replays with a few: each workgroup on their tasks holds up to two runs.
+static int64_t out_blocks(const bh_ctx *c, bool few) {
+  const int64_t tasks = 8 * std::min<int64_t>(kOutTasks, c->n / kOutBlock + 1);
+  return 2 * c->n / kOutBlock + (few ? 512 : 4096) +
+         (c->reserve ? 2 * kSpare * std::min<int64_t>(kTaskGroups * c->num_cu, tasks) : 0);
 }
 
 // The walk's counters have arrived: rows of list blocks beyond their arrays.
@@ -733,11 +751,26 @@ static bh_status forces_wide(bh_ctx *c, const float *theta_group, float *acc, fl
   return BH_OK;
 }
 
-// The sums over the single waves' lists by tiles, and the outliers' (O).
+// Rows of partial sums of this tree's lists by their ordinary length (see
+// outlier_cap), times what earlier calls needed more than that: the pools'
+// capacities count chunks for any earlier tree.
+static int64_t tile_rows_room(const bh_ctx *c) {
+  double theta = 1.0;
+  for (const SysParam &p : c->par_host) theta = std::min(theta, p.theta);
+  const double octaves = std::max(1.0, log2((double)c->n / c->n_crit) / 3.0);
+  const double len = std::min((double)c->n, (60.0 + 25.0 * sqrt((double)c->n_crit)) * octaves / pow(std::max(theta, 1e-3), 1.5));
+  const double groups = (double)std::min<int64_t>(c->n, 3 * c->n / (2 * c->n_crit) + 1 + c->nsys);
+  const double rows = groups * (1.4 * len / kDefaultTile + 2.2) + 16.0;
+  return (int64_t)std::min(rows * c->tile_factor * (c->reserve ? 1.25 : 1.0), 1e9);
+}
+
+// The sums over the single waves' lists by tiles, and the outliers' (O); the
+// counters' read-back in between.
 static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &O, bool outliers, float *acc,
                               float *pot) {
   // (a tile takes a chunk of a pool: no more rows than chunks)
-  const size_t rows = (size_t)W.far_cap + (size_t)W.near_cap;
+  const size_t most = (size_t)W.far_cap + (size_t)W.near_cap;
+  const size_t rows = std::min(most, (size_t)tile_rows_room(c));
   const size_t b0 = padded(sizeof(double) * 4 * rows * (size_t)c->n_crit), b1 = padded(sizeof(int4) * rows);
   bh_status st = ensure(c, c->tile_buf, b0 + b1 + sizeof(int2) * (size_t)c->n, "list tiles");
   if (st) return st;
@@ -761,6 +794,7 @@ static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &
   T.psum = P<double>(c->tile_buf);
   T.tinfo = (int4 *)(P<char>(c->tile_buf) + b0);
   T.gblocks = (int2 *)(P<char>(c->tile_buf) + b0 + b1);
+  T.row_cap = (int)rows;
   WideArgs R{};
   R.ginfo = W.ginfo;
   R.info = W.info;
@@ -774,6 +808,13 @@ static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &
   R.pot = pot;
   st = timer_start(c, c->t_force);
   if (st) return st;
+  tile_rows_device(T, c->stream);
+  if (!c->capturing) {
+    st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
+                   "hipMemcpyAsync info");
+    if (!st) st = hip_check(c, hipEventRecord(c->info_event, c->stream), "hipEventRecord");
+    if (st) return st;
+  }
   force_tiles_device(T, c->num_cu, c->stream);
   block_reduce_device(R, c->num_cu, false, c->stream);
   if (outliers) {
@@ -787,8 +828,8 @@ static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &
   return st;
 }
 
-// The outliers of the lists' walk, kOutMax at a time from the `first` such
-// lot on, their sums after the lists' (which leave an outlier's members with
+// The outliers of the lists' walk, out_lot at a time from the `first` such lot
+// on, their sums after the lists' (which leave an outlier's members with
 // none).  *whole: one of their lists does not fit, every group has to be walked
 // whole.  A captured step records as many lots as its eager run's outliers and a
 // quarter more would fill.  (128 Plummer spheres of 20,000 particles, 272
@@ -796,18 +837,20 @@ static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &
 // they are more than 256, 4731 in lots.)
 static bh_status outlier_rounds(bh_ctx *c, const float *theta_group, float *acc, float *pot, int first, bool *whole) {
   *whole = false;
-  if (!c->capturing) {
-    const int n_out = std::min(c->info_host->n_out, kOutPlaces);
-    c->out_rounds = std::max((n_out + n_out / 4 + kOutMax - 1) / kOutMax, 1);
-  }
-  const int rounds = c->capturing ? c->out_rounds : (std::min(c->info_host->n_out, kOutPlaces) + kOutMax - 1) / kOutMax;
+  const int lot = out_lot(c), n_out = std::min(c->info_host->n_out, kOutPlaces);
+  if (!c->capturing) c->out_rounds = std::max((n_out + n_out / 4 + lot - 1) / lot, 1);
+  const int rounds = c->capturing ? c->out_rounds : (n_out + lot - 1) / lot;
   for (int r = first; r < rounds; ++r) {
     WideArgs A{};
     for (int attempt = 0;; ++attempt) {
       bh_status st = wide_args(c, false, theta_group, acc, pot, A);
+      if (st == BH_ENOMEM && !c->capturing) {  // whole, then: that needs no more memory
+        *whole = true;
+        return BH_OK;
+      }
       if (st) return st;
-      A.out_first = r * kOutMax;
-      A.out_limit = c->capturing ? c->out_rounds * kOutMax : 0;
+      A.out_first = r * lot;
+      A.out_limit = c->capturing ? c->out_rounds * lot : 0;
       if (r > 0 || attempt > 0) next_outliers_device(A.info, attempt > 0, c->stream);
       walk_outliers_device(A, c->stream);
       walk_tasks_device(A, c->num_cu, c->stream);
@@ -901,14 +944,18 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
       few ? kOutMinWide
           : (int)std::min<int64_t>(std::max(kOutMin, kOutMinShare * c->n / (c->num_cu * c->walk_bpc)), INT32_MAX);
   bool outliers = c->opt.split_visits == 0 && c->n <= kOutMaxN && (few ? c->n > kOutMinTree : 2 * c->n > out_min) && !c->out_off;
-  if (outliers) wide_capacity(c, kOutBlock, 2 * c->n / kOutBlock + (few ? 512 : 4096));
+  if (outliers) {
+    // (with a wave per group the host sees first whether there are any; a captured
+    // step's replays may have them)
+    if (few || c->reserve) wide_capacity(c, kOutBlock, out_blocks(c, few));
+  }
   if (c->seg_cap == 0) {
     c->task_cap = 4096;
     c->range_cap = 1 << 16;
     c->seg_cap = 4096;
   }
   if (!c->order_hist.p) {
-    st = ensure(c, c->order_hist, order_hist_bytes(), "queue order bins");
+    st = ensure(c, c->order_hist, padded(order_hist_bytes()) + sizeof(int32_t) * kOutPlaces, "queue order bins");
     if (st) return st;
     order_clear_device(P<int32_t>(c->order_hist), c->stream);  // every later call leaves it zero
   }
@@ -971,11 +1018,13 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     W.n_crit = c->n_crit;
     WideArgs A{};
     if (outliers) {
-      st = wide_args(c, false, theta_group, acc, pot, A);
-      if (st) return st;
-      W.out = A.out;
-      W.out_places = A.out_places;
-      A.out_limit = c->capturing ? c->out_rounds * kOutMax : 0;
+      W.out = out_list(c);
+      W.out_places = kOutPlaces;
+      if (few || c->reserve) {
+        st = wide_args(c, false, theta_group, acc, pot, A);
+        if (st) return st;
+        A.out_limit = c->capturing ? c->out_rounds * A.lot : 0;
+      }
     }
     W.order = (theta_group && c->walk_order_valid) ? P<int32_t>(c->walk_order) : nullptr;
     W.wait_ticks = c->wait_ticks;
@@ -998,17 +1047,8 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     // the pools must have held every list before the sums may run; a captured
     // step cannot wait here: an overflow then leaves kErrPool for bh_sync
     if (c->capturing && !few) break;
-    if (!c->capturing) {
-      st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
-                     "hipMemcpyAsync info");
-      if (st) return st;
-    }
     if (few) {
       // (queued behind the walk; they leave at once when a list did not fit)
-      if (!c->capturing) {
-        st = hip_check(c, hipEventRecord(c->info_event, c->stream), "hipEventRecord");
-        if (st) return st;
-      }
       st = forces_tiles(c, W, A, outliers, acc, pot);
       if (!st && c->capturing && outliers) st = outlier_rounds(c, theta_group, acc, pot, 1, &have_out);
       if (st || c->capturing) return st;
@@ -1022,6 +1062,10 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
         st = outlier_rounds(c, theta_group, acc, pot, 1, &whole);
         return whole ? forces_common(c, eps_sys, theta_sys, theta_group, acc, pot, true) : st;
       }
+    } else {
+      st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
+                     "hipMemcpyAsync info");
+      if (st) return st;
     }
     if (visit_cap > 0) {
       st = hip_check(c, hipMemcpyAsync(c->split_host, W.ctr, sizeof(SplitCounters), hipMemcpyDeviceToHost,
@@ -1041,6 +1085,13 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
       c->out_off = true;  // every group by one wave after all
       outliers = have_out = false;
       continue;
+    }
+    if (few && c->info_host->tile_need > 0) {  // (the lists fitted)
+      const double room = (double)tile_rows_room(c), need = (double)c->info_host->tile_need;
+      if (need > room) {
+        c->tile_factor *= 1.25 * need / std::max(room, 1.0);
+        continue;
+      }
     }
     wide_grow(c);
     const int64_t fneed = (int64_t)c->info_host->far_chunks * kChunkRun, nneed = (int64_t)c->info_host->near_chunks * kChunkRun;
@@ -1116,6 +1167,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   force_lists_device(F, fgrid, c->stream);
   if (have_out) {
     bool whole;
+    wide_capacity(c, kOutBlock, out_blocks(c, false));
     st = outlier_rounds(c, theta_group, acc, pot, 0, &whole);
     if (st) return st;
     if (whole) return forces_common(c, eps_sys, theta_sys, theta_group, acc, pot, true);
@@ -1217,10 +1269,10 @@ static bh_status step_common(bh_ctx *c, int32_t n_systems, const int64_t *offset
   return st;
 }
 
-static bh_status capture_common(bh_ctx *c, int32_t n_systems, const int64_t *offsets, const double *pos,
-                                const double *mass, int32_t n_crit, const double *eps_sys, const double *theta_sys,
-                                const float *theta_group, const bh_mlp *net, float shift, float *theta_out,
-                                float *acc, float *pot) {
+static bh_status capture_step(bh_ctx *c, int32_t n_systems, const int64_t *offsets, const double *pos,
+                              const double *mass, int32_t n_crit, const double *eps_sys, const double *theta_sys,
+                              const float *theta_group, const bh_mlp *net, float shift, float *theta_out, float *acc,
+                              float *pot) {
   if (n_systems < 1 || n_systems > 65536 || !offsets || !eps_sys || !theta_sys)
     return fail(c, BH_EINVAL, "bad graph capture arguments");
   if (offsets[0] != 0) return fail(c, BH_EINVAL, "offsets[0] must be 0");
@@ -1292,6 +1344,17 @@ static bh_status capture_common(bh_ctx *c, int32_t n_systems, const int64_t *off
   }
   c->capturing = false;
   c->stream = saved;
+  return st;
+}
+
+static bh_status capture_common(bh_ctx *c, int32_t n_systems, const int64_t *offsets, const double *pos,
+                                const double *mass, int32_t n_crit, const double *eps_sys, const double *theta_sys,
+                                const float *theta_group, const bh_mlp *net, float shift, float *theta_out,
+                                float *acc, float *pot) {
+  c->reserve = true;
+  const bh_status st = capture_step(c, n_systems, offsets, pos, mass, n_crit, eps_sys, theta_sys, theta_group, net,
+                                    shift, theta_out, acc, pot);
+  c->reserve = false;
   return st;
 }
 

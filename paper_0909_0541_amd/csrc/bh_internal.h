@@ -86,7 +86,8 @@ struct DevInfo {
   int32_t tasks;                // walk tasks of the outliers in hand
   int32_t tasks_done;           // of those before them
   int32_t blocks_done;          // most list blocks taken for those before them
-  int32_t tile_rows;            // tiles of the lists (k_tile_rows)
+  int32_t tile_rows;            // tiles of the lists (k_tile_rows; 0 when there is no room)
+  int32_t tile_need;            // and the room they take
   alignas(128) int32_t far_chunks;   // runs of kChunkRun list chunks taken (may exceed the pool: then it is the need)
   alignas(128) int32_t near_chunks;
   alignas(128) int32_t xq[8 * kLineInts];  // walk queue heads, one per XCD: xq[x * kLineInts]
@@ -196,7 +197,7 @@ struct bh_ctx {
   bool have_quad = false;  // the current tree carries second moments
   bool have_neighbors = false;  // a neighbour search ran since the last build
   bool out_off = false;    // the last force call found more outliers than places: every group walked whole
-  int out_rounds = 1;      // times kOutMax outliers of the last force call
+  int out_rounds = 1;      // lots of outliers of the last force call
   bool integrates = false; // a kick or drift ran on this context: its quadrupole sums keep the single-wave list order too
   bool capturing = false;         // recording a step into a HIP graph: no uploads, syncs or timers
   hipStream_t capture_stream = nullptr;
@@ -263,12 +264,13 @@ struct bh_ctx {
   bh::DevBuf mlp_feat;          // FP32 [n][12] features of bh_group_theta
   // lists in blocks (sizes at which a group is walked by a workgroup)
   bh::DevBuf wide_buf;  // list blocks, rows of partial sums, outliers' walk tasks
-  bh::DevBuf out_list;  // outlier groups
   bh::DevBuf tile_buf;  // sums by list tiles: partial sums, rows, rows of a group
   int32_t wide_cap = 0, wide_block = 0;  // blocks in the pool, entries per block
+  double tile_factor = 1.0;              // rows needed over those expected
+  bool reserve = false;                  // about to capture: buffers that replays may need too
   bool counters_clean = false;           // the force counters are known to be 0 (reset by make_groups, used by forces, replays)
   hipEvent_t info_event = nullptr;       // completion of a read-back of the counters
-  bh::DevBuf order_hist;        // int32 cost bins of the queue orders
+  bh::DevBuf order_hist;        // int32 cost bins of the queue orders; outlier groups
   bh::DevBuf walk_order;        // int32 [n] order in which the list walk takes the groups (learned theta)
   bh::DevBuf walk_order_hist;   // int32 cost bins of the walk order (zero between calls)
   // split walks: tasks (ping-pong), range pool, segments, counters, per-group
@@ -562,7 +564,9 @@ struct TileArgs {
   int2 *gblocks;  // per group: first row, rows
   int4 *tinfo;    // per row: group, tile, entries, near
   double *psum;   // [rows][n_crit][4]
+  int row_cap;    // room for rows
 };
+void tile_rows_device(const TileArgs &a, hipStream_t s);
 void force_tiles_device(const TileArgs &a, int num_cu, hipStream_t s);
 void force_lists_device(const ForceArgs &a, int grid, hipStream_t s);
 // The force items in queue order (k_order.hip), with the list statistics;
@@ -581,11 +585,14 @@ int force_lists_blocks_per_cu(bool quad);
 void reset_list_counters(DevInfo *info, hipStream_t s);
 
 // k_wide.hip: walk by workgroups, sums over list blocks
-constexpr int kOutMax = 256;      // outlier groups walked and summed together
+constexpr int kOutMax = 256;      // outlier groups walked and summed together, in a
+constexpr int kOutSingle = 64;    // single system (which has a few)
 constexpr int kOutPlaces = 1 << 16;  // outlier groups of a call, kOutMax at a time
 constexpr int kOutNodes = 8192;   // task nodes of one outlier
 constexpr int kTaskNodes = 8;     // nodes per task
-constexpr int kTaskCap = kOutMax * (kOutNodes / kTaskNodes);
+constexpr int kOutTasks = kOutNodes / kTaskNodes;  // and its tasks
+constexpr int kTaskGroups = 5;    // workgroups a compute unit that walk tasks
+constexpr int kSpare = 8;         // list blocks a workgroup takes from the pool at a time, one such run ahead
 struct OutInfo {
   int32_t g, task0, tasks;      // group, its tasks
   int32_t row0, rows, len;      // rows and entries of its own part of the list
@@ -618,14 +625,14 @@ struct WideArgs {
   int out_min;           // smallest number of node tests that makes a group an outlier (0: never, see outlier_cap)
   int32_t *out;          // [out_places] outlier groups
   int out_places;
-  int out_first;         // those in hand: [out_first, out_first + kOutMax)
+  int out_first, lot;    // those in hand: [out_first, out_first + lot)
   int out_limit;         // more than this many: an error (0: the host looks)
-  OutInfo *outinfo;      // [kOutMax]
-  int32_t *tnodes;       // [kOutMax][kOutNodes] task nodes
-  int4 *tasks;           // [kTaskCap] group, first task node, nodes
-  int4 *trows;           // [kTaskCap] first row, rows, entries, node tests
-  int32_t *tnear;        // [kTaskCap] near entries
-  double *tmass;         // [kTaskCap] list mass
+  OutInfo *outinfo;      // [lot]
+  int32_t *tnodes;       // [lot][kOutNodes] task nodes
+  int4 *tasks;           // [lot kOutTasks] group, first task node, nodes
+  int4 *trows;           // [lot kOutTasks] first row, rows, entries, node tests
+  int32_t *tnear;        // [lot kOutTasks] near entries
+  double *tmass;         // [lot kOutTasks] list mass
 };
 int wide_block_length(int64_t n);  // of a tree of n particles
 bool wide_fits(int64_t n);         // whether the longest list of n particles fits the walk's block table

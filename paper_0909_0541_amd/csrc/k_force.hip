@@ -280,12 +280,13 @@ __global__ __launch_bounds__(kWave) void k_force_lists(ForceArgs a, const float4
 
 // Rows of the tile sums: one per tile of each group's list (far tiles, then
 // near ones), numbered by groups; list statistics.  One workgroup; bound by
-// following the tiles' links (a dozen reads).
+// following the tiles' links (a dozen reads).  Rows beyond the room for them are
+// counted and not written.
 __global__ __launch_bounds__(1024) void k_tile_rows(TileArgs a) {
   __shared__ int wsum[1024 / kWave];
   const int t = threadIdx.x, w = t / kWave;
   if (a.info->err & (kErrPool | kErrWide)) {  // lists incomplete: the host walks again
-    if (t == 0) a.info->tile_rows = 0;
+    if (t == 0) a.info->tile_rows = a.info->tile_need = 0;
     return;
   }
   const int G = a.info->n_groups;
@@ -313,12 +314,12 @@ __global__ __launch_bounds__(1024) void k_tile_rows(TileArgs a) {
     __syncthreads();
     if (g < G) a.gblocks[g] = make_int2(row, rows);
     int ch = L.x;
-    for (int left = L.y; left > 0; left -= a.far_tile) {
+    for (int left = L.y; left > 0 && row < a.row_cap; left -= a.far_tile) {
       a.tinfo[row++] = make_int4(g, ch, min(left, a.far_tile), 0);
       if (left > a.far_tile) ch = a.far_next[ch];
     }
     ch = L.z;
-    for (int left = L.w; left > 0; left -= a.near_tile) {
+    for (int left = L.w; left > 0 && row < a.row_cap; left -= a.near_tile) {
       a.tinfo[row++] = make_int4(g, ch, min(left, a.near_tile), 1);
       if (left > a.near_tile) ch = a.near_next[ch];
     }
@@ -334,7 +335,12 @@ __global__ __launch_bounds__(1024) void k_tile_rows(TileArgs a) {
     atomicAdd(&a.info->list_entries, entries);
     atomicMax(&a.info->max_list, longest);
   }
-  if (t == 0) a.info->tile_rows = base;
+  if (t == 0) {
+    const bool fits = base <= a.row_cap;
+    if (!fits) atomicOr(&a.info->err, kErrPool);  // (the sums leave at once, the host makes room)
+    a.info->tile_rows = fits ? base : 0;
+    a.info->tile_need = base;
+  }
 }
 
 // The sums of k_force_lists taken apart by tiles: a workgroup per tile, a wave
@@ -434,9 +440,10 @@ __global__ __launch_bounds__(256) void k_force_tiles(TileArgs a) {
 
 }  // namespace
 
+void tile_rows_device(const TileArgs &a, hipStream_t s) { k_tile_rows<<<1, 1024, 0, s>>>(a); }
+
 void force_tiles_device(const TileArgs &a, int num_cu, hipStream_t s) {
   const int nt = a.n_crit <= 64 ? 64 : (a.n_crit <= 128 ? 128 : 256);
-  k_tile_rows<<<1, 1024, 0, s>>>(a);
   if (a.far_slot && a.qpack)
     k_force_tiles<true><<<(unsigned)(num_cu * 8), nt, 0, s>>>(a);
   else

@@ -41,7 +41,6 @@ namespace {
 
 constexpr int kWideReserve = 8 * 24;         // growth bound in one-node mode
 constexpr int kWideIds = 3 * 1024 + 64;      // block ids of one list (BL >= n / 1024: at most 3 n / BL + 2)
-constexpr int kSpare = 8;                    // blocks a workgroup takes from the pool at a time
 constexpr int kStage = 256;                  // entries staged in LDS at a time by the sum
 
 // One workgroup per unit: a group, an outlier group over its large cells
@@ -81,8 +80,8 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
   int run = 0;  // (thread 0) the run asked for
   int *queue = MODE == kUnitTasks ? &a.info->queue2 : &a.info->queue;
   const int units = MODE == kUnitGroups     ? G
-                    : MODE == kUnitOutliers ? min(a.info->n_out - a.out_first, kOutMax)
-                                            : min(a.info->tasks, kTaskCap);
+                    : MODE == kUnitOutliers ? min(a.info->n_out - a.out_first, a.lot)
+                                            : min(a.info->tasks, a.lot * kOutTasks);
   if (MODE == kUnitOutliers && a.out_limit > 0 && a.info->n_out > a.out_limit && blockIdx.x == 0 && t == 0)
     atomicOr(&a.info->err, kErrWide);
   int unit = blockIdx.x;  // the first unit by place, the next ones from the queue
@@ -294,7 +293,7 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
         // an outlier: start again over the large cells
         cap = 0;
         if (t == 0) {
-          const int o = take_outlier(a.info, kOutMax);
+          const int o = take_outlier(a.info, a.lot);
           if (o >= 0) a.out[o] = g;
           sh_id = o;
         }
@@ -369,7 +368,7 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
     if (MODE != kUnitTasks && top) {
       const int t0 = __builtin_amdgcn_readfirstlane(sh_g);
       for (int k = t; k < (tcount + kTaskNodes - 1) / kTaskNodes; k += NT)
-        if (t0 + k < kTaskCap)
+        if (t0 + k < a.lot * kOutTasks)
           a.tasks[t0 + k] = make_int4(g, oidx * kOutNodes + kTaskNodes * k, min(kTaskNodes, tcount - kTaskNodes * k), 0);
       __syncthreads();
     }
@@ -577,7 +576,7 @@ __global__ __launch_bounds__(256) void k_task_reduce(WideArgs a) {
   __shared__ double pm[256];
   __shared__ int4 pl[4];
   if (a.info->err & (kErrPool | kErrWide)) return;
-  const int nout = min(a.info->n_out - a.out_first, kOutMax);
+  const int nout = min(a.info->n_out - a.out_first, a.lot);
   const int u = threadIdx.x & 3, sl = threadIdx.x >> 2;
   const int64_t step = 4 * (int64_t)a.n_crit;
   for (int o = blockIdx.y; o < nout; o += gridDim.y) {
@@ -696,12 +695,12 @@ void walk_wide_device(const WideArgs &a, int64_t n, int num_cu, hipStream_t s) {
   }
 }
 
-void walk_outliers_device(const WideArgs &a, hipStream_t s) { launch_walk_wide<1024, kUnitOutliers>(a, kOutMax, s); }
+void walk_outliers_device(const WideArgs &a, hipStream_t s) { launch_walk_wide<1024, kUnitOutliers>(a, a.lot, s); }
 
 void next_outliers_device(DevInfo *info, bool again, hipStream_t s) { k_next_outliers<<<1, 64, 0, s>>>(info, again); }
 
 void walk_tasks_device(const WideArgs &a, int num_cu, hipStream_t s) {
-  launch_walk_wide<256, kUnitTasks>(a, 5 * num_cu, s);
+  launch_walk_wide<256, kUnitTasks>(a, kTaskGroups * num_cu, s);
 }
 
 void force_blocks_device(const WideArgs &a, int num_cu, hipStream_t s) {

@@ -1,6 +1,7 @@
-"""More outlier groups than are walked and summed together (256): they come in
-lots, eager and captured, at sizes summed by tiles and by a wave per group.
-Against the FP64 oracle system by system; repeats and replays bit for bit."""
+"""More outlier groups than are walked and summed together (256 in a batch, 64 in
+a single system): they come in lots, eager and captured, at sizes summed by tiles
+and by a wave per group.  Against the FP64 oracle system by system, or against
+whole walks; repeats and replays bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -19,7 +20,7 @@ def _batch(k, n):
     return one, to_dev(pos), to_dev(np.full(k * n, 1.0 / n)), np.arange(k + 1, dtype=np.int64) * n
 
 
-@pytest.mark.parametrize("k,n,n_crit,lots", [(100, 5000, 256, 2), (120, 30000, 256, 2)])
+@pytest.mark.parametrize("k,n,n_crit,lots", [(120, 30000, 256, 2)])
 def test_lots(gpu, k, n, n_crit, lots):
     bh = gpu
     one, pos, mass, off = _batch(k, n)
@@ -56,24 +57,60 @@ def test_lots(gpu, k, n, n_crit, lots):
         assert g.get_stats().n_split_groups == st.n_split_groups
 
 
-def test_replay_with_more_than_recorded(gpu):
-    """A step captured on systems without outliers and replayed on systems with
-    hundreds reports it; captured again, it has room."""
+def _spheres(k, n):
+    """Plummer spheres far apart in one system: the outskirts of each are
+    a few groups whose lists hold nearly all of it."""
+    pos = np.concatenate([inputs.plummer(n, s % 4, with_vel=False)[0] + [1e4 * (s % 5), 1e4 * (s // 5), 0.0]
+                          for s in range(k)])
+    return to_dev(pos), to_dev(np.full(k * n, 1.0 / n)), k * n
+
+
+@pytest.mark.parametrize("k,n,theta", [(39, 10000, 1.0), (70, 20000, 0.8)])
+def test_single_system(gpu, k, n, theta):
     bh = gpu
-    k, n = 100, 5000
-    _, pos, mass, off = _batch(k, n)
-    plain = to_dev(np.tile(inputs.uniform_cube(n, 1)[0], (k, 1)))
+    pos, mass, n = _spheres(k, n)
+    res = []
+    for opts in ({}, {"split_visits": -1}):
+        c = bh.Context(**opts)
+        c.build_tree(pos, mass)
+        c.make_groups(256)
+        a, p = (v.clone() for v in c.compute_forces(1e-2, theta))
+        b, q = c.compute_forces(1e-2, theta)
+        assert torch.equal(a, b) and torch.equal(p, q)
+        res.append((a, p, c.get_stats(), c.export_groups(lists=True)[2]))
+    (a, p, st, ll), (b, q, whole, ll_whole) = res
+    assert st.error_flags == 0 and 64 < st.n_split_groups <= 192 and whole.n_split_groups == 0
+    assert torch.equal(ll, ll_whole) and st.interactions == whole.interactions
+    # FP32 sums of the same entries in two orders
+    assert float(((a - b).norm(dim=1) / (b.norm(dim=1) + b.norm(dim=1).mean())).max()) <= 1e-5
+    assert float(((p - q).abs() / q.abs()).max()) <= 1e-5
+    g = bh.Context()
+    acc, pot = g.graph_capture([0, n], pos, mass, 256, 1e-2, theta)
+    for _ in range(3):
+        acc.zero_()
+        g.graph_launch()
+        g.sync()
+        assert torch.equal(acc, a) and torch.equal(pot, p)
+        assert g.get_stats().n_split_groups == st.n_split_groups
+
+
+def test_replay_with_more_than_recorded(gpu):
+    """A step captured on a system without outliers and replayed on one with
+    more than a lot reports it; captured again, it has room."""
+    bh = gpu
+    pos, mass, n = _spheres(39, 10000)
+    x = to_dev(inputs.uniform_cube(n, 1)[0])
     c = bh.Context()
-    c.graph_capture(off, plain, mass, 256, 1e-2, 0.8)
+    c.graph_capture([0, n], x, mass, 256, 1e-2, 1.0)
     assert c.get_stats().n_split_groups == 0
-    plain.copy_(pos)
+    x.copy_(pos)
     c.graph_launch()
     with pytest.raises(bh.BHError):
         c.sync()
-    acc, pot = c.graph_capture(off, plain, mass, 256, 1e-2, 0.8)
-    c.build_batch(off, pos, mass)
+    acc, pot = c.graph_capture([0, n], x, mass, 256, 1e-2, 1.0)
+    c.build_tree(pos, mass)
     c.make_groups(256)
-    a, p = c.compute_forces_batch([1e-2] * k, [0.8] * k)
+    a, p = c.compute_forces(1e-2, 1.0)
     acc.zero_()
     c.graph_launch()
     c.sync()
