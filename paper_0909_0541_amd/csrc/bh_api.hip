@@ -342,6 +342,7 @@ static bh_status build_common(bh_ctx *c, int32_t nsys, const int64_t *offsets, c
     B.nonempty += c->sys_host[s].count > 0;
     B.largest = std::max(B.largest, (int)c->sys_host[s].count);
   }
+  c->largest = B.largest;
   const bool quad = c->opt.quadrupole != 0;
   if (quad) {
     const size_t slots = (size_t)B.slot_cap;
@@ -556,10 +557,11 @@ constexpr int64_t kTileParticles = 400000;
 constexpr int kWideMinCrit = 16;
 // Fewest node tests that make a group an outlier (see outlier_cap): a walk
 // this long is a small part of a launch (16 iterations of 256 threads, 256
-// batches of a wave).  In trees of up to kOutMinTree particles the walk of
+// batches of a wave).  In systems of up to kOutMinTree particles the walk of
 // everything is over before tasks could be (walk of 5000, 8192 Plummer
 // particles at theta 0.75: 47, 77 us with one workgroup a group, 64, 64 us with
-// tasks).
+// tasks; batch of 78 spheres of 5000 at n_crit 256, forces: 1140 us with the 254
+// outliers apart, 848 with none, with quadrupoles 1474 and 1174).
 constexpr int kOutMinWide = 4096;
 constexpr int kOutMinTree = 6500;
 constexpr int64_t kOutMin = 16384;
@@ -708,8 +710,9 @@ static bh_status forces_wide(bh_ctx *c, const float *theta_group, float *acc, fl
     WideArgs A{};
     bh_status st = wide_args(c, true, theta_group, acc, pot, A);
     if (st) return st;
-    const bool outliers = n > kOutMinTree && !c->out_off;
+    const bool outliers = c->largest > kOutMinTree && !c->out_off;
     A.out_min = outliers ? kOutMinWide : 0;
+    A.out_tree = kOutMinTree;
     if (!c->counters_clean) reset_list_counters(P<DevInfo>(c->info), c->stream);
     c->counters_clean = false;
     st = timer_start(c, c->t_walk);
@@ -943,7 +946,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   const int out_min =
       few ? kOutMinWide
           : (int)std::min<int64_t>(std::max(kOutMin, kOutMinShare * c->n / (c->num_cu * c->walk_bpc)), INT32_MAX);
-  bool outliers = c->opt.split_visits == 0 && c->n <= kOutMaxN && (few ? c->n > kOutMinTree : 2 * c->n > out_min) && !c->out_off;
+  bool outliers = c->opt.split_visits == 0 && c->n <= kOutMaxN && (few ? c->largest > kOutMinTree : 2 * (int64_t)c->largest > out_min) && !c->out_off;
   if (outliers) {
     // (with a wave per group the host sees first whether there are any; a captured
     // step's replays may have them)
@@ -1015,6 +1018,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     W.gsplit = P<int32_t>(c->gsplit);
     W.visit_cap = visit_cap;
     W.out_min = outliers ? out_min : 0;
+    W.out_tree = few ? kOutMinTree : 0;
     W.n_crit = c->n_crit;
     WideArgs A{};
     if (outliers) {
@@ -1327,6 +1331,7 @@ static bh_status capture_step(bh_ctx *c, int32_t n_systems, const int64_t *offse
     Captured &k = c->captured;
     k.n = c->n;
     k.nsys = c->nsys;
+    k.largest = c->largest;
     k.n_crit = c->n_crit;
     k.quad = c->have_quad;
     k.learned = net != nullptr;
@@ -1397,6 +1402,7 @@ bh_status bh_graph_launch(bh_ctx *c) {
   if (st) return st;
   c->n = k.n;
   c->nsys = k.nsys;
+  c->largest = k.largest;
   c->n_crit = k.n_crit;
   c->have_tree = c->have_groups = c->have_forces = true;
   c->have_quad = k.quad;

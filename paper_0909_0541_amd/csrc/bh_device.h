@@ -90,9 +90,10 @@ __device__ __forceinline__ int64_t shfl_i64(int64_t v, int lane) {
 // number (mean lists of clustered boxes, Plummer and uniform spheres from
 // 30,000 to 4 million particles at theta 0.33 to 0.75 lie within 0.6 to 1.4
 // of that), and a walk tests 1.3 nodes an entry.  A function of the group
-// alone, so that the same groups are outliers in every run.
-__device__ __forceinline__ int outlier_cap(int out_min, int n_crit, int count, double theta) {
-  if (out_min <= 0 || !(theta > 0.0)) return 0;
+// alone, so that the same groups are outliers in every run.  Systems of up to
+// out_tree particles have none.
+__device__ __forceinline__ int outlier_cap(int out_min, int out_tree, int n_crit, int count, double theta) {
+  if (out_min <= 0 || count <= out_tree || !(theta > 0.0)) return 0;
   const float octaves = fmaxf(1.0f, log2f((float)count / (float)n_crit) * (1.0f / 3.0f));
   const float th = (float)theta;
   const float cap = 5.2f * (60.0f + 25.0f * sqrtf((float)n_crit)) * octaves / (th * sqrtf(th));

@@ -167,7 +167,7 @@ struct Timer {
 // and forces the context's, and reads the systems and parameters on the device.
 struct Captured {
   int64_t n = 0;
-  int32_t nsys = 0, n_crit = 0;
+  int32_t nsys = 0, largest = 0, n_crit = 0;
   bool quad = false, learned = false;
   uint64_t *sorted_keys = nullptr;
   std::vector<SysInfo> sys;
@@ -189,6 +189,7 @@ struct bh_ctx {
   // current tree
   int64_t n = 0;
   int32_t nsys = 0;
+  int32_t largest = 0;  // particles of the largest system
   bool have_tree = false;
   bool have_groups = false;
   bool xq_clean = false;  // the per-XCD group queues are known to be 0 (reset by make_groups, used by walks, replays)
@@ -439,6 +440,7 @@ struct WalkListArgs {
   long long wait_ticks;      // wall-clock ticks a wave may wait for a task
   int32_t *gsplit;           // per group: 1 when its list is in segments
   int out_min;               // smallest number of node tests that makes a group an outlier (0: never, see outlier_cap)
+  int out_tree;              // largest system without outliers
   int n_crit;
   int32_t *out;              // [out_places] outlier groups (info->n_out of them)
   int out_places;
@@ -623,6 +625,7 @@ struct WideArgs {
   const int32_t *perm;
   float *acc, *pot;
   int out_min;           // smallest number of node tests that makes a group an outlier (0: never, see outlier_cap)
+  int out_tree;              // largest system without outliers
   int32_t *out;          // [out_places] outlier groups
   int out_places;
   int out_first, lot;    // those in hand: [out_first, out_first + lot)

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     int cap = (SPLIT && visit_cap > 0 && key_depth(key) < kSplitDepth) ? visit_cap : 0;
     wave_sync();
     int visits = 0;
-    int out_cap = SPLIT ? 0 : __builtin_amdgcn_readfirstlane(outlier_cap(a.out_min, a.n_crit, a.sys[gs].count, theta));
+    int out_cap = SPLIT ? 0 : __builtin_amdgcn_readfirstlane(outlier_cap(a.out_min, a.out_tree, a.n_crit, a.sys[gs].count, theta));
     bool outlier = false;
     // Software pipeline: the records of the next batch are loaded while the
     // current batch is tested, so that one batch's memory latency hides

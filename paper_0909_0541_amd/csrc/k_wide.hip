@@ -131,7 +131,7 @@ __global__ __launch_bounds__(NT) void k_walk_wide(WideArgs a) {
 
     bool top = MODE == kUnitOutliers;
     const int small = max(a.sys[gs].count >> 11, 64);  // cells of at most this many particles become tasks
-    int cap = MODE == kUnitGroups ? outlier_cap(a.out_min, a.n_crit, a.sys[gs].count, theta) : 0;
+    int cap = MODE == kUnitGroups ? outlier_cap(a.out_min, a.out_tree, a.n_crit, a.sys[gs].count, theta) : 0;
     int tcount = 0;  // task nodes
     int sp = 1, nbig = 0;
     int fcount = 0, ncount = 0, fblocks = 0, nblocks = 0;
