@@ -79,11 +79,11 @@ typedef struct {
    * of the calls made since the previous bh_get_stats, and their number. */
   double t_build_ms;     /* bh_build_tree / bh_build_batch kernels */
   double t_groups_ms;    /* bh_make_groups kernels */
-  double t_walk_ms;      /* group walk kernel of the force calls (lists) */
-  double t_force_ms;     /* force-sum kernel of the force calls */
+  double t_walk_ms;      /* group walk kernels of the force calls (lists), outliers' and repeated walks too */
+  double t_force_ms;     /* force-sum kernels of the force calls */
   int32_t n_build_calls;
   int32_t n_groups_calls;
-  int32_t n_walk_calls;
+  int32_t n_walk_calls;  /* walks of all groups (more than force calls when a list pool had to grow) */
   int32_t n_force_calls;
   int32_t n_split_groups;  /* last force call: groups whose walk was shared by several waves or workgroups */
   int32_t n_segments;      /* last force call: list segments of those groups */
@@ -214,9 +214,11 @@ bh_status bh_make_groups(bh_ctx *ctx, int32_t n_crit, int64_t *n_groups_out);
  * the tree once with the FP64 opening test and writes its list to HBM as FP32
  * (x - c_g, m), c_g the group's box centre (entries close to the box also
  * keep the FP32 rounding residue); then members sum Eq. (1) over the list in
- * FP32, folding partial sums into FP64.  The call synchronises once, after
- * the walk, to check that the list pool held every list (the pool grows and
- * the walk is repeated when it did not). */
+ * FP32, folding partial sums into FP64.  The call synchronises after the walk, to
+ * check that the list pool held every list (the pool grows and the walk is
+ * repeated when it did not), and where the lists are summed by a wave per group
+ * once more for every 64 outlier groups (bh_options.split_visits; 256 in a
+ * batch). */
 bh_status bh_compute_forces(bh_ctx *ctx, double eps, double theta, const float *theta_group, float *acc,
                             float *pot);
 

@@ -142,7 +142,8 @@ static T *P(DevBuf &b) {
   return reinterpret_cast<T *>(b.p);
 }
 
-static bh_status timer_start(bh_ctx *c, Timer &t) {
+// more: further work of the same call.
+static bh_status timer_start(bh_ctx *c, Timer &t, bool more = false) {
   t.open = false;
   if (!c->opt.timing || c->capturing) return BH_OK;
   if (t.used >= 4096) return BH_OK;  // bounded: later calls of a long run are not timed
@@ -153,6 +154,7 @@ static bh_status timer_start(bh_ctx *c, Timer &t) {
     t.ev.push_back(e);
   }
   t.open = true;
+  t.more = more;
   return hip_check(c, hipEventRecord(t.ev[2 * t.used], c->stream), "hipEventRecord");
 }
 
@@ -160,7 +162,10 @@ static bh_status timer_stop(bh_ctx *c, Timer &t) {
   if (!t.open) return BH_OK;
   t.open = false;
   bh_status st = hip_check(c, hipEventRecord(t.ev[2 * t.used + 1], c->stream), "hipEventRecord");
-  if (st == BH_OK) t.used++;
+  if (st == BH_OK) {
+    t.used++;
+    t.calls += t.more ? 0 : 1;
+  }
   return st;
 }
 
@@ -171,8 +176,8 @@ static double timer_take(Timer &t, int32_t *calls) {
     float ms = 0.0f;
     if (hipEventElapsedTime(&ms, t.ev[2 * k], t.ev[2 * k + 1]) == hipSuccess) total += (double)ms;
   }
-  *calls = t.used;
-  t.used = 0;
+  *calls = t.calls;
+  t.used = t.calls = 0;
   return total;
 }
 
@@ -730,7 +735,7 @@ static bh_status forces_wide(bh_ctx *c, const float *theta_group, float *acc, fl
       if (!st) st = hip_check(c, hipEventRecord(c->info_event, c->stream), "hipEventRecord");
       if (st) return st;
     }
-    st = timer_start(c, c->t_force);
+    st = timer_start(c, c->t_force, attempt > 0);
     if (st) return st;
     force_blocks_device(A, c->num_cu, c->stream);
     block_reduce_device(A, c->num_cu, true, c->stream);
@@ -769,8 +774,8 @@ static int64_t tile_rows_room(const bh_ctx *c) {
 
 // The sums over the single waves' lists by tiles, and the outliers' (O); the
 // counters' read-back in between.
-static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &O, bool outliers, float *acc,
-                              float *pot) {
+static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &O, bool outliers, bool again,
+                              float *acc, float *pot) {
   // (a tile takes a chunk of a pool: no more rows than chunks)
   const size_t most = (size_t)W.far_cap + (size_t)W.near_cap;
   const size_t rows = std::min(most, (size_t)tile_rows_room(c));
@@ -809,7 +814,7 @@ static bh_status forces_tiles(bh_ctx *c, const WalkListArgs &W, const WideArgs &
   R.perm = P<int32_t>(c->perm);
   R.acc = acc;
   R.pot = pot;
-  st = timer_start(c, c->t_force);
+  st = timer_start(c, c->t_force, again);
   if (st) return st;
   tile_rows_device(T, c->stream);
   if (!c->capturing) {
@@ -854,9 +859,13 @@ static bh_status outlier_rounds(bh_ctx *c, const float *theta_group, float *acc,
       if (st) return st;
       A.out_first = r * lot;
       A.out_limit = c->capturing ? c->out_rounds * lot : 0;
+      st = timer_start(c, c->t_walk, true);
+      if (st) return st;
       if (r > 0 || attempt > 0) next_outliers_device(A.info, attempt > 0, c->stream);
       walk_outliers_device(A, c->stream);
       walk_tasks_device(A, c->num_cu, c->stream);
+      st = timer_stop(c, c->t_walk);
+      if (st) return st;
       if (c->capturing) break;
       st = hip_check(c, hipMemcpyAsync(c->info_host, c->info.p, sizeof(DevInfo), hipMemcpyDeviceToHost, c->stream),
                      "hipMemcpyAsync info");
@@ -871,8 +880,12 @@ static bh_status outlier_rounds(bh_ctx *c, const float *theta_group, float *acc,
       if (attempt > 5) return fail(c, BH_EINTERNAL, "interaction list pool still too small after growing");
       wide_grow(c);
     }
+    bh_status st = timer_start(c, c->t_force, true);
+    if (st) return st;
     force_blocks_device(A, c->num_cu, c->stream);
     task_reduce_device(A, c->stream);
+    st = timer_stop(c, c->t_force);
+    if (st) return st;
   }
   return hip_check(c, hipGetLastError(), "kernel launch (outliers)");
 }
@@ -1053,7 +1066,7 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     if (c->capturing && !few) break;
     if (few) {
       // (queued behind the walk; they leave at once when a list did not fit)
-      st = forces_tiles(c, W, A, outliers, acc, pot);
+      st = forces_tiles(c, W, A, outliers, attempt > 0 || walk_whole, acc, pot);
       if (!st && c->capturing && outliers) st = outlier_rounds(c, theta_group, acc, pot, 1, &have_out);
       if (st || c->capturing) return st;
       st = hip_check(c, hipEventSynchronize(c->info_event), "hipEventSynchronize");
@@ -1166,9 +1179,11 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
   F.psum = split ? P<double>(c->psum) : nullptr;
   item_order_device(F, P<int32_t>(c->gsplit), P<int32_t>(c->gnseg), (int64_t)gcap, P<int32_t>(c->order_hist),
                     P<int32_t>(c->items), c->stream);
-  st = timer_start(c, c->t_force);
+  st = timer_start(c, c->t_force, walk_whole);
   if (st) return st;
   force_lists_device(F, fgrid, c->stream);
+  st = timer_stop(c, c->t_force);
+  if (st) return st;
   if (have_out) {
     bool whole;
     wide_capacity(c, kOutBlock, out_blocks(c, false));
@@ -1176,8 +1191,6 @@ static bh_status forces_common(bh_ctx *c, const double *eps_sys, const double *t
     if (st) return st;
     if (whole) return forces_common(c, eps_sys, theta_sys, theta_group, acc, pot, true);
   }
-  st = timer_stop(c, c->t_force);
-  if (st) return st;
   if (split)
     split_reduce_device(S, P<int32_t>(c->ginfo), P<double>(c->smass), P<int32_t>(c->perm), P<SysParam>(c->par), acc,
                         pot, c->stream);

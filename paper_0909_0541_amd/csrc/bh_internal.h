@@ -160,7 +160,8 @@ struct DevBuf {
 struct Timer {
   std::vector<hipEvent_t> ev;  // pairs: ev[2k] start, ev[2k+1] stop
   int used = 0;                // pairs recorded since the last read
-  bool open = false;
+  int calls = 0;               // calls they belong to
+  bool open = false, more = false;
 };
 
 // What the host knows of the captured step: a replay makes its tree, groups
