@@ -260,7 +260,9 @@ bh_status bh_compute_forces_particle_batch(bh_ctx *ctx, const double *eps_sys, c
  * captures.  A replay reads pos and mass where they were at capture (update
  * them in place between replays) and writes acc and pot.  Sizes, offsets,
  * n_crit, eps and theta are those of the capture.  A replay cannot wait for
- * the list-pool check: if a list does not fit, bh_sync (or bh_get_stats)
+ * the list-pool check: if a list does not fit, or there are more outlier groups
+ * (bh_options.split_visits) than the captured step has room for, its own and a
+ * quarter more, at least 64 (256 in a batch), bh_sync (or bh_get_stats)
  * reports it and the replay's forces are invalid; capture again.  A later
  * call on the context that has to grow a buffer (a larger input, for one)
  * discards the capture.  Synchronises (the eager step). */

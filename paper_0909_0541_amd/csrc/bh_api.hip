@@ -268,7 +268,9 @@ static bh_status check_device_errors(bh_ctx *c) {
   if (e & kErrTheta) return fail(c, BH_EINVAL, "per-group theta outside [0, 1]");
   if (e & kErrBuild) return fail(c, BH_EINTERNAL, "tree build produced an inconsistent node layout");
   if (e & kErrStack) return fail(c, BH_EINTERNAL, "walk stack capacity exceeded or node range corrupt");
-  if (e & (kErrPool | kErrWide)) return fail(c, BH_EINTERNAL, "interaction list pool exhausted");
+  if (e & kErrWide)
+    return fail(c, BH_EINTERNAL, "more outlier groups, or longer lists of theirs, than the captured step has room for");
+  if (e & kErrPool) return fail(c, BH_EINTERNAL, "interaction list pool exhausted");
   if (e & kErrWait) return fail(c, BH_EINTERNAL, "a bounded device wait timed out (walk task or sort look-back)");
   if (e & kErrRadius) return fail(c, BH_EINVAL, "search radius h must be positive and finite");
   if (e & kErrListSpace) return fail(c, BH_EINVAL, "neighbour list offsets do not match the neighbour counts");

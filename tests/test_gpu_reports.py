@@ -50,3 +50,15 @@ def test_repeated_walks_are_one_force_call(gpu, quad, n, n_crit, theta):
         st = c.get_stats()
         assert st.error_flags == 0 and st.n_force_calls == 1
         assert st.n_walk_calls == st.n_walk_attempts and (st.n_walk_calls > 1) == first
+
+
+def test_replay_names_the_outliers(gpu):
+    bh = gpu
+    pos, mass, n = _spheres(39, 10000)
+    x = to_dev(inputs.uniform_cube(n, 1)[0])
+    c = bh.Context()
+    c.graph_capture([0, n], x, mass, 256, 1e-2, 1.0)
+    x.copy_(pos)
+    c.graph_launch()
+    with pytest.raises(bh.BHError, match="outlier groups"):
+        c.sync()
