@@ -216,9 +216,9 @@ bh_status bh_make_groups(bh_ctx *ctx, int32_t n_crit, int64_t *n_groups_out);
  * keep the FP32 rounding residue); then members sum Eq. (1) over the list in
  * FP32, folding partial sums into FP64.  The call synchronises after the walk, to
  * check that the list pool held every list (the pool grows and the walk is
- * repeated when it did not), and where the lists are summed by a wave per group
- * once more for every 64 outlier groups (bh_options.split_visits; 256 in a
- * batch). */
+ * repeated when it did not), and again for each lot of 256 outlier groups
+ * (bh_options.split_visits; 64 in a single system of up to 400,000 particles),
+ * but not for the first lot where there are too few groups for a wave each. */
 bh_status bh_compute_forces(bh_ctx *ctx, double eps, double theta, const float *theta_group, float *acc,
                             float *pot);
 
@@ -262,7 +262,8 @@ bh_status bh_compute_forces_particle_batch(bh_ctx *ctx, const double *eps_sys, c
  * n_crit, eps and theta are those of the capture.  A replay cannot wait for
  * the list-pool check: if a list does not fit, or there are more outlier groups
  * (bh_options.split_visits) than the captured step has room for, its own and a
- * quarter more, at least 64 (256 in a batch), bh_sync (or bh_get_stats)
+ * quarter more, at least as many as are summed together (64 or 256, as for
+ * bh_compute_forces), bh_sync (or bh_get_stats)
  * reports it and the replay's forces are invalid; capture again.  A later
  * call on the context that has to grow a buffer (a larger input, for one)
  * discards the capture.  Synchronises (the eager step). */

@@ -607,8 +607,11 @@ static bool few_groups(const bh_ctx *c) {
          (c->opt.quadrupole || c->n <= kTileParticles) && wide_fits(c->n);
 }
 
-// Outliers walked and summed together: 80 KiB of tables each.
-static int out_lot(const bh_ctx *c) { return c->nsys == 1 ? kOutSingle : kOutMax; }
+// Outliers walked and summed together: 80 KiB of tables each, and a lot costs
+// its launches and a wait (100 Plummer spheres of 14,000 particles far apart in
+// one system, n_crit 256, 259 outliers, forces: 2895 us by 64, 2621 by 256, 2410
+// with none apart; 40 of 40,000, 148 outliers: 2927, 2711, 5565).
+static int out_lot(const bh_ctx *c) { return c->nsys == 1 && c->n <= kTileParticles ? kOutSingle : kOutMax; }
 
 static size_t padded(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 

@@ -589,7 +589,7 @@ void reset_list_counters(DevInfo *info, hipStream_t s);
 
 // k_wide.hip: walk by workgroups, sums over list blocks
 constexpr int kOutMax = 256;      // outlier groups walked and summed together, in a
-constexpr int kOutSingle = 64;    // single system (which has a few)
+constexpr int kOutSingle = 64;    // single system summed by tiles (which has a few)
 constexpr int kOutPlaces = 1 << 16;  // outlier groups of a call, kOutMax at a time
 constexpr int kOutNodes = 8192;   // task nodes of one outlier
 constexpr int kTaskNodes = 8;     // nodes per task
