@@ -128,6 +128,7 @@ bh_status ensure(bh_ctx *c, DevBuf &b, size_t bytes, const char *what) {
     return fail(c, BH_ENOMEM, std::string("hipMalloc failed for ") + what);
   }
   b.bytes = want;
+  b.fresh = true;
   return BH_OK;
 }
 
@@ -517,9 +518,9 @@ bh_status bh_make_groups(bh_ctx *c, int32_t n_crit, int64_t *n_groups_out) {
   B.info = P<DevInfo>(c->info);
   B.glen = P<int32_t>(c->glen);
   B.tiles = P<int32_t>(c->tiles);
-  if (c->glen_zeroed != c->glen.bytes) {
+  if (c->glen.fresh) {
     fill_i32(B.glen, 0, (int64_t)(c->glen.bytes / sizeof(int32_t)), c->stream);
-    c->glen_zeroed = c->glen.bytes;
+    c->glen.fresh = false;
   }
   B.ginfo = P<int32_t>(c->ginfo);
   B.gbox = P<double>(c->gbox);

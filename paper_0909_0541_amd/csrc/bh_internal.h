@@ -154,6 +154,7 @@ struct SplitCounters {               // device
 struct DevBuf {
   void *p = nullptr;
   size_t bytes = 0;
+  bool fresh = false;  // allocated since its user last cleared this
 };
 
 // Event pairs recorded around one stage, summed when the stats are read.
@@ -241,7 +242,6 @@ struct bh_ctx {
   bh::DevBuf pieces, tops;      // int32 pieces of the cells above them, and those cells
   bh::DevBuf highs, highs2;     // int32 cells above the pieces, and the same by level
   bh::DevBuf glen;              // int32 group length at its start position, 0 between calls
-  size_t glen_zeroed = 0;       // bytes of it cleared once (its size unless it has grown since)
   bh::DevBuf ginfo;             // int32 [G][3] first, count, system
   bh::DevBuf gbox;              // FP64 [G][6]
   bh::DevBuf glist;             // int32 [G] list length of the last force call
