@@ -112,14 +112,17 @@ typedef struct {
                             by several waves; tasks 5 hand-overs deep walk to the end (>= 64,
                             exactly; -1: never).  0 (default): no hand-over by visits; groups
                             whose walk is several times an ordinary one's at their theta
-                            (outliers, a few per system) are walked and summed by many
+                            (outliers, a few per large system) are walked and summed by many
                             workgroups, and with the other tuning options at their defaults
-                            trees of up to 2048 n_crit particles (n_crit >= 16) have their lists
-                            summed by a workgroup per tile or, with quadrupoles, are walked and
-                            summed by a workgroup per group and list block.  Results do not
-                            depend on when or where a walk ran, only on the input and this
-                            option; up to FP32 rounding (the order in which a list is summed)
-                            not on the option either. */
+                            trees of up to 2048 n_crit particles (n_crit >= 16; without
+                            quadrupoles at most 400,000) have their lists summed by a workgroup
+                            per tile or, with quadrupoles, are walked and summed by a workgroup
+                            per group and list block (by tiles, in the order that one wave sums
+                            them in, from the first bh_kick, bh_drift or bh_leapfrog of a
+                            particle on the context on).  Results do not depend on when or where a walk
+                            ran, only on the input, the tuning options and, with quadrupoles,
+                            on whether the context integrates; up to FP32 rounding (the order
+                            in which a list is summed) on the input alone. */
   int32_t quadrupole;    /* 1: builds also compute every cell's second mass moments S about its
                             centre of mass (bottom-up, parallel axes, FP64), and bh_compute_forces
                             and bh_compute_forces_batch add to each cell entry of a list the

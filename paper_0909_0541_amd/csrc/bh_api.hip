@@ -1518,7 +1518,7 @@ bh_status bh_kick(bh_ctx *c, int64_t n, double *vel, const float *acc, double dt
   if (!c) return BH_EINVAL;
   c->err.clear();
   if (n < 0 || (n > 0 && (!vel || !acc))) return fail(c, BH_EINVAL, "bad kick arguments");
-  c->integrates = true;
+  c->integrates = c->integrates || n > 0;
   kick_device(n, vel, acc, dt, c->stream);
   return hip_check(c, hipGetLastError(), "kernel launch (kick)");
 }
@@ -1527,7 +1527,7 @@ bh_status bh_drift(bh_ctx *c, int64_t n, double *pos, const double *vel, double 
   if (!c) return BH_EINVAL;
   c->err.clear();
   if (n < 0 || (n > 0 && (!pos || !vel))) return fail(c, BH_EINVAL, "bad drift arguments");
-  c->integrates = true;
+  c->integrates = c->integrates || n > 0;
   drift_device(n, pos, vel, dt, c->stream);
   return hip_check(c, hipGetLastError(), "kernel launch (drift)");
 }
