@@ -70,11 +70,6 @@ __global__ void k_copy_i32(const int32_t *__restrict__ src, int32_t *__restrict_
   if (i < n) dst[i] = src[i];
 }
 
-__global__ void k_copy_f64(const double *__restrict__ src, double *__restrict__ dst, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[i];
-}
-
 __global__ void k_export_groups(const int32_t *__restrict__ ginfo, const double *__restrict__ gbox,
                                 const int32_t *__restrict__ glist, const double *__restrict__ gmass,
                                 const DevInfo *__restrict__ info, int32_t *ints, double *box, int32_t *ll,

@@ -201,15 +201,4 @@ __device__ __forceinline__ uint32_t quantise(double x, double lo, double scale) 
   return (uint32_t)u;  // truncation == floor for u >= 0
 }
 
-// Cell coordinates (21 bits per axis) of a Morton key.
-__device__ __forceinline__ void key_cells(uint64_t k, uint32_t q[3]) {
-  q[0] = q[1] = q[2] = 0;
-#pragma unroll 1
-  for (int b = 0; b < kKeyLevels; ++b) {
-    q[0] |= (uint32_t)((k >> (3 * b + 2)) & 1) << b;
-    q[1] |= (uint32_t)((k >> (3 * b + 1)) & 1) << b;
-    q[2] |= (uint32_t)((k >> (3 * b)) & 1) << b;
-  }
-}
-
 }  // namespace bh

@@ -79,7 +79,7 @@ struct DevInfo {
   unsigned long long near_entries;  // list entries the last walk wrote to near lists
   // Counters that every wave of a kernel updates, each in a 128-byte line of
   // its own (atomics on one line serialise behind each other).
-  alignas(128) int32_t queue2;  // force work queue head
+  alignas(128) int32_t queue2;  // head of the outliers' task queue
   alignas(128) int32_t blocks;  // list blocks taken by the workgroup walk (may exceed the pool: then it is the need)
   int32_t rows;                 // list blocks it used (rows of partial sums)
   int32_t n_out;                // outlier groups (more than there are places: an error, the host walks another way)
@@ -322,7 +322,6 @@ int radix_pass_by_system(uint64_t *k0, uint64_t *k1, uint32_t *v0, uint32_t *v1,
                          const int32_t *sys_in, int shift, uint32_t *hist, void *scan_tmp, hipStream_t s);
 
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
-void iota_u32(uint32_t *v, int64_t n, hipStream_t s);
 
 // k_tree.hip
 constexpr int kSmallMax = 16384;  // largest system sorted by counting (k_small_sort)
@@ -407,7 +406,6 @@ struct GroupBuffers {
   int num_cu;
 };
 void make_groups_device(GroupBuffers &B, hipStream_t s);
-void reset_force_counters(DevInfo *info, hipStream_t s);
 
 // k_walk.hip: group walk writing the interaction lists
 struct WalkListArgs {

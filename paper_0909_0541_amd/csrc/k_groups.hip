@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void k_group_box(const int32_t *__restrict__ g
   }
 }
 
-__global__ void k_reset_force_counters(DevInfo *info) {
+__global__ void k_reset_list_counters(DevInfo *info) {
   if (threadIdx.x == 0 && blockIdx.x == 0) reset_counters(info);
 }
 
@@ -262,7 +262,6 @@ void make_groups_device(GroupBuffers &B, hipStream_t s) {
   k_group_box<<<(unsigned)(B.num_cu * 8), 256, 0, s>>>(B.ginfo, B.spos, B.info, B.gbox);
 }
 
-void reset_force_counters(DevInfo *info, hipStream_t s) { k_reset_force_counters<<<1, 64, 0, s>>>(info); }
-void reset_list_counters(DevInfo *info, hipStream_t s) { k_reset_force_counters<<<1, 64, 0, s>>>(info); }
+void reset_list_counters(DevInfo *info, hipStream_t s) { k_reset_list_counters<<<1, 64, 0, s>>>(info); }
 
 }  // namespace bh

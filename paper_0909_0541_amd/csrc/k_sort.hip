@@ -30,13 +30,7 @@ constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kSortTile = kSortThreads * kSortChunks;
 constexpr int kRadix = 256;
 
-// Digit of a (key, value) pair: 8 bits of the key ...
-struct KeyDigit {
-  int bit;
-  __device__ __forceinline__ int of(uint64_t k, uint32_t) const { return (int)((k >> bit) & 255u); }
-};
-
-// ... or 8 bits of the system of the input row the value names.
+// Digit of a (key, value) pair: 8 bits of the system of the input row the value names.
 struct SysDigit {
   const int32_t *sys_in;
   int shift;
@@ -341,11 +335,6 @@ __global__ __launch_bounds__(kSortThreads) void k_onesweep(const uint64_t *__res
   }
 }
 
-__global__ void k_iota(uint32_t *v, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) v[i] = (uint32_t)i;
-}
-
 template <class Digit>
 void one_pass(const uint64_t *kin, const uint32_t *vin, uint64_t *kout, uint32_t *vout, int64_t n, Digit dig,
               uint32_t *hist, void *scan_tmp, hipStream_t s) {
@@ -385,11 +374,6 @@ static void key_pass(const uint64_t *kin, const uint32_t *vin, uint64_t *kout, u
   k_onesweep<CHUNKS><<<(unsigned)ntiles, kSortThreads, 0, s>>>(kin, vin, kout, vout, n, bit, pass, ntiles, state, err);
 }
 
-size_t radix_scan_elems(int64_t n) {
-  int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-  return (size_t)(ntiles * kRadix);
-}
-
 int radix_sort_pairs(uint64_t *k0, uint64_t *k1, uint32_t *v0, uint32_t *v1, int64_t n, int bit0, int bit1,
                      uint32_t *hist, void *scan_tmp, int32_t *err, hipStream_t s) {
   (void)scan_tmp;
@@ -417,10 +401,6 @@ int radix_pass_by_system(uint64_t *k0, uint64_t *k1, uint32_t *v0, uint32_t *v1,
   SysDigit dig{sys_in, shift};
   one_pass(k[cur], v[cur], k[cur ^ 1], v[cur ^ 1], n, dig, hist, scan_tmp, s);
   return cur ^ 1;
-}
-
-void iota_u32(uint32_t *v, int64_t n, hipStream_t s) {
-  if (n > 0) k_iota<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(v, n);
 }
 
 }  // namespace bh
