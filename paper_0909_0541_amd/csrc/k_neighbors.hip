@@ -237,8 +237,9 @@ __device__ __forceinline__ void direct(const NeighborArgs &a, const Cand &cd, in
 // listed in LDS and each member adding its terms one after another, 2.99 ms
 // in rounds, 2.84 ms without visiting the leaves (then bound by vector issue at
 // 87 %), 2.52 ms with the scan on the matrix units (before, nine vector
-// instructions a candidate and wave).  Now 70 % vector issue, most of it the
-// rounds, about 180 instructions each.
+// instructions a candidate and wave).  Now vector issue takes 69 % of the
+// cycles of a compute unit that has waves (three a SIMD), most of it the rounds,
+// about 180 instructions each.
 template <int kNbBlocks>
 __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark, int nc, int gf, int gc, int nb, int lane,
                                       const float (&fb)[kNbBlocks][4], const float (&ft)[kNbBlocks][4],

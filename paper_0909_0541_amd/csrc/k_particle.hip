@@ -17,8 +17,8 @@
 // particle, 64 / P nodes at a time.  Accepted nodes go to LDS with the mask of
 // the particles that take them and are summed from there, 64 / P at a time.
 //
-// Bound by vector issue (70 % of the cycles; half for terms, about 20
-// instructions each, half for tests and bookkeeping).  With one lane per walk
+// Bound by vector issue (81 % of the launch's cycles, sphere of 200,003; half for
+// terms, about 20 instructions each, half for tests and bookkeeping).  With one lane per walk
 // over a threaded tree, each visit waiting for its node's 64 bytes: sphere of
 // 200,003 particles 1411 us, with this 343; clustered box of 2M 46.4 and 5.1
 // ms.
