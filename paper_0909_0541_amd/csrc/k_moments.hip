@@ -309,9 +309,9 @@ constexpr int kManySystems = 256;
 // five waves a SIMD (the build of 300k particles 386 us, with room for three
 // workgroups 405); larger trees take them level by level (k_second_moments).
 //
-// A launch takes the subtrees of more than `above` and at most SUB particles,
-// one of them (lone) those particles.
-template <int SUB, bool QUAD>
+// With SPLIT a launch takes the subtrees of more than `above` and at most SUB
+// particles, one of them (lone) those particles.
+template <int SUB, bool QUAD, bool SPLIT>
 __global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 1))) void k_subtrees(MomentArgs a,
                                                                                                    int above,
                                                                                                    bool lone) {
@@ -326,8 +326,8 @@ __global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 
   const int nsub = a.info->n_subs;
   for (int i = blockIdx.x; i < nsub; i += gridDim.x) {
     const int r = a.subs[i];
-    const int f = a.cfirst[r], cnt = a.ccount[r];
-    if (cnt <= above || cnt > SUB) continue;
+    const int f = a.cfirst[r], cnt = SPLIT ? a.ccount[r] : min(a.ccount[r], SUB);
+    if (SPLIT && (cnt <= above || cnt > SUB)) continue;
     const SysInfo &S = a.sys[system_of(a.sys, a.nsys, f)];
     const int j = f + t;
     if (t == 0) levels = 0;
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(SUB) __attribute__((amdgpu_waves_per_eu(QUAD ? 5 : 
     if (t == 0 && all) note_level(a, 31 - __clz(all));
     __syncthreads();
   }
-  if (!lone) return;
+  if (SPLIT && !lone) return;
   for (int64_t b = ((int64_t)blockIdx.x * SUB + t) * 16; b < a.n; b += (int64_t)gridDim.x * SUB * 16) {
     const uint4 kd = *reinterpret_cast<const uint4 *>(a.kind + b);
     const uint32_t w[4] = {kd.x, kd.y, kd.z, kd.w};
@@ -908,10 +908,12 @@ void launch(const MomentArgs &a, hipStream_t s) {
   const int tiny = a.nonempty >= kManySystems ? kWave : 0;
   const bool larger = a.largest > tiny;
   if (tiny)
-    k_subtrees<kWave, QUAD><<<(unsigned)std::min(a.nonempty, 1 << 14), kWave, 0, s>>>(a, 0, !larger);
+    k_subtrees<kWave, QUAD, true><<<(unsigned)std::min(a.nonempty, 1 << 14), kWave, 0, s>>>(a, 0, !larger);
   // (a subtree holds 100 to 250 particles, or a system)
   const int64_t subs = std::max<int64_t>((a.n + 127) / 128, tiny ? 0 : a.nonempty);
-  if (larger) k_subtrees<SUB, QUAD><<<(unsigned)std::min<int64_t>(subs, 2048), SUB, 0, s>>>(a, tiny, true);
+  const unsigned grid = (unsigned)std::min<int64_t>(subs, 2048);
+  if (larger && tiny) k_subtrees<SUB, QUAD, true><<<grid, SUB, 0, s>>>(a, tiny, true);
+  if (!tiny) k_subtrees<SUB, QUAD, false><<<grid, SUB, 0, s>>>(a, 0, true);
   if (a.largest > SUB)
     k_top_cells<QUAD><<<(unsigned)std::min<int64_t>((a.n + 1023) / 1024, 1024), Piece<QUAD>::kThreads, 0, s>>>(a);
   if (a.largest > SUB * Piece<QUAD>::kFan) k_high_cells<QUAD><<<1, Piece<QUAD>::kThreads, 0, s>>>(a);
