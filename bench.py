@@ -57,13 +57,13 @@ HELDOUT_SEED = 54321            # a second judge sample, not used by any calibra
 # was taken on.
 TRAFFIC = {
     # clustered box, 4,194,304 particles, theta 0.3328125 (the 1e-3 RMS theta):
-    # FETCH_SIZE 5493643.8 KiB x 1.99986 (a 512 MiB device copy reads as
-    # 262162.06 KiB) + WRITE_SIZE 284494.7 KiB x 1.0 (the copy writes 524288 KiB)
-    "clustered_4m": {"theta": 0.3328125, "bytes_per_launch": 11541517506,
+    # FETCH_SIZE 5491322.9 KiB x 1.99986 (a 512 MiB device copy reads as
+    # 262162.06 KiB) + WRITE_SIZE 284525.4 KiB x 1.0 (the copy writes 524288 KiB)
+    "clustered_4m": {"theta": 0.3328125, "bytes_per_launch": 11536796073,
                      "k_force_sha256": "2fc5575c90f30892c16d579095380bf51558e0739e558dad6c85852d823274dc"},
     # clustered box, 2,097,152 particles, theta 0.41997070312499996:
-    # FETCH_SIZE 1654857.0 KiB x 1.99986 + WRITE_SIZE 146766.9 KiB x 1.0
-    "clustered_2m": {"theta": 0.41997070312499996, "bytes_per_launch": 3539199201,
+    # FETCH_SIZE 1658197.5 KiB x 1.99986 + WRITE_SIZE 146784.9 KiB x 1.0
+    "clustered_2m": {"theta": 0.41997070312499996, "bytes_per_launch": 3546058498,
                      "k_force_sha256": "2fc5575c90f30892c16d579095380bf51558e0739e558dad6c85852d823274dc"},
 }
 
