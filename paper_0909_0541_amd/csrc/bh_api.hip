@@ -1716,8 +1716,8 @@ bh_status bh_neighbors(bh_ctx *c, const double *h, int32_t *count, double *rho, 
   if ((offsets == nullptr) != (nbr == nullptr)) return fail(c, BH_EINVAL, "offsets and nbr go together");
   if (!count && !rho && !nbr) return fail(c, BH_EINVAL, "no output requested");
   c->have_neighbors = true;
-  const int variant = (c->n_crit <= 64 ? 0 : (c->n_crit <= 128 ? 1 : 2)) + (nbr ? 3 : 0);
-  if (!c->nb_bpc[variant]) c->nb_bpc[variant] = neighbors_blocks_per_cu(c->n_crit, nbr != nullptr);
+  const int variant = (c->n_crit <= 64 ? 0 : (c->n_crit <= 128 ? 1 : 2)) + (nbr ? 3 : 0) + (rho ? 6 : 0);
+  if (!c->nb_bpc[variant]) c->nb_bpc[variant] = neighbors_blocks_per_cu(c->n_crit, nbr != nullptr, rho != nullptr);
   const int grid = c->num_cu * (c->opt.waves_per_cu > 0 ? c->opt.waves_per_cu : c->nb_bpc[variant]);
   NeighborArgs A{};
   A.nodes = P<NodeRec>(c->nodes);

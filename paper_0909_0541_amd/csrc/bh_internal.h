@@ -186,7 +186,7 @@ struct bh_ctx {
   int num_cu = 0;
   std::string err;
   bh_options opt{0, 0, 0, 0, 0, 0};
-  int walk_bpc = 0, force_bpc = 0, force_bpc_q = 0, probe_bpc = 0, nb_bpc[6] = {};  // resident blocks per CU of the persistent kernels
+  int walk_bpc = 0, force_bpc = 0, force_bpc_q = 0, probe_bpc = 0, nb_bpc[12] = {};  // resident blocks per CU of the persistent kernels
 
   // current tree
   int64_t n = 0;
@@ -471,7 +471,7 @@ struct NeighborArgs {
 void neighbors_device(const NeighborArgs &a, int grid, hipStream_t s);
 int neighbors_out_min(int64_t n);  // out_min (INT32_MAX: so few particles have no outliers)
 size_t neighbors_parts(int n_crit);
-int neighbors_blocks_per_cu(int n_crit, bool lists);
+int neighbors_blocks_per_cu(int n_crit, bool lists, bool rho);
 // k_particle.hip: the per-particle walk and sum (no shared lists)
 void particle_forces_device(const NodeRec *nodes, int nsys, const SysInfo *sys, const SysParam *par,
                             const double *spos, const int32_t *perm, int64_t n, float *acc, float *pot, int4 *stat,

@@ -56,11 +56,15 @@ constexpr int kNbSliceMin = 1024;                // of at least so many particle
 constexpr int kNbRows = 256 * kNbSlices;         // parts of all outliers
 constexpr int kNbCand = 128;                     // candidate buffer: 64 to test and 64 that a batch may add
 // Marks per candidate beyond which the members test the candidates one after
-// another instead (flush): with densities, and counts only.  30,000 clustered
-// particles with 1855 neighbours each in groups of 64, us: 1718 and 703, always in
-// rounds 5016 and 3237; a sphere of 1M, 209 neighbours: 1834 and 1217, with 10
-// and 4 here 1911 and 1239, with 20 and 12 1847 and 1252.
-constexpr int kDenseSum = 14, kDenseCount = 8;
+// another instead (flush): with densities, counts only, and with lists, whose
+// rows the members then write at 64 places rather than run by run.  30,000
+// clustered particles with 1855 neighbours each in groups of 64, us: 1718 and 703,
+// always in rounds 5016 and 3237; a sphere of 1M, 209 neighbours: 1834 and 1217,
+// with 10 and 4 here 1911 and 1239, with 20 and 12 1847 and 1252.  Lists of 128,052
+// Plummer particles in groups of 128 (42 neighbours) and of 139,809 in groups of 32
+// (71), ms: always in rounds 23.2 and 35.5, from 14 on 26.3 and 29.1, 20 23.0 and
+// 29.3, 28 23.1 and 33.9.
+constexpr int kDenseSum = 14, kDenseCount = 8, kDenseList = 20;
 constexpr double kHalfSqrt3 = 0.86602540378443865;
 
 __device__ __forceinline__ void wave_sync() { __syncthreads(); }
@@ -240,7 +244,7 @@ __device__ __forceinline__ void direct(const NeighborArgs &a, const Cand &cd, in
 // instructions a candidate and wave).  Now vector issue takes 69 % of the
 // cycles of a compute unit that has waves (three a SIMD), most of it the rounds,
 // about 180 instructions each.
-template <int kNbBlocks>
+template <int kNbBlocks, bool RHO, bool LISTS>
 __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark, int nc, int gf, int gc, int nb, int lane,
                                       const float (&fb)[kNbBlocks][4], const float (&ft)[kNbBlocks][4],
                                       const double (&hb)[kNbBlocks], int (&cb)[kNbBlocks], double (&rb)[kNbBlocks],
@@ -286,21 +290,13 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark
         tests += nc;
       }
       const double h = hb[b], hi = 1.0 / h;
-      const double sigma = a.rho ? sph_sigma(h) : 0.0;
+      const double sigma = RHO ? sph_sigma(h) : 0.0;
       int c = cb[b];
       double r = rb[b];
-      if (total > (a.rho ? kDenseSum : kDenseCount) * nc) {
-        constexpr int kU = 2, kUCount = kNbBlocks > 2 ? 2 : 4;  // (registers)
-        const int own = live ? i : -1;
-        const double h2 = live ? __dmul_rn(h, h) : 0.0;
-        if (a.nbr && a.rho)
-          direct<kU, true, true>(a, cd, nc, own, x0, x1, x2, h, h2, hi, sigma, plain, ob[b], lb[b], c, r);
-        else if (a.nbr)
-          direct<kUCount, false, true>(a, cd, nc, own, x0, x1, x2, h, h2, hi, sigma, plain, ob[b], lb[b], c, r);
-        else if (a.rho)
-          direct<kU, true, false>(a, cd, nc, own, x0, x1, x2, h, h2, hi, sigma, plain, ob[b], lb[b], c, r);
-        else
-          direct<kUCount, false, false>(a, cd, nc, own, x0, x1, x2, h, h2, hi, sigma, plain, ob[b], lb[b], c, r);
+      if (total > (LISTS ? kDenseList : RHO ? kDenseSum : kDenseCount) * nc) {
+        constexpr int kU = RHO || kNbBlocks > 2 ? 2 : 4;  // (registers)
+        direct<kU, RHO, LISTS>(a, cd, nc, live ? i : -1, x0, x1, x2, h, live ? __dmul_rn(h, h) : 0.0, hi, sigma, plain,
+                               ob[b], lb[b], c, r);
         cb[b] = c;
         rb[b] = r;
         continue;
@@ -327,14 +323,14 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark
         const double hu = shfl_d(h, u);
         const bool hit = have && j != gf + b * kWave + u && r2 < __dmul_rn(hu, hu);
         const unsigned long long hits = __ballot(hit);
-        if (a.nbr) {
+        if (LISTS) {
           // place in the member's row: the hits of its earlier pairs
           const unsigned long long before = ((1ull << lane) - 1ull) & ~((1ull << max(uoff, 0)) - 1ull);
           const int n0 = __shfl(c, u, kWave) + (int)__popcll(hits & before);
           const int64_t row = shfl_i64(ob[b], u), len = shfl_i64(lb[b], u);
           if (hit && n0 < len) a.nbr[row + n0] = a.perm[j];
         }
-        if (a.rho) {
+        if (RHO) {
           double x = 0.0;
           if (plain) x = ratio(r2, hu, shfl_d(hi, u));
           else x = sqrt(r2) / hu;
@@ -362,13 +358,15 @@ __device__ __forceinline__ void flush(const NeighborArgs &a, Cand &cd, int *mark
 // candidates are the same in another order.  Without (calls that ask for
 // lists, whose order is the walk's) every leaf's 64-byte record is visited.
 //
-// SLICES: the launch for outliers, over the parts of info->nb_out groups.
+// SLICES: the launch for outliers, over the parts of info->nb_out groups.  RHO:
+// densities too.  (With densities and lists chosen at run time a wave holds 10 to
+// 60 registers more, and calls without dense blocks take 2 to 8 % longer.)
 __device__ __forceinline__ int slices_per_outlier(int nout) {
   return nout <= kNbRows / kNbSlices ? kNbSlices : max(1, kNbRows / nout);
 }
 __device__ __forceinline__ int slices_of(int per, int count) { return max(1, min(per, count / kNbSliceMin)); }
 
-template <int kNbBlocks, bool RUNS, bool SLICES>
+template <int kNbBlocks, bool RUNS, bool SLICES, bool RHO>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kNbBlocks == 1 ? 3 : 2))) void k_neighbors(NeighborArgs a) {
   __shared__ int2 stk[kNbStack];
   __shared__ Cand cd;
@@ -420,7 +418,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kNbBlocks
       rb[b] = 0.0;
       ob[b] = 0;
       lb[b] = 0;
-      if (live && a.offsets) {
+      if (!RUNS && live) {
         ob[b] = a.offsets[o];
         lb[b] = a.offsets[o + 1] - ob[b];
       }
@@ -630,7 +628,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kNbBlocks
       ncand += nc;
       wave_sync();
       if (ncand >= kWave) {
-        flush<kNbBlocks>(a, cd, mark, kWave, gf, gc, nb, lane, fb, ft, hb, cb, rb, ob, lb, plain, tests);
+        flush<kNbBlocks, RHO, !RUNS>(a, cd, mark, kWave, gf, gc, nb, lane, fb, ft, hb, cb, rb, ob, lb, plain, tests);
         // the rest (at most 64) move to the front
         ncand -= kWave;
         wave_sync();
@@ -647,7 +645,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kNbBlocks
       wave_sync();
       continue;
     }
-    flush<kNbBlocks>(a, cd, mark, ncand, gf, gc, nb, lane, fb, ft, hb, cb, rb, ob, lb, plain, tests);
+    flush<kNbBlocks, RHO, !RUNS>(a, cd, mark, ncand, gf, gc, nb, lane, fb, ft, hb, cb, rb, ob, lb, plain, tests);
     all_tests += (unsigned long long)tests;
     wave_sync();
     if (SLICES && parts > 1) {
@@ -671,8 +669,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kNbBlocks
       if (b < nb && i < gf + gc) {
         const int o = a.perm[i];
         if (a.count) a.count[o] = cb[b];
-        if (a.rho) a.rho[o] = __dadd_rn(__dmul_rn(a.smass[i], sph_sigma(hb[b])), rb[b]);
-        if (a.offsets && (int64_t)cb[b] != lb[b]) short_list = true;
+        if (RHO) a.rho[o] = __dadd_rn(__dmul_rn(a.smass[i], sph_sigma(hb[b])), rb[b]);
+        if (!RUNS && (int64_t)cb[b] != lb[b]) short_list = true;
         pairs += (unsigned long long)cb[b];
       }
     }
@@ -713,29 +711,32 @@ __global__ __launch_bounds__(256) void k_nb_parts(NeighborArgs a) {
 
 }  // namespace
 
+template <bool RUNS, bool SLICES, bool RHO>
+static auto kernel(int n_crit) {
+  return n_crit <= kWave ? k_neighbors<1, RUNS, SLICES, RHO>
+                         : (n_crit <= 2 * kWave ? k_neighbors<2, RUNS, SLICES, RHO>
+                                                : k_neighbors<BH_MAX_NCRIT / kWave, RUNS, SLICES, RHO>);
+}
 template <bool RUNS, bool SLICES>
-static int blocks_per_cu(int n_crit) {
-  int b = 0;
-  hipError_t e;
-  if (n_crit <= kWave) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<1, RUNS, SLICES>, kWave, 0);
-  else if (n_crit <= 2 * kWave)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<2, RUNS, SLICES>, kWave, 0);
-  else
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_neighbors<BH_MAX_NCRIT / kWave, RUNS, SLICES>, kWave, 0);
-  if (e != hipSuccess || b < 1) b = 8;
-  return b;
+static auto kernel(int n_crit, bool rho) {
+  return rho ? kernel<RUNS, SLICES, true>(n_crit) : kernel<RUNS, SLICES, false>(n_crit);
 }
 
-int neighbors_blocks_per_cu(int n_crit, bool lists) {
-  return lists ? blocks_per_cu<false, false>(n_crit)
-               : std::min(blocks_per_cu<true, false>(n_crit), blocks_per_cu<true, true>(n_crit));
+template <bool RUNS, bool SLICES>
+static int blocks_per_cu(int n_crit, bool rho) {
+  int b = 0;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel<RUNS, SLICES>(n_crit, rho), kWave, 0);
+  return e != hipSuccess || b < 1 ? 8 : b;
+}
+
+int neighbors_blocks_per_cu(int n_crit, bool lists, bool rho) {
+  return lists ? blocks_per_cu<false, false>(n_crit, rho)
+               : std::min(blocks_per_cu<true, false>(n_crit, rho), blocks_per_cu<true, true>(n_crit, rho));
 }
 
 template <bool RUNS, bool SLICES>
 static void launch(const NeighborArgs &a, int grid, hipStream_t s) {
-  if (a.n_crit <= kWave) k_neighbors<1, RUNS, SLICES><<<(unsigned)grid, kWave, 0, s>>>(a);
-  else if (a.n_crit <= 2 * kWave) k_neighbors<2, RUNS, SLICES><<<(unsigned)grid, kWave, 0, s>>>(a);
-  else k_neighbors<BH_MAX_NCRIT / kWave, RUNS, SLICES><<<(unsigned)grid, kWave, 0, s>>>(a);
+  kernel<RUNS, SLICES>(a.n_crit, a.rho != nullptr)<<<(unsigned)grid, kWave, 0, s>>>(a);
 }
 
 int neighbors_out_min(int64_t n) {
