@@ -266,8 +266,8 @@ bh_status bh_compute_forces_particle_batch(bh_ctx *ctx, const double *eps_sys, c
  * the list-pool check: if a list does not fit, or there are more outlier groups
  * (bh_options.split_visits) than the captured step has room for, its own and a
  * quarter more, at least as many as are summed together (64 or 256, as for
- * bh_compute_forces), bh_sync (or bh_get_stats)
- * reports it and the replay's forces are invalid; capture again.  A later
+ * bh_compute_forces), bh_sync (or bh_get_stats) reports it and the replay's
+ * forces are invalid; capture again.  A later
  * call on the context that has to grow a buffer (a larger input, for one)
  * discards the capture.  Synchronises (the eager step). */
 bh_status bh_graph_capture(bh_ctx *ctx, int32_t n_systems, const int64_t *offsets, const double *pos,
